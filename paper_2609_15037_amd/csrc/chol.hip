@@ -1,7 +1,7 @@
 // Blocked Cholesky factorisation and triangular inverse of the fp64 Gram
 // matrices of a refresh batch (CholeskyQR: Z = Q R with R^T R = Z^T Z, then
 // Q = Z R^{-1}). 64 x 64 blocks; every launch covers all matrices of the batch:
-//   block row 0:   diag      factor C_00 = R_00^T R_00 and invert R_00 (one wave per matrix)
+//   block row 0:   diag      factor C_00 = R_00^T R_00 and invert R_00 (one WG per matrix)
 //   block row k:   row(k)    C_kc -= sum_{j<k} R_jk^T R_jc for c >= k (one WG per block, k >= 1);
 //                            the WG of the diagonal block then factors C_kk and inverts
 //                            R_kk while the launch's other WGs still run
@@ -65,93 +65,216 @@ __device__ __forceinline__ void mfma_blk(const double (*A)[LDB], const double (*
 __device__ __forceinline__ int mfma_row(int r) { return 16 * (threadIdx.x >> 6) + 4 * r + ((threadIdx.x & 63) >> 4); }
 __device__ __forceinline__ int mfma_col(int jt) { return 16 * jt + (threadIdx.x & 15); }
 
-// One wave factors a 64 x 64 diagonal block held in LDS (D_ic at Dl[i * LD + c]) and
-// inverts its factor; it writes R_kk, X_kk = R_kk^{-1} and its fp32 copy. Lane c keeps
-// column c in registers (col[i] = D_ic); row j of R, which every column's update needs,
-// goes through LDS (over the block's own rows, which are in registers by then), where
-// all lanes read one address at a time (a broadcast). The LDS operations of one wave
-// take effect in program order, so no step needs a workgroup barrier. A ragged block is
-// padded with the identity, which factors and inverts to itself; take = 0 (an all-zero
-// Gram) gives R_kk = X_kk = I.
-//   factor, right-looking, column j = 0 .. kb-1:
-//     R_jj = sqrt(D_jj) (0 for a dependent column), R_jc = D_jc / R_jj (c > j),
-//     D_ac -= R_ja R_jc for a > j (lane c; for a > c this is the lower triangle,
-//     which follows the symmetric Schur complement and is not read);
-//   invert from the last row up, lane c: a_ic = sum_{t > i} R_it X_tc accumulated as
-//     the rows of X below i are finished (X_tc = 0 for t > c),
-//     X_cc = 1 / R_cc, X_ic = -a_ic / R_ii (i < c); a zero R_ii gives a zero row of X.
-// Each step's updates are kept inside the step (a wave-uniform branch per step ends its
-// basic block): left free, the compiler defers them into long chains that spill.
-template <int LD>
-__device__ __forceinline__ void diag_factor(double* Dl, int kb, bool take, double floor_piv, const RefDev& d,
-                                            int r0) {
-  const int w = d.w;
-  const int lane = threadIdx.x & 63;
-  const bool live = lane < kb;
-  double col[NB];
+// Factorisation of one 64 x 64 diagonal block and inverse of its factor by a workgroup of
+// four waves, in 16 x 16 sub-blocks. What bounds it is the chain of 64 pivots (a reciprocal
+// square root, then the next pivot's update), so only the 16 x 16 diagonal sub-blocks are
+// worked entry by entry, by one wave in registers (16 values per lane, pivots and rows
+// broadcast by v_readlane); everything between them is 16 x 16 x 16 products on fp64 MFMA.
+// Measured against the whole 64 x 64 block in one wave's registers (64 values per lane, rows
+// broadcast through LDS): a launch that factors one block 28 us instead of 74 (d = 256 layer),
+// k_chol_row over a Llama-2-7B-shaped layer 90 us on average instead of 151, its refresh 311
+// ms instead of 353 (four 300M-shaped layers 50.9 instead of 60.7, d = 256 10.5 instead of 13.4).
+constexpr int SB = 16, LDX = SB + 1;
+struct DiagLds {
+  double D[NB][LDB];        // the block; then R in its upper part and, in the strictly lower
+                            // sub-blocks (j, i), the sub-blocks X_ij (i < j) of X = R^{-1}
+  double Xd[4][SB][LDX];    // X_kk of the diagonal sub-blocks
+};
+
+// a lane's double as a wave-uniform value (the source lane is a compile-time constant)
+__device__ __forceinline__ double lane_d(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// An empty asm on a value keeps the compiler from deferring the updates before it to their
+// last use and from carrying the 120 row broadcasts and the lane masks of one loop into the
+// next: both spill.
+__device__ __forceinline__ void pin(double& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ int fresh(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// sqrt(v) and 1 / sqrt(v) of a positive v: the hardware's reciprocal square root refined by
+// two Goldschmidt iterations (g -> sqrt(v), 2 h -> 1 / sqrt(v)) and one residual step on g
+__device__ __forceinline__ void sqrt_rsqrt(double v, double& root, double& rinv) {
+  const double y = __builtin_amdgcn_rsq(v);
+  double g = v * y, h = 0.5 * y;
 #pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const double c = Dl[i * LD + lane];
-    col[i] = (take && live && i < kb) ? c : (i == lane ? 1.0 : 0.0);
+  for (int q = 0; q < 2; ++q) {
+    const double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
   }
+  root = fma(fma(-g, g, v), h, g);
+  rinv = 2.0 * h;
+}
+
+// One wave: factor the 16 x 16 sub-block (k, k) in place (R_kk, zero below its diagonal) and
+// write its inverse. Lane l works on column l % 16 (the four quarters of the wave alike).
+//   column j: R_jj = sqrt(D_jj) (0 for a dependent column), R_jc = D_jc / R_jj (c > j),
+//             D_ac -= R_ja R_jc for a > j
+//   inverse from the last row up: a_ic = sum_{t > i} R_it X_tc, X_cc = 1 / R_cc,
+//             X_ic = -a_ic / R_ii (i < c); a zero R_ii gives a zero row of X.
+__device__ __forceinline__ void factor16(DiagLds& S, int k, double floor_piv) {
+  const int lane = threadIdx.x & 63, c = lane & 15;
+  double col[SB], ri[SB];
 #pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    if (j >= kb) continue;
-    const double v = __shfl(col[j], j, 64);
-    const double rjj = v > floor_piv ? sqrt(v) : 0.0;   // 0: dependent column
-    const double q = col[j] / (rjj > 0.0 ? rjj : 1.0);
-    const double rjc = lane == j ? rjj : (lane > j && rjj > 0.0 ? q : 0.0);
+  for (int i = 0; i < SB; ++i) col[i] = S.D[SB * k + i][SB * k + c];
+#pragma unroll
+  for (int j = 0; j < SB; ++j) {
+    const double v = lane_d(col[j], j);
+    const bool dep = !(v > floor_piv);
+    double root, rinv;
+    sqrt_rsqrt(dep ? 1.0 : v, root, rinv);
+    root = dep ? 0.0 : root;
+    rinv = dep ? 0.0 : rinv;
+    ri[j] = rinv;
+    const int cj = fresh(c);
+    const double rjc = cj == j ? root : (cj > j ? col[j] * rinv : 0.0);
     col[j] = rjc;
-    Dl[j * LD + lane] = rjc;
 #pragma unroll
-    for (int a = j + 1; a < NB; ++a) col[a] -= Dl[j * LD + a] * rjc;
+    for (int a = j + 1; a < SB; ++a) pin(col[a] = fma(-lane_d(rjc, a), rjc, col[a]));
   }
-  if (live) {
+  double x[SB];
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
-      if (i < kb) d.C[(int64_t)(r0 + i) * w + r0 + lane] = col[i];
+  for (int i = 0; i < SB; ++i) {
+    pin(col[i]);
+    x[i] = 0.0;
   }
-  double* acc = col;   // a_ic, accumulated from the bottom row up
 #pragma unroll
-  for (int i = 0; i < NB; ++i) acc[i] = 0.0;
+  for (int t = SB - 1; t >= 0; --t) {
+    const int ct = fresh(c);
+    x[t] = ct >= t ? ((ct == t ? 1.0 : 0.0) - x[t]) * ri[t] : 0.0;
 #pragma unroll
-  for (int t = NB - 1; t >= 0; --t) {
-    if (t >= kb) continue;
-    const double rtt = Dl[t * LD + t];
-    const double num = lane == t ? 1.0 : -acc[t];
-    const double q = num / (rtt > 0.0 ? rtt : 1.0);
-    const double x = (lane >= t && rtt > 0.0) ? q : 0.0;
-    acc[t] = x;
-#pragma unroll
-    for (int i = 0; i < t; ++i) acc[i] += Dl[i * LD + t] * x;
+    for (int i = 0; i < t; ++i) pin(x[i] = fma(lane_d(col[i], t), x[t], x[i]));
   }
-  if (live) {
+  if (lane < SB) {
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
-      if (i < kb) {
-        const int64_t g = (int64_t)(r0 + i) * w + r0 + lane;
-        d.X[g] = acc[i];
-        d.Rinv[g] = (float)acc[i];
-      }
+    for (int i = 0; i < SB; ++i) {
+      S.D[SB * k + i][SB * k + c] = col[i];
+      S.Xd[k][i][c] = x[i];
+    }
   }
 }
 
-// Block 0 (no update before it): one wave per matrix; also records the pivot floor's
+// acc += op(A) B on 16 x 16 sub-blocks (v_mfma_f64_16x16x4): fa(i, t) = op(A)[i][t] and
+// fb(ks) = this lane's B operand of rows 4 ks .. 4 ks + 3. Register r of acc holds row
+// 4 r + l / 16, column l % 16, which is the B operand of ks = r: products chain through
+// registers.
+template <class FA, class FB>
+__device__ __forceinline__ void prod16(f64x4& acc, FA fa, FB fb) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks)
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fa(lane & 15, 4 * ks + (lane >> 4)), fb(ks), acc, 0, 0, 0);
+}
+
+// LDS accesses of one wave complete in program order: keep the compiler's order too
+__device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory"); }
+
+// S.D holds the updated block (identity in the padding of a ragged block; the identity as a
+// whole for an all-zero Gram, which gives R_kk = X_kk = I). Called by all 256 threads after a
+// barrier; writes R_kk, X_kk and the fp32 copy of X_kk.
+__device__ __forceinline__ void diag_factor(DiagLds& S, int kb, double floor_piv, const RefDev& d, int r0) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lr = lane >> 4, lc = lane & 15;
+  const f64x4 zero = f64x4{0.0, 0.0, 0.0, 0.0};
+  if (wave == 0) factor16(S, 0, floor_piv);
+#pragma unroll 1
+  for (int k = 0; k < 3; ++k) {
+    __syncthreads();
+    if (wave < 3 - k) {   // row k of R: R_kj = X_kk^T D_kj
+      const int j = k + 1 + wave;
+      f64x4 acc = zero;
+      prod16(acc, [&](int i, int t) { return S.Xd[k][t][i]; },
+             [&](int ks) { return S.D[SB * k + 4 * ks + lr][SB * j + lc]; });
+#pragma unroll
+      for (int r = 0; r < 4; ++r) S.D[SB * k + 4 * r + lr][SB * j + lc] = acc[r];
+    }
+    __syncthreads();
+    // D_ij -= R_ki^T R_kj for k < i <= j: the next diagonal sub-block by wave 0, which then
+    // factors it while the other waves update the rest
+    int q = 0;
+    for (int i = k + 1; i < 4; ++i)
+      for (int j = i; j < 4; ++j, ++q) {
+        if ((q == 0 ? 0 : 1 + (q - 1) % 3) != wave) continue;
+        f64x4 acc = zero;
+        prod16(acc, [&](int a, int t) { return S.D[SB * k + t][SB * i + a]; },
+               [&](int ks) { return S.D[SB * k + 4 * ks + lr][SB * j + lc]; });
+#pragma unroll
+        for (int r = 0; r < 4; ++r) S.D[SB * i + 4 * r + lr][SB * j + lc] -= acc[r];
+      }
+    if (wave == 0) {
+      wave_lds_order();
+      factor16(S, k + 1, floor_piv);
+    }
+  }
+  __syncthreads();
+  // X by doubling: X_01 = -X_00 (R_01 X_11) and X_23 likewise, then the 2 x 2 sub-blocks
+  // X_ij = -sum_{u = i, 1} X_iu T_uj, T_uj = sum_{t = 2 .. j} R_ut X_tj (i < 2 <= j)
+  auto X = [&](int i, int j, int a, int b) { return i == j ? S.Xd[i][a][b] : S.D[SB * j + a][SB * i + b]; };
+  auto R = [&](int i, int j, int a, int b) { return S.D[SB * i + a][SB * j + b]; };
+  auto put = [&](int i, int j, const f64x4& acc) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) S.D[SB * j + 4 * r + lr][SB * i + lc] = -acc[r];
+  };
+  if (wave < 2) {
+    const int i = 2 * wave, j = i + 1;
+    f64x4 T = zero, acc = zero;
+    prod16(T, [&](int a, int t) { return R(i, j, a, t); }, [&](int ks) { return X(j, j, 4 * ks + lr, lc); });
+    prod16(acc, [&](int a, int t) { return X(i, i, a, t); }, [&](int ks) { return T[ks]; });
+    put(i, j, acc);
+  }
+  __syncthreads();
+  {
+    const int i = wave >> 1, j = 2 + (wave & 1);
+    f64x4 acc = zero;
+    for (int u = i; u < 2; ++u) {
+      f64x4 T = zero;
+      for (int t = 2; t <= j; ++t)
+        prod16(T, [&](int a, int b) { return R(u, t, a, b); }, [&](int ks) { return X(t, j, 4 * ks + lr, lc); });
+      prod16(acc, [&](int a, int b) { return X(i, u, a, b); }, [&](int ks) { return T[ks]; });
+    }
+    put(i, j, acc);   // sub-blocks (j, i): read by nobody before the barrier
+  }
+  __syncthreads();
+  const int w = d.w;
+  for (int e = threadIdx.x; e < NB * NB; e += 256) {
+    const int i = e >> 6, j = e & 63, bi = i >> 4, bj = j >> 4;
+    if (i >= kb || j >= kb) continue;
+    const int64_t g = (int64_t)(r0 + i) * w + r0 + j;
+    const double x = bi > bj ? 0.0 : X(bi, bj, i & 15, j & 15);
+    d.C[g] = bi > bj ? 0.0 : S.D[i][j];
+    d.X[g] = x;
+    d.Rinv[g] = (float)x;
+  }
+}
+
+// Block 0 (no update before it): one workgroup per matrix; also records the pivot floor's
 // reference, the largest diagonal entry of the untouched Gram.
-__global__ __launch_bounds__(64) void k_chol_diag(const RefDev* __restrict__ ds) {
-  __shared__ double Dl[NB][NB];
+__global__ __launch_bounds__(256) void k_chol_diag(const RefDev* __restrict__ ds) {
+  __shared__ DiagLds S;
   const RefDev& d = ds[blockIdx.x];
   const int w = d.w;
-  const int lane = threadIdx.x;
+  const int tid = threadIdx.x;
+  const int kb = bsz(w, 0);
   double mx = 0.0;
-  for (int i = lane; i < w; i += 64) mx = fmax(mx, d.C[(int64_t)i * w + i]);
+  for (int i = tid; i < w; i += 256) mx = fmax(mx, d.C[(int64_t)i * w + i]);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
-  if (lane == 0) d.cmax[0] = mx;
-  const int kb = bsz(w, 0);
-  const int lc = min(lane, kb - 1);   // clamped: every lane loads in bounds
-  for (int i = 0; i < NB; ++i) Dl[i][lane] = d.C[(int64_t)min(i, kb - 1) * w + lc];
-  diag_factor<NB>(&Dl[0][0], kb, mx > 0.0, mx * 1e-13, d, 0);
+  double* red = &S.Xd[0][0][0];   // free until the factorisation
+  if ((tid & 63) == 0) red[tid >> 6] = mx;
+  __syncthreads();
+  mx = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  if (tid == 0) d.cmax[0] = mx;
+  for (int e = tid; e < NB * NB; e += 256) {
+    const int i = e >> 6, j = e & 63;
+    S.D[i][j] = (mx > 0.0 && i < kb && j < kb) ? d.C[(int64_t)i * w + j] : (i == j ? 1.0 : 0.0);
+  }
+  __syncthreads();
+  diag_factor(S, kb, mx * 1e-13, d, 0);
 }
 
 __global__ __launch_bounds__(256, 4) void k_chol_panel(const RefDev* __restrict__ ds, const uint32_t* __restrict__ pref,
@@ -215,7 +338,8 @@ __global__ __launch_bounds__(256, 2) void k_chol_row(const RefDev* __restrict__ 
   const int w = d.w;
   if (diag && k >= nblk(w)) return;
   const int c = diag ? k : k + 1 + (int)(t - n - pref[mi]);
-  __shared__ double Rb[NB][LDB];
+  __shared__ DiagLds S;
+  double (*Rb)[LDB] = S.D;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double av[NB / 4], an[NB / 4], pb[16];
   auto fetch = [&](int j, double (&a)[NB / 4]) {
@@ -272,18 +396,19 @@ __global__ __launch_bounds__(256, 2) void k_chol_row(const RefDev* __restrict__ 
       }
     return;
   }
-  // diagonal block: the updated C_kk goes to LDS (Rb is free: the K loop ended with a
-  // barrier) and wave 0 factors it while the other workgroups of the launch run on
+  // diagonal block: the updated C_kk goes to LDS (free: the K loop ended with a barrier)
+  // and is factored while the other workgroups of the launch run on
   const double cmax = d.cmax[0];
+  const int kb = bsz(w, k);
 #pragma unroll
   for (int jt = 0; jt < 4; ++jt)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int i = mfma_row(r), j = mfma_col(jt), row = k * NB + i, col = k * NB + j;
-      Rb[i][j] = (row < w && col < w) ? d.C[(int64_t)row * w + col] - acc[jt][r] : 0.0;
+      Rb[i][j] = (cmax > 0.0 && i < kb && j < kb) ? d.C[(int64_t)row * w + col] - acc[jt][r] : (i == j ? 1.0 : 0.0);
     }
   __syncthreads();
-  if (wave == 0) diag_factor<LDB>(&Rb[0][0], bsz(w, k), cmax > 0.0, cmax * 1e-13, d, k * NB);
+  diag_factor(S, kb, cmax * 1e-13, d, k * NB);
 }
 
 // Triangular inverse X = R^{-1} by recursive doubling over the 64 x 64 blocks. Level l
@@ -385,7 +510,7 @@ int chol_blocks(int32_t w) { return (w + NB - 1) / NB; }
 
 hipError_t launch_chol_diag(const RefDev* d, int n, hipStream_t st) {
   if (!n) return hipSuccess;
-  hipLaunchKernelGGL(k_chol_diag, dim3(n), dim3(64), 0, st, d);
+  hipLaunchKernelGGL(k_chol_diag, dim3(n), dim3(256), 0, st, d);
   return hipGetLastError();
 }
 hipError_t launch_chol_panel(const RefDev* d, const uint32_t* pref, int n, uint32_t total, int k, hipStream_t st) {
