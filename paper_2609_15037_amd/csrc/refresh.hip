@@ -573,9 +573,12 @@ __global__ __launch_bounds__(256) void k_r_colmajor(const RefDev* __restrict__ d
 
 // ------------------------------------------------------------------ finalize
 // After the Jacobi sweeps Zc = R J has orthogonal columns whose norms are the Ritz
-// values; the Ritz vectors are Q (R J) / norm. k_finalize_order (one workgroup per
-// matrix): column norms, order by decreasing norm, Bt = the first r columns,
-// normalised (zero for numerically null directions). A GEMM then forms Pw = Q Bt^T.
+// values; the Ritz vectors are Q (R J) / norm. k_col_norms, k_order, k_ritz_basis: column
+// norms, order by decreasing norm, Bt = the first r columns, normalised (zero for numerically
+// null directions). A GEMM then forms Pw = Q Bt^T. All three run NORM_COLS columns per
+// workgroup: the ordering and the normalisation are dependent reads of w doubles per column,
+// bound by latency: the latter two took 4.1 ms of a Llama-2-7B-shaped layer's refresh and 320 us
+// of four 300M-shaped ones' in one workgroup per matrix, and now take under 50 and 20 us.
 // k_finalize_out: make each column's largest-magnitude entry positive (lowest index on
 // ties) and write P (fp32 master and both operand copies). An all-zero iterate (V == 0) keeps the previous projector, or yields the
 // first r canonical basis vectors when there is none; numerically null directions
@@ -607,49 +610,62 @@ __global__ __launch_bounds__(256) void k_col_norms(const RefDev* __restrict__ ds
   }
 }
 
-__global__ __launch_bounds__(256) void k_finalize_order(const RefDev* __restrict__ ds) {
-  const RefDev& d = ds[blockIdx.x];
-  const int tid = threadIdx.x;
-  const int64_t L = d.jl;
-  // rank of every column by decreasing norm (ties by index), norms read from LDS
-  __shared__ double nl[2048];
-  const bool in_lds = d.wpad <= 2048;
-  // a norm that is not a finite number >= 0 ranks as -1, so the keys are totally ordered
-  // and the ranks form a permutation of 0 .. wpad-1 (every entry of order is written)
+// Order of the columns by decreasing norm (ties by index): NORM_COLS columns per workgroup, 16
+// lanes counting the columns ahead of one. A norm that is not a finite number >= 0 ranks as
+// -1, so the keys are totally ordered and the ranks form a permutation of 0 .. wpad-1 (every
+// entry of order is written).
+static_assert(NORM_COLS * 16 == 256, "sixteen lanes per column");
+__global__ __launch_bounds__(256) void k_order(const RefDev* __restrict__ ds, int n) {
+  const uint32_t t = blockIdx.x;
+  int lo = 0, hi = n - 1;
+  while (lo < hi) { int mid = (lo + hi + 1) >> 1; if (ds[mid].tile_norm <= t) lo = mid; else hi = mid - 1; }
+  const RefDev& d = ds[lo];
+  const int sub = threadIdx.x & 15, c = (int)(t - d.tile_norm) * NORM_COLS + (threadIdx.x >> 4);
   auto key = [](double v) { return (v >= 0.0 && v <= 1.7976931348623157e308) ? v : -1.0; };
-  if (in_lds)
-    for (int c = tid; c < d.wpad; c += 256) nl[c] = key(d.norms[c]);
-  __syncthreads();
-  for (int c = tid; c < d.wpad; c += 256) {
-    const double nc = in_lds ? nl[c] : key(d.norms[c]);
-    int rank = 0;
-    for (int c2 = 0; c2 < d.wpad; ++c2) {
-      const double n2 = in_lds ? nl[c2] : key(d.norms[c2]);
-      rank += (n2 > nc) || (n2 == nc && c2 < c);
-    }
-    d.order[rank] = c;
+  const double nc = c < d.wpad ? key(d.norms[c]) : 0.0;
+  int rank = 0;
+  for (int c2 = sub; c2 < d.wpad; c2 += 16) {
+    const double n2 = key(d.norms[c2]);
+    rank += (n2 > nc) || (n2 == nc && c2 < c);
   }
-  __syncthreads();
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) rank += __shfl_xor(rank, o, 16);
+  if (sub == 0 && c < d.wpad) d.order[rank] = c;
+}
+
+// Bt = the first r columns in that order, normalised: NORM_COLS of them per workgroup, one wave
+// per column at a time. The matrix's first workgroup writes its refresh record.
+__global__ __launch_bounds__(256) void k_ritz_basis(const RefDev* __restrict__ ds, int n) {
+  const uint32_t t = blockIdx.x;
+  int lo = 0, hi = n - 1;
+  while (lo < hi) { int mid = (lo + hi + 1) >> 1; if (ds[mid].tile_norm <= t) lo = mid; else hi = mid - 1; }
+  const RefDev& d = ds[lo];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j0 = (int)(t - d.tile_norm) * NORM_COLS;
   const double nmax = d.norms[d.order[0]];
-  int kept = 0;
-  for (int j = 0; j < d.r; ++j) {
+  for (int j = j0 + wave; j < j0 + NORM_COLS && j < d.r; j += 4) {
     const int src = d.order[j];
     const double nrm = d.norms[src];
     const bool deg = null_dir(nrm, nmax);
-    kept += deg ? 0 : 1;
-    const double* col = d.Zc + (int64_t)src * L;
-    for (int64_t i = tid; i < d.w; i += 256) d.Bt[(int64_t)j * d.w + i] = deg ? 0.f : (float)(col[i] / nrm);
+    const double* col = d.Zc + (int64_t)src * d.jl;
+    for (int i = lane; i < d.w; i += 64) d.Bt[(int64_t)j * d.w + i] = deg ? 0.f : (float)(col[i] / nrm);
   }
-  if (tid == 0) {
-    // the first sweep whose measured pair cosines all fell below the tolerance ended the
-    // iteration (later sweeps returned at once and left their entries at zero)
-    int sw = 0;
-    while (sw < d.max_sweeps && !(__uint_as_float(d.off[sw]) < (float)JAC_TOL)) ++sw;
-    const bool conv = sw < d.max_sweeps;
-    d.info[0] = conv ? sw + 1 : d.max_sweeps;
-    d.info[1] = conv ? 1 : 0;
-    d.info[2] = kept;
-    d.info[3] = (int32_t)d.off[conv ? sw : d.max_sweeps - 1];
+  if (j0 == 0 && wave == 0) {
+    int kept = 0;
+    for (int j = lane; j < d.r; j += 64) kept += null_dir(d.norms[d.order[j]], nmax) ? 0 : 1;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) kept += __shfl_xor(kept, o, 64);
+    if (lane == 0) {
+      // the first sweep whose measured pair cosines all fell below the tolerance ended the
+      // iteration (later sweeps returned at once and left their entries at zero)
+      int sw = 0;
+      while (sw < d.max_sweeps && !(__uint_as_float(d.off[sw]) < (float)JAC_TOL)) ++sw;
+      const bool conv = sw < d.max_sweeps;
+      d.info[0] = conv ? sw + 1 : d.max_sweeps;
+      d.info[1] = conv ? 1 : 0;
+      d.info[2] = kept;
+      d.info[3] = (int32_t)d.off[conv ? sw : d.max_sweeps - 1];
+    }
   }
 }
 
@@ -999,7 +1015,8 @@ uint32_t norm_tiles(int32_t wpad) { return (uint32_t)((wpad + NORM_COLS - 1) / N
 hipError_t launch_finalize_order(const RefDev* d, int n, uint32_t norm_total, hipStream_t st) {
   if (!n) return hipSuccess;
   hipLaunchKernelGGL(k_col_norms, dim3(norm_total), dim3(256), 0, st, d, n);
-  hipLaunchKernelGGL(k_finalize_order, dim3(n), dim3(256), 0, st, d);
+  hipLaunchKernelGGL(k_order, dim3(norm_total), dim3(256), 0, st, d, n);
+  hipLaunchKernelGGL(k_ritz_basis, dim3(norm_total), dim3(256), 0, st, d, n);
   return hipGetLastError();
 }
 hipError_t launch_finalize_out(const RefDev* d, int n, int32_t rmax, hipStream_t st) {
