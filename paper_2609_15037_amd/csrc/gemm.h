@@ -79,7 +79,7 @@ struct GemmUniform {
   float beta1, beta2, adam_eps;
   float lr, scale;
   int32_t moment_bf16;  // EP_ADAM: the moments are stored in bf16
-  int32_t pad_;
+  int32_t lgB;          // log2(B) when B is a power of two, else -1 (set by launch_gemm)
 };
 
 template <int KIND> struct GemmTile;
@@ -105,7 +105,16 @@ __device__ __forceinline__ void tile_coords(uint32_t lt, uint32_t tiles_m, uint3
 uint32_t gemm_tiles_m(int kind, int64_t M);
 uint32_t gemm_tiles_n(int kind, int64_t N);
 hipError_t launch_gemm(int kind, int amode, int bmode, int ep, const GemmProb* probs_dev, int nprob,
-                       uint32_t total_tiles, const GemmUniform& u, hipStream_t st);
+                       uint32_t total_tiles, const GemmUniform& u, hipStream_t st, int tile = 128);
+// fp32 kind: the tile (128 or 64) a list of problems, laid out for 128 x 128 tiles (`total` of
+// them), is launched with; for 64 the list's prefixes and the total are rewritten.
+// 64 up to 4096 tiles of 128 x 128 (eight rounds of the 512 that run at once): a short list leaves
+// CUs idle or ends in a nearly empty round, and a quarter-size tile fills them (seven d = 256
+// matrices: projections 45 and 37 -> 17 and 16 us, update 19 -> 7 us; 96 to 528 tiles at 300M
+// shapes 251 and 289 -> 162 and 195 us per product; 1032 to 1284 tiles of a 7B-shaped layer 1.77
+// and 2.03 -> 1.72 and 1.99 ms). At 12352 tiles the larger tile's operand reuse wins (3.38
+// against 4.31 ms). Both tiles add a product's terms in the same order.
+int gemm_f32_fit(GemmProb* probs, int n, uint32_t* total);
 
 // Large-tile bf16 path (gemm_nt.hip): A (M x K) and B (N x K) bf16, K-contiguous,
 // EP_ADAM, EP_UPDATE, EP_STORE or EP_STORE_BF16; 256-row tiles.

@@ -24,7 +24,9 @@ namespace {
 
 constexpr int BF_LD = 64 + 8;     // bf16 LDS row stride (elements)
 constexpr int F_LDK = 32 + 1;     // fp32 LDS row stride, K-contiguous layout
-constexpr int F_LDT = 128 + 32;   // fp32 LDS row stride, M/N-contiguous layout
+// fp32 LDS row stride of a BT-wide tile, M/N-contiguous layout (32 modulo the 64 banks: the two
+// half-waves of a fragment read, one row apart, use different banks)
+constexpr int f_ldt(int BT) { return BT + 32; }
 
 __device__ __forceinline__ int find_prob(const GemmProb* probs, int n, uint32_t t) {
   int lo = 0, hi = n - 1;
@@ -33,6 +35,12 @@ __device__ __forceinline__ int find_prob(const GemmProb* probs, int n, uint32_t 
     if (probs[mid].tile_start <= t) lo = mid; else hi = mid - 1;
   }
   return lo;
+}
+
+// magnitude block of column x (x < 2^31): a shift when B is a power of two (U.lgB), else a
+// 32-bit division; as a 64-bit division by the runtime B it was most of the loads' address work
+__device__ __forceinline__ uint32_t blk(const GemmUniform& U, int64_t x) {
+  return U.lgB >= 0 ? (uint32_t)x >> U.lgB : (uint32_t)x / (uint32_t)U.B;
 }
 
 // ------------------------------------------------------------------ loads
@@ -87,7 +95,7 @@ struct BfA {
   float s[8];
   uint4 u[(AM == A_KC) ? TASKS : 1];
 
-  __device__ __forceinline__ void load(const GemmProb& P, const Rs& R, int64_t row0, int64_t k0, int B) {
+  __device__ __forceinline__ void load(const GemmProb& P, const Rs& R, int64_t row0, int64_t k0, const GemmUniform& U) {
     const int tid = threadIdx.x;
     if constexpr (AM == A_G_ROW) {
       static_assert(TASKS == 4, "A_G_ROW expects 4 tasks per thread");
@@ -102,11 +110,11 @@ struct BfA {
           const float4 x0 = bld4(R.a, off), x1 = bld4(R.a, off + 16);
           d[0] = x0.x; d[1] = x0.y; d[2] = x0.z; d[3] = x0.w;
           d[4] = x1.x; d[5] = x1.y; d[6] = x1.z; d[7] = x1.w;
-          s[u] = P.inv ? bld1(R.inv, (uint32_t)((gr * P.inv_ld + gk / B) * 4)) : 1.f;
+          s[u] = P.inv ? bld1(R.inv, (uint32_t)((gr * P.inv_ld + blk(U, gk)) * 4)) : 1.f;
         } else {
 #pragma unroll
           for (int e = 0; e < 8; ++e) d[e] = (gr < P.M && gk + e < P.K) ? G[gr * P.lda + gk + e] : 0.f;
-          s[u] = (P.inv && gr < P.M && gk < P.K) ? P.inv[gr * P.inv_ld + gk / B] : 1.f;
+          s[u] = (P.inv && gr < P.M && gk < P.K) ? P.inv[gr * P.inv_ld + blk(U, gk)] : 1.f;
         }
       }
     } else if constexpr (AM == A_G_TRANS) {
@@ -121,11 +129,11 @@ struct BfA {
         if constexpr (FAST) {
           const float4 x = bld4(R.a, (uint32_t)((gk * P.lda + gi) * 4));
           d[0] = x.x; d[1] = x.y; d[2] = x.z; d[3] = x.w;
-          s[e] = P.inv ? bld1(R.inv, (uint32_t)((gk * P.inv_ld + gi / B) * 4)) : 1.f;
+          s[e] = P.inv ? bld1(R.inv, (uint32_t)((gk * P.inv_ld + blk(U, gi)) * 4)) : 1.f;
         } else {
 #pragma unroll
           for (int q = 0; q < 4; ++q) d[q] = (gk < P.K && gi + q < P.M) ? G[gk * P.lda + gi + q] : 0.f;
-          s[e] = (P.inv && gk < P.K && gi < P.M) ? P.inv[gk * P.inv_ld + gi / B] : 1.f;
+          s[e] = (P.inv && gk < P.K && gi < P.M) ? P.inv[gk * P.inv_ld + blk(U, gi)] : 1.f;
         }
       }
     } else {
@@ -148,10 +156,10 @@ struct BfA {
     }
   }
 
-  __device__ __forceinline__ void store(const GemmProb& P, int64_t row0, int64_t k0, int B, bf16* As) const {
+  __device__ __forceinline__ void store(const GemmProb& P, int64_t row0, int64_t k0, const GemmUniform& U, bf16* As) const {
     const int tid = threadIdx.x;
     if constexpr (AM == A_G_ROW) {
-      const bool per_elem = (P.inv != nullptr) && (B & 7);
+      const bool per_elem = (P.inv != nullptr) && (U.B & 7);
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int idx = tid + NT * u;
@@ -161,14 +169,14 @@ struct BfA {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           float sc = s[u];
-          if (per_elem && gr < P.M && gk + e < P.K) sc = P.inv[gr * P.inv_ld + (gk + e) / B];
+          if (per_elem && gr < P.M && gk + e < P.K) sc = P.inv[gr * P.inv_ld + blk(U, gk + e)];
           const float v = f[u * 8 + e] * sc;
           t[e] = f2bf((FAST && gk + e >= P.K) ? 0.f : v);
         }
         *reinterpret_cast<bf16x8*>(As + i * BF_LD + kc) = t;
       }
     } else if constexpr (AM == A_G_TRANS) {
-      const bool per_elem = (P.inv != nullptr) && (B & 3);
+      const bool per_elem = (P.inv != nullptr) && (U.B & 3);
       const int ig = tid % (BM / 4), kc = (tid / (BM / 4)) * 8;
       const int64_t gi = row0 + ig * 4;
 #pragma unroll
@@ -179,7 +187,7 @@ struct BfA {
         for (int e = 0; e < 8; ++e) {
           float sc = s[e];
           const int64_t gk = k0 + kc + e;
-          if (per_elem && gk < P.K && colok) sc = P.inv[gk * P.inv_ld + (gi + q) / B];
+          if (per_elem && gk < P.K && colok) sc = P.inv[gk * P.inv_ld + blk(U, gi + q)];
           const float v = f[e * 4 + q] * sc;
           t[e] = f2bf((FAST && !colok) ? 0.f : v);
         }
@@ -232,80 +240,82 @@ struct BfB {
   }
 };
 
-// ------------------------------------------------------------------ fp32 kind (128 x 128, 4 waves)
+// ------------------------------------------------------------------ fp32 kind (BT x BT tiles, 4 waves)
 constexpr int FNT = 256;
 
-template <int AM, bool FAST>
+template <int AM, int BT, bool FAST>
 struct FA {
-  float f[16];
-  float s[4];
-  __device__ __forceinline__ void load(const GemmProb& P, const Rs& R, int64_t row0, int64_t k0, int B) {
+  static constexpr int TASKS = BT * 32 / 4 / FNT;   // 16-byte loads per thread and K step
+  static constexpr int GRP = BT / 4, F_LDT = f_ldt(BT);
+  float f[4 * TASKS];
+  float s[TASKS];
+  __device__ __forceinline__ void load(const GemmProb& P, const Rs& R, int64_t row0, int64_t k0, const GemmUniform& U) {
     const int tid = threadIdx.x;
     const float* A = (const float*)P.a;
     if constexpr (AM == A_G_TRANS) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < TASKS; ++u) {
         const int idx = tid + FNT * u;
-        const int64_t gi = row0 + (idx & 31) * 4, gk = k0 + (idx >> 5);
+        const int64_t gi = row0 + (idx % GRP) * 4, gk = k0 + idx / GRP;
         float* d = &f[u * 4];
         if constexpr (FAST) {
           const float4 x = bld4(R.a, (uint32_t)((gk * P.lda + gi) * 4));
           d[0] = x.x; d[1] = x.y; d[2] = x.z; d[3] = x.w;
-          s[u] = P.inv ? bld1(R.inv, (uint32_t)((gk * P.inv_ld + gi / B) * 4)) : 1.f;
+          s[u] = P.inv ? bld1(R.inv, (uint32_t)((gk * P.inv_ld + blk(U, gi)) * 4)) : 1.f;
         } else {
 #pragma unroll
           for (int q = 0; q < 4; ++q) d[q] = (gk < P.K && gi + q < P.M) ? A[gk * P.lda + gi + q] : 0.f;
-          s[u] = (P.inv && gk < P.K && gi < P.M) ? P.inv[gk * P.inv_ld + gi / B] : 1.f;
+          s[u] = (P.inv && gk < P.K && gi < P.M) ? P.inv[gk * P.inv_ld + blk(U, gi)] : 1.f;
         }
       }
     } else {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < TASKS; ++u) {
         const int idx = tid + FNT * u;
         const int64_t gr = row0 + (idx >> 3), gk = k0 + (idx & 7) * 4;
         float* d = &f[u * 4];
         if constexpr (FAST) {
           const float4 x = bld4(R.a, (uint32_t)((gr * P.lda + gk) * 4));
           d[0] = x.x; d[1] = x.y; d[2] = x.z; d[3] = x.w;
-          if constexpr (AM == A_G_ROW) s[u] = P.inv ? bld1(R.inv, (uint32_t)((gr * P.inv_ld + gk / B) * 4)) : 1.f;
+          if constexpr (AM == A_G_ROW) s[u] = P.inv ? bld1(R.inv, (uint32_t)((gr * P.inv_ld + blk(U, gk)) * 4)) : 1.f;
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e) d[e] = (gr < P.M && gk + e < P.K) ? A[gr * P.lda + gk + e] : 0.f;
           if constexpr (AM == A_G_ROW)
-            s[u] = (P.inv && gr < P.M && gk < P.K) ? P.inv[gr * P.inv_ld + gk / B] : 1.f;
+            s[u] = (P.inv && gr < P.M && gk < P.K) ? P.inv[gr * P.inv_ld + blk(U, gk)] : 1.f;
         }
       }
     }
   }
-  __device__ __forceinline__ void store(const GemmProb& P, int64_t row0, int64_t k0, int B, float* As) const {
+  __device__ __forceinline__ void store(const GemmProb& P, int64_t row0, int64_t k0, const GemmUniform& U, float* As) const {
     const int tid = threadIdx.x;
     if constexpr (AM == A_G_TRANS) {
-      const bool per_elem = (P.inv != nullptr) && (B & 3);
+      const bool per_elem = (P.inv != nullptr) && (U.B & 3);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < TASKS; ++u) {
         const int idx = tid + FNT * u;
-        const int ig = idx & 31, kr = idx >> 5;
+        const int ig = idx % GRP, kr = idx / GRP;
         const int64_t gi = row0 + ig * 4, gk = k0 + kr;
         float v[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           float sc = s[u];
-          if (per_elem && gk < P.K && gi + q < P.M) sc = P.inv[gk * P.inv_ld + (gi + q) / B];
+          if (per_elem && gk < P.K && gi + q < P.M) sc = P.inv[gk * P.inv_ld + blk(U, gi + q)];
           v[q] = (FAST && gi + q >= P.M) ? 0.f : f[u * 4 + q] * sc;
         }
         *reinterpret_cast<float4*>(As + kr * F_LDT + ig * 4) = make_float4(v[0], v[1], v[2], v[3]);
       }
     } else {
-      const bool per_elem = (AM == A_G_ROW) && (P.inv != nullptr) && (B & 3);
+      const bool per_elem = (AM == A_G_ROW) && (P.inv != nullptr) && (U.B & 3);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < TASKS; ++u) {
         const int idx = tid + FNT * u;
         const int i = idx >> 3, kq = (idx & 7) * 4;
         const int64_t gr = row0 + i, gk = k0 + kq;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           float sc = (AM == A_G_ROW) ? s[u] : 1.f;
-          if (per_elem && gr < P.M && gk + e < P.K) sc = P.inv[gr * P.inv_ld + (gk + e) / B];
+          if (per_elem && gr < P.M && gk + e < P.K) sc = P.inv[gr * P.inv_ld + blk(U, gk + e)];
           As[i * F_LDK + kq + e] = (FAST && gk + e >= P.K) ? 0.f : f[u * 4 + e] * sc;
         }
       }
@@ -313,18 +323,19 @@ struct FA {
   }
 };
 
-template <int BMODE, bool FAST>
+template <int BMODE, int BT, bool FAST>
 struct FB {
-  float f[16];
+  static constexpr int TASKS = BT * 32 / 4 / FNT, GRP = BT / 4, F_LDT = f_ldt(BT);
+  float f[4 * TASKS];
   __device__ __forceinline__ void load(const GemmProb& P, const Rs& R, int64_t col0, int64_t k0) {
     const int tid = threadIdx.x;
     const float* Bp = (const float*)P.b;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < TASKS; ++u) {
       const int idx = tid + FNT * u;
       float* d = &f[u * 4];
       if constexpr (BMODE == B_NC) {
-        const int64_t gj = col0 + (idx & 31) * 4, gk = k0 + (idx >> 5);
+        const int64_t gj = col0 + (idx % GRP) * 4, gk = k0 + idx / GRP;
         if constexpr (FAST) {
           const float4 x = bld4(R.b, (uint32_t)((gk * P.ldb + gj) * 4));
           d[0] = x.x; d[1] = x.y; d[2] = x.z; d[3] = x.w;
@@ -347,14 +358,14 @@ struct FB {
   __device__ __forceinline__ void store(const GemmProb& P, int64_t col0, int64_t k0, float* Bs) const {
     const int tid = threadIdx.x;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < TASKS; ++u) {
       const int idx = tid + FNT * u;
       if constexpr (BMODE == B_NC) {
-        const int64_t gj = col0 + (idx & 31) * 4;
+        const int64_t gj = col0 + (idx % GRP) * 4;
         float v[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) v[q] = (FAST && gj + q >= P.N) ? 0.f : f[u * 4 + q];
-        *reinterpret_cast<float4*>(Bs + (idx >> 5) * F_LDT + (idx & 31) * 4) = make_float4(v[0], v[1], v[2], v[3]);
+        *reinterpret_cast<float4*>(Bs + (idx / GRP) * F_LDT + (idx % GRP) * 4) = make_float4(v[0], v[1], v[2], v[3]);
       } else {
         const int j = idx >> 3, kq = (idx & 7) * 4;
         const int64_t gk = k0 + kq;
@@ -372,21 +383,22 @@ struct FB {
 // i.e. four consecutive columns per (mi, ni, g = j/4).
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-template <int KIND, int EP, int WN>
+template <int KIND, int EP, int WN, int MB>
 __device__ __forceinline__ void epilogue(const GemmProb& P, const GemmUniform& U, int64_t row0, int64_t col0,
-                                         const f32x16 (&acc)[2][2]) {
+                                         const f32x16 (&acc)[MB][MB]) {
+  constexpr int WT = 32 * MB;   // a wave's sub-tile
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / WN, wn = wave % WN;
   double s_gr = 0.0, s_rr = 0.0, s_gg = 0.0;   // EP_ALIGN partial sums
 #pragma unroll
-  for (int mi = 0; mi < 2; ++mi) {
-    const int64_t row = row0 + wm * 64 + mi * 32 + (lane & 31);
+  for (int mi = 0; mi < MB; ++mi) {
+    const int64_t row = row0 + wm * WT + mi * 32 + (lane & 31);
     if (row >= P.M) continue;
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni)
+    for (int ni = 0; ni < MB; ++ni)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int64_t col = col0 + wn * 64 + ni * 32 + 8 * g + 4 * (lane >> 5);
+        const int64_t col = col0 + wn * WT + ni * 32 + 8 * g + 4 * (lane >> 5);
         if (col >= P.N) continue;
         float v[4] = {acc[mi][ni][4 * g + 0], acc[mi][ni][4 * g + 1], acc[mi][ni][4 * g + 2], acc[mi][ni][4 * g + 3]};
         const int64_t idx = row * P.ldc + col;
@@ -403,6 +415,8 @@ __device__ __forceinline__ void epilogue(const GemmProb& P, const GemmUniform& U
           // G_recon = Rep_B(M) * (projected direction); the gradient is read, never written
           const float* Gr = (const float*)P.c;
           const float* ivr = P.inv ? P.inv + row * P.inv_ld : nullptr;
+          const bool one = (U.B & 3) == 0;   // the four columns share a block
+          const float mag0 = ivr && one ? 1.f / ivr[blk(U, col)] - U.decomp_eps : 1.f;
           float gv[4] = {0.f, 0.f, 0.f, 0.f};
           if (full) {
             const float4 x = *reinterpret_cast<const float4*>(Gr + idx);
@@ -413,7 +427,7 @@ __device__ __forceinline__ void epilogue(const GemmProb& P, const GemmUniform& U
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             if (col + q >= P.N) continue;
-            const float mag = ivr ? 1.f / ivr[(col + q) / U.B] - U.decomp_eps : 1.f;
+            const float mag = ivr && !one ? 1.f / ivr[blk(U, col + q)] - U.decomp_eps : mag0;
             const double rec = (double)mag * (double)v[q], g = (double)gv[q];
             s_gr += g * rec;
             s_rr += rec * rec;
@@ -474,9 +488,9 @@ __device__ __forceinline__ void epilogue(const GemmProb& P, const GemmUniform& U
           if (!dmr) {
             mag[0] = mag[1] = mag[2] = mag[3] = 1.f;
           } else if ((U.B & 3) == 0) {
-            mag[0] = mag[1] = mag[2] = mag[3] = dmr[col / U.B];
+            mag[0] = mag[1] = mag[2] = mag[3] = dmr[blk(U, col)];
           } else {
-            for (int q = 0; q < 4; ++q) mag[q] = (col + q < P.N) ? dmr[(col + q) / U.B] : 1.f;
+            for (int q = 0; q < 4; ++q) mag[q] = (col + q < P.N) ? dmr[blk(U, col + q)] : 1.f;
           }
           float wv[4] = {0.f, 0.f, 0.f, 0.f};
           if (U.weight_bf16) {
@@ -535,11 +549,12 @@ __device__ __forceinline__ void epilogue(const GemmProb& P, const GemmUniform& U
   }
 }
 
-__device__ __forceinline__ void zero_acc(f32x16 (&acc)[2][2]) {
+template <int MB>
+__device__ __forceinline__ void zero_acc(f32x16 (&acc)[MB][MB]) {
 #pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
+  for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni)
+    for (int ni = 0; ni < MB; ++ni)
 #pragma unroll
       for (int j = 0; j < 16; ++j) acc[mi][ni][j] = 0.f;
 }
@@ -576,41 +591,41 @@ __device__ __forceinline__ void mainloop_bf16(const GemmProb& P, const GemmUnifo
   if constexpr (PD2) {
     BfA<AM, BBM, BNT, FAST> ra0, ra1;
     BfB<BBN, BNT, FAST> rb0, rb1;
-    ra0.load(P, R, row0, 0, U.B);
+    ra0.load(P, R, row0, 0, U);
     rb0.load(P, R, col0, 0);
-    if (nk > 1) { ra1.load(P, R, row0, BK, U.B); rb1.load(P, R, col0, BK); }
-    ra0.store(P, row0, 0, U.B, As[0]);
+    if (nk > 1) { ra1.load(P, R, row0, BK, U); rb1.load(P, R, col0, BK); }
+    ra0.store(P, row0, 0, U, As[0]);
     rb0.store(P, 0, Bs[0]);
     __syncthreads();
-    if (nk > 2) { ra0.load(P, R, row0, 2 * BK, U.B); rb0.load(P, R, col0, 2 * BK); }
+    if (nk > 2) { ra0.load(P, R, row0, 2 * BK, U); rb0.load(P, R, col0, 2 * BK); }
     for (int kt = 0; kt < nk; kt += 2) {
       // even: tile kt in stage 0; register set 1 holds tile kt+1, set 0 holds tile kt+2
       compute(As[0], Bs[0]);
-      if (kt + 1 < nk) { ra1.store(P, row0, (int64_t)(kt + 1) * BK, U.B, As[1]); rb1.store(P, (int64_t)(kt + 1) * BK, Bs[1]); }
+      if (kt + 1 < nk) { ra1.store(P, row0, (int64_t)(kt + 1) * BK, U, As[1]); rb1.store(P, (int64_t)(kt + 1) * BK, Bs[1]); }
       __syncthreads();
-      if (kt + 3 < nk) { ra1.load(P, R, row0, (int64_t)(kt + 3) * BK, U.B); rb1.load(P, R, col0, (int64_t)(kt + 3) * BK); }
+      if (kt + 3 < nk) { ra1.load(P, R, row0, (int64_t)(kt + 3) * BK, U); rb1.load(P, R, col0, (int64_t)(kt + 3) * BK); }
       if (kt + 1 >= nk) break;
       // odd: tile kt+1 in stage 1; set 0 holds tile kt+2, set 1 holds tile kt+3
       compute(As[1], Bs[1]);
-      if (kt + 2 < nk) { ra0.store(P, row0, (int64_t)(kt + 2) * BK, U.B, As[0]); rb0.store(P, (int64_t)(kt + 2) * BK, Bs[0]); }
+      if (kt + 2 < nk) { ra0.store(P, row0, (int64_t)(kt + 2) * BK, U, As[0]); rb0.store(P, (int64_t)(kt + 2) * BK, Bs[0]); }
       __syncthreads();
-      if (kt + 4 < nk) { ra0.load(P, R, row0, (int64_t)(kt + 4) * BK, U.B); rb0.load(P, R, col0, (int64_t)(kt + 4) * BK); }
+      if (kt + 4 < nk) { ra0.load(P, R, row0, (int64_t)(kt + 4) * BK, U); rb0.load(P, R, col0, (int64_t)(kt + 4) * BK); }
     }
   } else {
     BfA<AM, BBM, BNT, FAST> ra;
     BfB<BBN, BNT, FAST> rb;
-    ra.load(P, R, row0, 0, U.B);
+    ra.load(P, R, row0, 0, U);
     rb.load(P, R, col0, 0);
-    ra.store(P, row0, 0, U.B, As[0]);
+    ra.store(P, row0, 0, U, As[0]);
     rb.store(P, 0, Bs[0]);
     __syncthreads();
     for (int kt = 0; kt < nk; ++kt) {
       const int cur = kt & 1;
       const bool more = kt + 1 < nk;
       const int64_t kn = (int64_t)(kt + 1) * BK;
-      if (more) { ra.load(P, R, row0, kn, U.B); rb.load(P, R, col0, kn); }
+      if (more) { ra.load(P, R, row0, kn, U); rb.load(P, R, col0, kn); }
       compute(As[cur], Bs[cur]);
-      if (more) { ra.store(P, row0, kn, U.B, As[cur ^ 1]); rb.store(P, kn, Bs[cur ^ 1]); }
+      if (more) { ra.store(P, row0, kn, U, As[cur ^ 1]); rb.store(P, kn, Bs[cur ^ 1]); }
       __syncthreads();
     }
   }
@@ -630,80 +645,109 @@ __global__ __launch_bounds__(64 * BWM * BWN, 2) void k_gemm_bf16(const GemmProb*
   zero_acc(acc);
   if (P.vec & 4) mainloop_bf16<AM, BWM, BWN, PD2, true>(P, U, row0, col0, As, Bs, acc);
   else mainloop_bf16<AM, BWM, BWN, false, false>(P, U, row0, col0, As, Bs, acc);
-  epilogue<KIND_BF16, EP, BWN>(P, U, row0, col0, acc);
+  epilogue<KIND_BF16, EP, BWN, 2>(P, U, row0, col0, acc);
 }
 
-template <int AM, int BMODE, bool FAST>
+// Two LDS stages, one barrier per K step of 32. The 128 x 128 tile (64 x 64 per wave) keeps one
+// register set of loads in flight, the 64 x 64 tile (32 x 32 per wave, a quarter of the MFMA
+// work per K step, so the loads' latency is longer than it) two.
+template <int AM, int BMODE, int BT, bool FAST>
 __device__ __forceinline__ void mainloop_f32(const GemmProb& P, const GemmUniform& U, int64_t row0, int64_t col0,
-                                             float (*As)[(AM == A_G_TRANS) ? 32 * F_LDT : 128 * F_LDK],
-                                             float (*Bs)[(BMODE == B_NC) ? 32 * F_LDT : 128 * F_LDK],
-                                             f32x16 (&acc)[2][2]) {
-  constexpr int BK = 32;
+                                             float (*As)[(AM == A_G_TRANS) ? 32 * f_ldt(BT) : BT * F_LDK],
+                                             float (*Bs)[(BMODE == B_NC) ? 32 * f_ldt(BT) : BT * F_LDK],
+                                             f32x16 (&acc)[BT / 64][BT / 64]) {
+  constexpr int BK = 32, F_LDT = f_ldt(BT), MB = BT / 64, WT = BT / 2;
   constexpr bool AT = (AM == A_G_TRANS);
-  constexpr bool BT = (BMODE == B_NC);
+  constexpr bool BTR = (BMODE == B_NC);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const Rs R = make_rs(P);
-  FA<AM, FAST> ra;
-  FB<BMODE, FAST> rb;
   // an upper triangular right factor contributes nothing past the tile's last column
-  const int64_t kend = (P.tri_b && col0 + 128 < P.K) ? col0 + 128 : P.K;
+  const int64_t kend = (P.tri_b && col0 + BT < P.K) ? col0 + BT : P.K;
   const int nk = (int)((kend + BK - 1) / BK);
   auto compute = [&](const float* Ac, const float* Bc) {
 #pragma unroll
     for (int kk = 0; kk < BK / 2; ++kk) {
       const int kx = kk * 2 + (lane >> 5);
-      float af[2], bv[2];
+      float af[MB], bv[MB];
 #pragma unroll
-      for (int mi = 0; mi < 2; ++mi) {
-        const int i = wm * 64 + mi * 32 + (lane & 31);
+      for (int mi = 0; mi < MB; ++mi) {
+        const int i = wm * WT + mi * 32 + (lane & 31);
         af[mi] = AT ? Ac[kx * F_LDT + i] : Ac[i * F_LDK + kx];
       }
 #pragma unroll
-      for (int ni = 0; ni < 2; ++ni) {
-        const int j = wn * 64 + ni * 32 + (lane & 31);
-        bv[ni] = BT ? Bc[kx * F_LDT + j] : Bc[j * F_LDK + kx];
+      for (int ni = 0; ni < MB; ++ni) {
+        const int j = wn * WT + ni * 32 + (lane & 31);
+        bv[ni] = BTR ? Bc[kx * F_LDT + j] : Bc[j * F_LDK + kx];
       }
 #pragma unroll
-      for (int mi = 0; mi < 2; ++mi)
+      for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < 2; ++ni)
+        for (int ni = 0; ni < MB; ++ni)
           acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[ni], af[mi], acc[mi][ni], 0, 0, 0);
     }
   };
-  ra.load(P, R, row0, 0, U.B);
+  FA<AM, BT, FAST> ra;
+  FB<BMODE, BT, FAST> rb;
+  ra.load(P, R, row0, 0, U);
   rb.load(P, R, col0, 0);
-  ra.store(P, row0, 0, U.B, As[0]);
-  rb.store(P, col0, 0, Bs[0]);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    const bool more = kt + 1 < nk;
-    const int64_t kn = (int64_t)(kt + 1) * BK;
-    if (more) { ra.load(P, R, row0, kn, U.B); rb.load(P, R, col0, kn); }
-    compute(As[cur], Bs[cur]);
-    if (more) { ra.store(P, row0, kn, U.B, As[cur ^ 1]); rb.store(P, col0, kn, Bs[cur ^ 1]); }
+  if constexpr (BT == 64) {
+    FA<AM, BT, FAST> ra1;
+    FB<BMODE, BT, FAST> rb1;
+    auto load = [&](int kt, auto& a, auto& b) {
+      if (kt < nk) { a.load(P, R, row0, (int64_t)kt * BK, U); b.load(P, R, col0, (int64_t)kt * BK); }
+    };
+    auto store = [&](int kt, const auto& a, const auto& b) {
+      if (kt < nk) { a.store(P, row0, (int64_t)kt * BK, U, As[kt & 1]); b.store(P, col0, (int64_t)kt * BK, Bs[kt & 1]); }
+    };
+    load(1, ra1, rb1);
+    store(0, ra, rb);
+    load(2, ra, rb);
     __syncthreads();
+    for (int kt = 0; kt < nk; kt += 2) {   // even steps: set 1 holds kt + 1, set 0 holds kt + 2
+      compute(As[0], Bs[0]);
+      store(kt + 1, ra1, rb1);
+      load(kt + 3, ra1, rb1);
+      __syncthreads();
+      if (kt + 1 >= nk) break;
+      compute(As[1], Bs[1]);
+      store(kt + 2, ra, rb);
+      load(kt + 4, ra, rb);
+      __syncthreads();
+    }
+  } else {
+    ra.store(P, row0, 0, U, As[0]);
+    rb.store(P, col0, 0, Bs[0]);
+    __syncthreads();
+    for (int kt = 0; kt < nk; ++kt) {
+      const int cur = kt & 1;
+      const bool more = kt + 1 < nk;
+      const int64_t kn = (int64_t)(kt + 1) * BK;
+      if (more) { ra.load(P, R, row0, kn, U); rb.load(P, R, col0, kn); }
+      compute(As[cur], Bs[cur]);
+      if (more) { ra.store(P, row0, kn, U, As[cur ^ 1]); rb.store(P, col0, kn, Bs[cur ^ 1]); }
+      __syncthreads();
+    }
   }
 }
 
-template <int AM, int BMODE, int EP>
-__global__ __launch_bounds__(FNT, 2) void k_gemm_f32(const GemmProb* __restrict__ probs, GemmUniform U) {
-  constexpr int BM = 128, BN = 128, BK = 32;
+template <int AM, int BMODE, int EP, int BT>
+__global__ __launch_bounds__(FNT, BT == 64 ? 4 : 2) void k_gemm_f32(const GemmProb* __restrict__ probs, GemmUniform U) {
+  constexpr int BK = 32, F_LDT = f_ldt(BT);
   constexpr bool AT = (AM == A_G_TRANS);
-  constexpr bool BT = (BMODE == B_NC);
-  __shared__ __attribute__((aligned(16))) float As[2][AT ? BK * F_LDT : BM * F_LDK];
-  __shared__ __attribute__((aligned(16))) float Bs[2][BT ? BK * F_LDT : BN * F_LDK];
+  constexpr bool BTR = (BMODE == B_NC);
+  __shared__ __attribute__((aligned(16))) float As[2][AT ? BK * F_LDT : BT * F_LDK];
+  __shared__ __attribute__((aligned(16))) float Bs[2][BTR ? BK * F_LDT : BT * F_LDK];
   const uint32_t t = xcd_remap(blockIdx.x, gridDim.x);
   const GemmProb& P = probs[find_prob(probs, U.nprob, t)];
   uint32_t tm, tn;
-  tile_coords(t - P.tile_start, (uint32_t)((P.M + BM - 1) / BM), P.tiles_n, tm, tn);
-  const int64_t row0 = (int64_t)tm * BM, col0 = (int64_t)tn * BN;
-  f32x16 acc[2][2];
+  tile_coords(t - P.tile_start, (uint32_t)((P.M + BT - 1) / BT), P.tiles_n, tm, tn);
+  const int64_t row0 = (int64_t)tm * BT, col0 = (int64_t)tn * BT;
+  f32x16 acc[BT / 64][BT / 64];
   zero_acc(acc);
-  if (P.vec & 4) mainloop_f32<AM, BMODE, true>(P, U, row0, col0, As, Bs, acc);
-  else mainloop_f32<AM, BMODE, false>(P, U, row0, col0, As, Bs, acc);
-  epilogue<KIND_F32, EP, 2>(P, U, row0, col0, acc);
+  if (P.vec & 4) mainloop_f32<AM, BMODE, BT, true>(P, U, row0, col0, As, Bs, acc);
+  else mainloop_f32<AM, BMODE, BT, false>(P, U, row0, col0, As, Bs, acc);
+  epilogue<KIND_F32, EP, 2, BT / 64>(P, U, row0, col0, acc);
 }
 
 }  // namespace
@@ -717,19 +761,37 @@ uint32_t gemm_tiles_n(int kind, int64_t N) {
   return (uint32_t)((N + 127) / 128);
 }
 
+constexpr uint32_t F32_SMALL_TILES = 4096;
+int gemm_f32_fit(GemmProb* probs, int n, uint32_t* total) {
+  if (*total > F32_SMALL_TILES) return 128;
+  uint32_t t = 0;
+  for (int i = 0; i < n; ++i) {
+    probs[i].tiles_n = (uint32_t)((probs[i].N + 63) / 64);
+    probs[i].tile_start = t;
+    t += (uint32_t)((probs[i].M + 63) / 64) * probs[i].tiles_n;
+  }
+  *total = t;
+  return 64;
+}
+
 #define GEMM_BF(AM, EP)                                                                  \
   if (amode == AM && ep == EP) {                                                       \
     hipLaunchKernelGGL((k_gemm_bf16<AM, EP, 2, 2, AM == A_KC>), grid, dim3(256), 0, st, probs_dev, u); \
     return hipGetLastError();                                                          \
   }
-#define GEMM_F(AM, BMO, EP) \
-  if (amode == AM && bmode == BMO && ep == EP) { hipLaunchKernelGGL((k_gemm_f32<AM, BMO, EP>), grid, dim3(FNT), 0, st, probs_dev, u); return hipGetLastError(); }
+#define GEMM_F(AM, BMO, EP)                                                                                              \
+  if (amode == AM && bmode == BMO && ep == EP) {                                                                         \
+    if (tile == 64) hipLaunchKernelGGL((k_gemm_f32<AM, BMO, EP, 64>), grid, dim3(FNT), 0, st, probs_dev, u);             \
+    else hipLaunchKernelGGL((k_gemm_f32<AM, BMO, EP, 128>), grid, dim3(FNT), 0, st, probs_dev, u);                       \
+    return hipGetLastError();                                                                                            \
+  }
 
 hipError_t launch_gemm(int kind, int amode, int bmode, int ep, const GemmProb* probs_dev, int nprob,
-                       uint32_t total_tiles, const GemmUniform& u0, hipStream_t st) {
+                       uint32_t total_tiles, const GemmUniform& u0, hipStream_t st, int tile) {
   if (total_tiles == 0 || nprob == 0) return hipSuccess;
   GemmUniform u = u0;
   u.nprob = nprob;
+  u.lgB = (u.B > 0 && (u.B & (u.B - 1)) == 0) ? __builtin_ctz(u.B) : -1;
   const dim3 grid(total_tiles);
   if (kind == KIND_BF16) {
     if (bmode != B_KC) return hipErrorInvalidValue;

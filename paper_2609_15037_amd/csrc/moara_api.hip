@@ -569,6 +569,12 @@ int run_project_back(moara_state* st, const std::vector<int>& idx, void* const* 
     if (h.side == MOARA_SIDE_LEFT) { g.tile_start = tl; tl += nt; left.push_back(g); }
     else { g.tile_start = tr; tr += nt; right.push_back(g); }
   }
+  int til = 128, tir = 128, tib = 128;   // fp32 operands: the tile each list runs on
+  if (!ob) {
+    til = gemm_f32_fit(left.data(), (int)left.size(), &tl);
+    tir = gemm_f32_fit(right.data(), (int)right.size(), &tr);
+    tib = gemm_f32_fit(back.data(), (int)back.size(), &tb);
+  }
   Stager sg;
   int rc = begin_stage(st, sg);
   if (rc) return rc;
@@ -587,16 +593,16 @@ int run_project_back(moara_state* st, const std::vector<int>& idx, void* const* 
     if (!pnt.empty())
       HIP_TRY(launch_gemm_nt(EP_ADAM, (const GemmProb*)(st->dev_arena + opn), (int)pnt.size(), tpn, u, stream));
     if (!right.empty())
-      HIP_TRY(launch_gemm(kind, A_G_ROW, B_KC, EP_ADAM, (const GemmProb*)(st->dev_arena + orr), (int)right.size(), tr, u, stream));
+      HIP_TRY(launch_gemm(kind, A_G_ROW, B_KC, EP_ADAM, (const GemmProb*)(st->dev_arena + orr), (int)right.size(), tr, u, stream, tir));
     if (!left.empty())
-      HIP_TRY(launch_gemm(kind, A_G_TRANS, B_KC, EP_ADAM, (const GemmProb*)(st->dev_arena + ol), (int)left.size(), tl, u, stream));
+      HIP_TRY(launch_gemm(kind, A_G_TRANS, B_KC, EP_ADAM, (const GemmProb*)(st->dev_arena + ol), (int)left.size(), tl, u, stream, til));
   }
   {
     TimerScope ts(st, MOARA_KERN_BACKPROJ, stream);
     if (!bnt.empty())
       HIP_TRY(launch_gemm_nt(EP_UPDATE, (const GemmProb*)(st->dev_arena + obn), (int)bnt.size(), tbn, u, stream));
     if (!back.empty())
-      HIP_TRY(launch_gemm(kind, A_KC, B_KC, EP_UPDATE, (const GemmProb*)(st->dev_arena + obk), (int)back.size(), tb, u, stream));
+      HIP_TRY(launch_gemm(kind, A_KC, B_KC, EP_UPDATE, (const GemmProb*)(st->dev_arena + obk), (int)back.size(), tb, u, stream, tib));
   }
   return MOARA_OK;
 }
@@ -825,6 +831,14 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
     }
     return std::make_pair(g, t);
   };
+  struct GemmList { std::vector<GemmProb> first; uint32_t second = 0; int tile = 128; };
+  auto fitted = [](std::vector<GemmProb>& g, uint32_t t) {
+    GemmList l;
+    l.tile = gemm_f32_fit(g.data(), (int)g.size(), &t);
+    l.first = std::move(g);
+    l.second = t;
+    return l;
+  };
   auto apply_list = [&](bool onY, bool only_f32 = false) {   // Z = Z2 Rinv  or  Y2 = Y Rinv
     std::vector<GemmProb> g;
     uint32_t t = 0;
@@ -846,7 +860,7 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
       gp.tile_start = t;
       t += gemm_tiles_m(kind, gp.M) * gp.tiles_n;
     }
-    return std::make_pair(g, t);
+    return fitted(g, t);
   };
   // Y = X Z  (tall: M = L, K = s)   or   Z2 = X^T Yin  (M = s, K = L)
   auto big_list = [&](int side, bool xt, bool fromY2, bool only_f32 = false) {
@@ -870,7 +884,7 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
       t += gemm_tiles_m(kind, gp.M) * gp.tiles_n;
       g.push_back(gp);
     }
-    return std::make_pair(g, t);
+    return fitted(g, t);
   };
   // workgroup prefixes of the blocked Cholesky / inverse launches (same for every orth of the chunk)
   int nbmax = 1;
@@ -923,6 +937,7 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
     tpw += gemm_tiles_m(kind, gp.M) * gp.tiles_n;
     pwl.push_back(gp);
   }
+  const int tile_pw = gemm_f32_fit(pwl.data(), nm, &tpw);
   std::vector<TransProb> tZ, tX, tZs, tY2, tR;
   std::vector<GemmProb> nY, nZ, nYs, nZs, nYf, nYs3, nZs3, nZf, qZ, qZs;
   std::vector<SplitProb> vlo;
@@ -1132,9 +1147,9 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
   auto D = [&](int q) { return (const void*)(st->ref_arena + offs[q]); };
   const RefDev* RD = (const RefDev*)D(0);
 
-  auto gemm = [&](int am, int q, const std::pair<std::vector<GemmProb>, uint32_t>& l) -> hipError_t {
+  auto gemm = [&](int am, int q, const GemmList& l) -> hipError_t {
     if (l.first.empty()) return hipSuccess;
-    return launch_gemm(kind, am, B_NC, EP_STORE, (const GemmProb*)D(q), (int)l.first.size(), l.second, u, stream);
+    return launch_gemm(kind, am, B_NC, EP_STORE, (const GemmProb*)D(q), (int)l.first.size(), l.second, u, stream, l.tile);
   };
   const uint32_t* PAN = (const uint32_t*)D(11);
   const uint32_t* UPD = (const uint32_t*)D(12);
@@ -1225,7 +1240,7 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
   for (int sw = 0; sw < MAX_SWEEPS; ++sw)
     for (int rr = 0; rr < nb_max - 1; ++rr) HIP_TRY(launch_jacobi_round(RD, nm, tj, rr, sw, stream));
   HIP_TRY(launch_finalize_order(RD, nm, tnorm, stream));
-  HIP_TRY(launch_gemm(kind, A_KC, B_KC, EP_STORE, (const GemmProb*)D(22), nm, tpw, u, stream));
+  HIP_TRY(launch_gemm(kind, A_KC, B_KC, EP_STORE, (const GemmProb*)D(22), nm, tpw, u, stream, tile_pw));
   int32_t rmax = 0;
   for (auto& x : rm) rmax = std::max(rmax, st->mats[x.idx].r);
   HIP_TRY(launch_finalize_out(RD, nm, rmax, stream));
@@ -1616,6 +1631,9 @@ int moara_alignment(moara_state* st, const void* const* grads, const uint8_t* ac
     tr += gemm_tiles_m(KIND_F32, b.M) * b.tiles_n;
     rec.push_back(b);
   }
+  const int tiR = gemm_f32_fit(projR.data(), (int)projR.size(), &tR);
+  const int tiL = gemm_f32_fit(projL.data(), (int)projL.size(), &tL);
+  const int tiB = gemm_f32_fit(rec.data(), (int)rec.size(), &tr);
   Stager sg;
   if ((rc = begin_stage(st, sg))) return rc;
   const size_t oR = projR.empty() ? 0 : sg.push(projR.data(), projR.size());
@@ -1628,11 +1646,11 @@ int moara_alignment(moara_state* st, const void* const* grads, const uint8_t* ac
   {
     TimerScope ts(st, MOARA_KERN_ALIGN, hs);
     if (!projR.empty())
-      HIP_TRY(launch_gemm(KIND_F32, A_G_ROW, B_NC, EP_STORE, (const GemmProb*)(st->dev_arena + oR), (int)projR.size(), tR, u, hs));
+      HIP_TRY(launch_gemm(KIND_F32, A_G_ROW, B_NC, EP_STORE, (const GemmProb*)(st->dev_arena + oR), (int)projR.size(), tR, u, hs, tiR));
     if (!projL.empty())
-      HIP_TRY(launch_gemm(KIND_F32, A_G_TRANS, B_NC, EP_STORE, (const GemmProb*)(st->dev_arena + oL), (int)projL.size(), tL, u, hs));
+      HIP_TRY(launch_gemm(KIND_F32, A_G_TRANS, B_NC, EP_STORE, (const GemmProb*)(st->dev_arena + oL), (int)projL.size(), tL, u, hs, tiL));
     HIP_TRY(hipMemsetAsync(red, 0, 8 * 3 * idx.size(), hs));
-    HIP_TRY(launch_gemm(KIND_F32, A_KC, B_KC, EP_ALIGN, (const GemmProb*)(st->dev_arena + oB), (int)rec.size(), tr, u, hs));
+    HIP_TRY(launch_gemm(KIND_F32, A_KC, B_KC, EP_ALIGN, (const GemmProb*)(st->dev_arena + oB), (int)rec.size(), tr, u, hs, tiB));
   }
   std::vector<double> sums(3 * idx.size());
   HIP_TRY(hipMemcpyAsync(sums.data(), red, 8 * sums.size(), hipMemcpyDeviceToHost, hs));
