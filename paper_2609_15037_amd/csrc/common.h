@@ -26,7 +26,7 @@ struct MatDev {
   float* dM;           // m x k: Optimizer_M output
   float* mag1;         // m x k: Optimizer_M moments
   float* mag2;
-  float* exp1;         // L x r: Optimizer_V moments (row l, column j)
+  float* exp1;         // L x r, row stride ldr: Optimizer_V moments (row l, column j)
   float* exp2;
   void* N;             // L x r: Optimizer_V output in operand dtype
   const void* Pop;     // s x r projector, operand dtype
@@ -36,11 +36,12 @@ struct MatDev {
   uint32_t tile_proj;  // ... in the projection launch
   uint32_t tile_back;  // ... in the back-projection launch
   int32_t vt;          // V output layout: 0 row-major m x n, 1 transposed n x m
-  bf16* Vb;            // bf16 direction tensor V written by the decomposition (nullptr: none)
+  bf16* Vb;            // bf16 direction tensor V written by the decomposition (nullptr: none); its
+                       // padding up to whole 32-wide K panels is zero and stays so
   int32_t n_bf16;      // zero-gradient step: N is bf16 (else fp32) ...
   int32_t n_kp;        // ... in the blocked layout kp_index(l, j, L)
   int32_t mom_bf16;    // zero-gradient step: exp1 / exp2 hold bf16 values
-  int32_t pad_;
+  int32_t ldr;         // row stride of exp1 / exp2
 };
 
 struct StepParams {
@@ -55,7 +56,8 @@ struct StepParams {
 
 // ---------------------------------------------------------------- helpers
 // Blocked ("K-panel") layout of a bf16 GEMM operand with `rows` rows and reduction
-// length K (a multiple of 32): element (i, k) sits at ((k / 32) * rows + i) * 32 + k % 32.
+// length K (rounded up to a multiple of 32, the last panel's tail zero): element (i, k) sits
+// at ((k / 32) * rows + i) * 32 + k % 32.
 // The 64-byte row segments of one 32-wide K step of consecutive rows are then one
 // contiguous run, which the large-tile GEMM streams with whole-line DMA loads.
 __host__ __device__ __forceinline__ int64_t kp_index(int64_t i, int64_t k, int64_t rows) {
@@ -116,9 +118,11 @@ __device__ __forceinline__ float adam_out_bf16(float x, bf16& e, bf16& q, float 
 // ---------------------------------------------------------------- launchers
 // All launchers return hipError_t from hipGetLastError after the launch.
 struct GemmProb;
-hipError_t launch_decompose(const MatDev* mats_dev, const StepParams& p, hipStream_t st);
-hipError_t launch_decompose_inv_only(const MatDev* mats_dev, const StepParams& p, hipStream_t st);
-hipError_t launch_decompose_vt(const MatDev* mats_dev, const StepParams& p, int adam_m, hipStream_t st);
+// One launch covers matrices that are all plain (decompose_plain) or all not. adam_m: also run
+// Optimizer_M.
+bool decompose_plain(const float* G, int64_t n, int k, bool decompose, bool transposed);
+hipError_t launch_decompose(const MatDev* mats_dev, const StepParams& p, int adam_m, bool plain, hipStream_t st);
+hipError_t launch_decompose_vt(const MatDev* mats_dev, const StepParams& p, int adam_m, bool plain, hipStream_t st);
 int decompose_tiles(int64_t m);
 int decompose_vt_tiles(int64_t m);
 // Optimizer_M and Optimizer_V of a matrix whose gradient is exactly zero (no G is read):
@@ -127,7 +131,7 @@ int decompose_vt_tiles(int64_t m);
 uint32_t zero_grad_tiles(int64_t mk, int64_t Lr);
 hipError_t launch_zero_grad(const MatDev* mats_dev, const StepParams& p, hipStream_t st);
 // limits of the V-writing decomposition paths (blocks per row)
-constexpr int DEC_VT_MAX_K = 160;    // transposed path, 64 rows per workgroup
+constexpr int DEC_VT_MAX_K = 160;    // transposed path: blocks held in LDS at a time (any k runs)
 constexpr int DEC_ROW_MAX_K = 512;   // row-major path, 16 rows per workgroup
 hipError_t launch_project(const MatDev* mats_dev, const StepParams& p, int operand_bf16, hipStream_t st);
 hipError_t launch_backproject(const MatDev* mats_dev, const StepParams& p, int operand_bf16, hipStream_t st);

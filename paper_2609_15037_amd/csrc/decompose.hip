@@ -27,6 +27,22 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 constexpr int DEC_ROWS = 16;   // rows per workgroup (4 waves x 4 rows)
 
+// Columns c .. c + 3 of a gradient row of n columns (zeros past its end). PLAIN: n % 4 == 0 and
+// rows 16-byte aligned. Otherwise rows start at any multiple of 4 bytes, which a 16-byte global
+// load takes, and a group may end inside the row. One code path with the tail test made the
+// transposed decomposition 3 to 40 % slower at aligned sizes (more live masks around its 8 loads
+// in flight), so the kernels are instantiated for both and each matrix goes to its own launch.
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+template <bool PLAIN>
+__device__ __forceinline__ float4 load_g4(const float* row, int64_t c, int64_t n) {
+  if (PLAIN) return c < n ? *reinterpret_cast<const float4*>(row + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+  if (c + 4 <= n) {
+    const f32x4_a4 v = *reinterpret_cast<const f32x4_a4*>(row + c);
+    return make_float4(v.x, v.y, v.z, v.w);
+  }
+  return make_float4(c < n ? row[c] : 0.f, c + 1 < n ? row[c + 1] : 0.f, c + 2 < n ? row[c + 2] : 0.f, 0.f);
+}
+
 // Sum over aligned groups of gl lanes (gl a power of two <= 64). The first four
 // levels use DPP lane permutations (pairs within a quad, then the two quads of an
 // 8-lane half-row, then the two halves of a 16-lane row: mirror permutations pair
@@ -68,6 +84,7 @@ __device__ __forceinline__ void block_out(const MatDev& d, const StepParams& p, 
 // contiguous in the m x k layout, so the moment/inv/dM traffic is coalesced.
 constexpr int DEC_LDS = 8192;   // floats of LDS for block sums (phase 1 -> 2)
 
+template <bool PLAIN>
 __global__ __launch_bounds__(256) void k_decompose(const MatDev* __restrict__ mats, StepParams p, int adam_m) {
   __shared__ float sums[DEC_LDS];
   const uint32_t t = blockIdx.x;
@@ -76,12 +93,13 @@ __global__ __launch_bounds__(256) void k_decompose(const MatDev* __restrict__ ma
   const int64_t row0 = (int64_t)(t - d.tile_dec) * DEC_ROWS;
   const int rows = (int)((d.m - row0 < DEC_ROWS) ? d.m - row0 : DEC_ROWS);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int B = p.B;
+  // without the decomposition V = G: only V is written (any group width does)
+  const bool dec = PLAIN || p.decompose != 0;
+  const int B = dec ? p.B : 128;
   const int64_t n = d.n;
   const int k = d.k;
-  const bool staged = (int64_t)rows * k <= DEC_LDS;
-  const bool fast = staged && B >= 4 && B <= 256 && (B & (B - 1)) == 0 && (n & 3) == 0 &&
-                    ((uintptr_t)d.G & 15) == 0;
+  const bool staged = !dec || (int64_t)rows * k <= DEC_LDS;
+  const bool fast = staged && B >= 4 && B <= 256 && (B & (B - 1)) == 0;
   if (!staged) {
     // generic path (very many blocks per row): one block at a time, Optimizer_M inline
     for (int rr = wave; rr < rows; rr += 4) {
@@ -116,7 +134,7 @@ __global__ __launch_bounds__(256) void k_decompose(const MatDev* __restrict__ ma
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
           const int64_t c = c00 + 128 * u + 4 * hl;
-          v[u] = (rok && c < n) ? *reinterpret_cast<const float4*>(g + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+          v[u] = load_g4<PLAIN>(g, rok ? c : n, n);
         }
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
@@ -124,9 +142,9 @@ __global__ __launch_bounds__(256) void k_decompose(const MatDev* __restrict__ ma
           float ss = v[u].x * v[u].x + v[u].y * v[u].y + v[u].z * v[u].z + v[u].w * v[u].w;
           ss = group_sum(ss, gl);
           if (rok && c < n) {
-            if ((hl & (gl - 1)) == 0) sums[rr * k + (int)(c >> lgB)] = ss;
+            if (dec && (hl & (gl - 1)) == 0) sums[rr * k + (int)(c >> lgB)] = ss;
             if (d.Vb) {
-              const float inv = 1.0f / (sqrtf(ss) + p.decomp_eps);
+              const float inv = dec ? 1.0f / (sqrtf(ss) + p.decomp_eps) : 1.0f;
               bf16x4 o;
               o[0] = f2bf(v[u].x * inv); o[1] = f2bf(v[u].y * inv); o[2] = f2bf(v[u].z * inv); o[3] = f2bf(v[u].w * inv);
               *reinterpret_cast<bf16x4*>(d.Vb + kp_index(row, c, d.m)) = o;   // blocked, K = n
@@ -148,7 +166,7 @@ __global__ __launch_bounds__(256) void k_decompose(const MatDev* __restrict__ ma
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
           const int64_t c = c00 + 256 * u + 4 * lane;
-          v[u] = (c < n) ? *reinterpret_cast<const float4*>(g + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+          v[u] = load_g4<PLAIN>(g, c, n);
         }
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
@@ -175,6 +193,7 @@ __global__ __launch_bounds__(256) void k_decompose(const MatDev* __restrict__ ma
       }
     }
   }
+  if (!dec) return;
   __syncthreads();
   const int total = rows * k;
   for (int e = threadIdx.x; e < total; e += 256) {
@@ -191,9 +210,10 @@ __global__ __launch_bounds__(256) void k_decompose(const MatDev* __restrict__ ma
 // each), i.e. 64-byte (one K panel) segments of Vt. The odd 4-byte pitch of T keeps the
 // row groups read by one instruction on distinct banks. Optimizer_M then runs over the
 // VT_ROWS x k sums as in k_decompose. 32-row slabs (143 VGPRs, three waves per SIMD)
-// measured 1.7 % faster than 64-row ones (231 VGPRs, two). Preconditions (checked by
-// the host): B a power of two in [4, 256], n % 4 == 0, m % 32 == 0, k <= DEC_VT_MAX_K,
-// G 16-byte aligned.
+// measured 1.7 % faster than 64-row ones (231 VGPRs, two). The sums of DEC_VT_MAX_K blocks per
+// row fit in LDS; longer rows run in column ranges of that many blocks. Rows past m are zero in
+// the last K panel. Preconditions (checked by the host): B a power of two in [4, 256], or no
+// decomposition (V = G); PLAIN: decompose_plain.
 #ifndef DEC_VT_ROWS
 #define DEC_VT_ROWS 32
 #endif
@@ -202,6 +222,7 @@ constexpr int VT_RPW = VT_ROWS / 4;    // rows per wave
 constexpr int VT_GRP = VT_ROWS / 8;    // 8-row groups of a column (16-byte output runs)
 static_assert(VT_ROWS % 32 == 0, "whole 32-row K panels of the blocked output");
 
+template <bool PLAIN>
 __global__ __launch_bounds__(256) void k_decompose_vt(const MatDev* __restrict__ mats, StepParams p, int adam_m) {
   __shared__ float sums[VT_ROWS * DEC_VT_MAX_K];
   __shared__ __attribute__((aligned(16))) bf16 T[VT_ROWS * VT_PITCH];
@@ -211,8 +232,9 @@ __global__ __launch_bounds__(256) void k_decompose_vt(const MatDev* __restrict__
   const int64_t row0 = (int64_t)(t - d.tile_dec) * VT_ROWS;
   const int rows = (int)((d.m - row0 < VT_ROWS) ? d.m - row0 : VT_ROWS);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int B = p.B, gl = B >> 2, k = d.k, lgB = __builtin_ctz(B);
-  const int64_t n = d.n, m = d.m;
+  const bool dec = PLAIN || p.decompose != 0;
+  const int B = dec ? p.B : 128, gl = B >> 2, k = d.k, lgB = __builtin_ctz(B);
+  const int64_t n = d.n;
   // the slab loop is software-pipelined: the VT_RPW loads of the next slab are issued
   // before the current slab is reduced, transposed and written out
   float4 va[VT_RPW], vb[VT_RPW];
@@ -221,10 +243,10 @@ __global__ __launch_bounds__(256) void k_decompose_vt(const MatDev* __restrict__
 #pragma unroll
     for (int i = 0; i < VT_RPW; ++i) {
       const int rr = wave + 4 * i;
-      v[i] = (rr < rows && c < n) ? *reinterpret_cast<const float4*>(d.G + (row0 + rr) * n + c)
-                                  : make_float4(0.f, 0.f, 0.f, 0.f);
+      v[i] = load_g4<PLAIN>(d.G + (row0 + rr) * n, rr < rows ? c : n, n);
     }
   };
+  int kc0 = 0, kc = 0;   // blocks of the current column range: [kc0, kc0 + kc)
   auto process = [&](int64_t c0, const float4 (&v)[VT_RPW]) {
     const int64_t c = c0 + 4 * lane;
 #pragma unroll
@@ -232,8 +254,8 @@ __global__ __launch_bounds__(256) void k_decompose_vt(const MatDev* __restrict__
       const int rr = wave + 4 * i;
       float ss = v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
       ss = group_sum(ss, gl);
-      if (rr < rows && c < n && (lane & (gl - 1)) == 0) sums[rr * k + (int)(c >> lgB)] = ss;
-      const float inv = 1.0f / (sqrtf(ss) + p.decomp_eps);
+      if (dec && rr < rows && c < n && (lane & (gl - 1)) == 0) sums[rr * kc + (int)(c >> lgB) - kc0] = ss;
+      const float inv = dec ? 1.0f / (sqrtf(ss) + p.decomp_eps) : 1.0f;
       bf16x2 a, b;
       a[0] = f2bf(v[i].x * inv); a[1] = f2bf(v[i].y * inv);
       b[0] = f2bf(v[i].z * inv); b[1] = f2bf(v[i].w * inv);
@@ -255,18 +277,46 @@ __global__ __launch_bounds__(256) void k_decompose_vt(const MatDev* __restrict__
     }
     __syncthreads();
   };
+  auto adam_m_blocks = [&]() {
+    const int total = rows * kc;
+    for (int e = threadIdx.x; e < total; e += 256) {
+      const int rr = e / kc, j = e - (e / kc) * kc;
+      block_out(d, p, row0 + rr, kc0 + j, sums[e], adam_m);
+    }
+  };
   load(0, va);
-  for (int64_t c0 = 0; c0 < n; c0 += 2 * VT_COLS) {
-    if (c0 + VT_COLS < n) load(c0 + VT_COLS, vb);
-    process(c0, va);
-    if (c0 + VT_COLS >= n) break;
-    if (c0 + 2 * VT_COLS < n) load(c0 + 2 * VT_COLS, va);
-    process(c0 + VT_COLS, vb);
+  if (PLAIN) {
+    kc = k;
+    for (int64_t c0 = 0; c0 < n; c0 += 2 * VT_COLS) {
+      if (c0 + VT_COLS < n) load(c0 + VT_COLS, vb);
+      process(c0, va);
+      if (c0 + VT_COLS >= n) break;
+      if (c0 + 2 * VT_COLS < n) load(c0 + 2 * VT_COLS, va);
+      process(c0 + VT_COLS, vb);
+    }
+    adam_m_blocks();
+    return;
   }
-  const int total = rows * k;
-  for (int e = threadIdx.x; e < total; e += 256) {
-    const int rr = e / k, j = e - (e / k) * k;
-    block_out(d, p, row0 + rr, j, sums[e], adam_m);
+  // column ranges of at most DEC_VT_MAX_K blocks, whole slabs (B divides VT_COLS)
+  const int64_t span = dec ? (int64_t)DEC_VT_MAX_K * B / VT_COLS * VT_COLS : n;
+  for (int64_t cr = 0; cr < n; cr += span) {
+    const int64_t ce = cr + span < n ? cr + span : n;
+    kc0 = (int)(cr >> lgB);
+    kc = (int)((ce + B - 1) >> lgB) - kc0;
+    for (int64_t c0 = cr; c0 < ce; c0 += 2 * VT_COLS) {
+      if (c0 + VT_COLS < n) load(c0 + VT_COLS, vb);
+      process(c0, va);
+      if (c0 + VT_COLS >= ce) {   // odd number of slabs: the next range starts with vb's columns
+#pragma unroll
+        for (int i = 0; i < VT_RPW; ++i) va[i] = vb[i];
+        break;
+      }
+      if (c0 + 2 * VT_COLS < n) load(c0 + 2 * VT_COLS, va);
+      process(c0 + VT_COLS, vb);
+    }
+    if (!dec) break;
+    adam_m_blocks();
+    __syncthreads();   // the next range's sums overwrite these
   }
 }
 // A zero gradient gives M = 0, V = 0 and R = P^T V = 0 (Algorithm 1 with G = 0), so the
@@ -290,7 +340,7 @@ __global__ __launch_bounds__(256) void k_zero_grad(const MatDev* __restrict__ ma
       d.mag2[e] = q;
       d.dM[e] = out;
     } else {
-      const int64_t x = e - mk;   // (l, j) of the L x r moments, row-major
+      const int64_t el = e - mk, l = el / d.r, j = el - l * d.r, x = l * d.ldr + j;   // (l, j) of the moments
       float out;
       if (d.mom_bf16) {
         bf16* E1 = reinterpret_cast<bf16*>(d.exp1);
@@ -306,10 +356,9 @@ __global__ __launch_bounds__(256) void k_zero_grad(const MatDev* __restrict__ ma
         d.exp2[x] = q;
       }
       if (d.n_bf16) {
-        const int64_t l = x / d.r, j = x % d.r;
-        ((bf16*)d.N)[d.n_kp ? kp_index(l, j, d.L) : x] = f2bf(out);
+        ((bf16*)d.N)[d.n_kp ? kp_index(l, j, d.L) : el] = f2bf(out);
       } else {
-        ((float*)d.N)[x] = out;
+        ((float*)d.N)[el] = out;
       }
     }
   }
@@ -327,20 +376,20 @@ hipError_t launch_zero_grad(const MatDev* mats_dev, const StepParams& p, hipStre
 int decompose_tiles(int64_t m) { return (int)((m + DEC_ROWS - 1) / DEC_ROWS); }
 int decompose_vt_tiles(int64_t m) { return (int)((m + VT_ROWS - 1) / VT_ROWS); }
 
-hipError_t launch_decompose_vt(const MatDev* mats_dev, const StepParams& p, int adam_m, hipStream_t st) {
+bool decompose_plain(const float* G, int64_t n, int k, bool decompose, bool transposed) {
+  return decompose && (n & 3) == 0 && ((uintptr_t)G & 15) == 0 && (!transposed || k <= DEC_VT_MAX_K);
+}
+
+hipError_t launch_decompose_vt(const MatDev* mats_dev, const StepParams& p, int adam_m, bool plain, hipStream_t st) {
   if (p.total_dec == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_decompose_vt, dim3(p.total_dec), dim3(256), 0, st, mats_dev, p, adam_m);
+  if (plain) hipLaunchKernelGGL((k_decompose_vt<true>), dim3(p.total_dec), dim3(256), 0, st, mats_dev, p, adam_m);
+  else hipLaunchKernelGGL((k_decompose_vt<false>), dim3(p.total_dec), dim3(256), 0, st, mats_dev, p, adam_m);
   return hipGetLastError();
 }
 
-hipError_t launch_decompose(const MatDev* mats_dev, const StepParams& p, hipStream_t st) {
+hipError_t launch_decompose(const MatDev* mats_dev, const StepParams& p, int adam_m, bool plain, hipStream_t st) {
   if (p.total_dec == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_decompose, dim3(p.total_dec), dim3(256), 0, st, mats_dev, p, 1);
-  return hipGetLastError();
-}
-
-hipError_t launch_decompose_inv_only(const MatDev* mats_dev, const StepParams& p, hipStream_t st) {
-  if (p.total_dec == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_decompose, dim3(p.total_dec), dim3(256), 0, st, mats_dev, p, 0);
+  if (plain) hipLaunchKernelGGL((k_decompose<true>), dim3(p.total_dec), dim3(256), 0, st, mats_dev, p, adam_m);
+  else hipLaunchKernelGGL((k_decompose<false>), dim3(p.total_dec), dim3(256), 0, st, mats_dev, p, adam_m);
   return hipGetLastError();
 }

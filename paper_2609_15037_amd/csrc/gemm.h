@@ -19,8 +19,9 @@ enum { KIND_BF16 = 0, KIND_F32 = 1 };
 enum { A_G_ROW = 0, A_G_TRANS = 1, A_KC = 2 };
 enum { B_KC = 0, B_NC = 1 };
 // Epilogues:
-//   EP_ADAM   : Optimizer_V on the projected tile; moments e1/e2 and output c are [M][N]
-//               (e1/e2 hold bf16 values when GemmUniform::moment_bf16 is set)
+//   EP_ADAM   : Optimizer_V on the projected tile; moments e1/e2 and output c are [M][N], row
+//               stride ldc (e1/e2 hold bf16 values when GemmUniform::moment_bf16 is set); on the
+//               large-tile path ldc is a multiple of 4 and c is blocked (rows M, K = N padded)
 //   EP_UPDATE : W[i][j] -= lr * scale * dM[i][j/B] * C[i][j] (bf16 or fp32 W in c)
 //   EP_STORE  : c[i*ldc + j] = C[i][j] (fp32)
 //   EP_STORE_BF16: c[i*ldc + j] = bf16(C[i][j])   (large-tile path only)
@@ -121,6 +122,6 @@ int gemm_f32_fit(GemmProb* probs, int n, uint32_t* total);
 uint32_t gemm_nt_tiles_m(int64_t M);
 uint32_t gemm_nt_tiles_n(int64_t N);
 bool gemm_nt_eligible(int ep, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc,
-                      const void* a, const void* b, const void* c, int weight_bf16);
+                      const void* a, const void* b, const void* c);
 hipError_t launch_gemm_nt(int ep, const GemmProb* probs_dev, int nprob, uint32_t total_tiles, const GemmUniform& u,
                           hipStream_t st);

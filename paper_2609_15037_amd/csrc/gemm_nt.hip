@@ -48,6 +48,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+// eight bf16 / four fp32 weights at any address a row of odd length or a caller's view gives
+typedef unsigned int u32x4_w2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef float f32x4_w4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void lds_void;
 
@@ -67,6 +70,12 @@ __device__ __forceinline__ void wait_vm(int n) {
     default: __builtin_amdgcn_s_waitcnt(0x0F7F); break;
   }
 #undef WVM
+}
+
+// the first n of four columns, zeros for the rest: the padding of the moments and of N (their
+// rows hold whole 4-column groups) stays at zero
+__device__ __forceinline__ float4 keep_cols(float4 v, int n) {
+  return make_float4(v.x, n > 1 ? v.y : 0.f, n > 2 ? v.z : 0.f, n > 3 ? v.w : 0.f);
 }
 
 // Workgroup barrier for the stage ring: each wave has already waited (vmcnt) for its
@@ -357,7 +366,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, (OCC * NWM * NWN + 3) / 4) void k_g
         const int rr = PR * (h % NPC) + RPP * p + lane / LPR;
         const int64_t row = wrow0 + PR * h + RPP * p + lane / LPR;
         if (row < P.M && col < P.N) {
-          const float4 v = *reinterpret_cast<const float4*>(slab + rr * EPLD + cc);
+          const float4 v = keep_cols(*reinterpret_cast<const float4*>(slab + rr * EPLD + cc), (int)(P.N - col));
           const float vv[4] = {v.x, v.y, v.z, v.w};
           const int64_t idx = row * P.ldc + col;
           bf16x4 e = ev[h % DB][p], q = qv[h % DB][p], o;
@@ -370,7 +379,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, (OCC * NWM * NWN + 3) / 4) void k_g
           }
           __builtin_nontemporal_store(__builtin_bit_cast(u32x2, e), reinterpret_cast<u32x2*>(reinterpret_cast<bf16*>(P.e1) + idx));
           __builtin_nontemporal_store(__builtin_bit_cast(u32x2, q), reinterpret_cast<u32x2*>(reinterpret_cast<bf16*>(P.e2) + idx));
-          *reinterpret_cast<bf16x4*>((bf16*)P.c + ((P.kp & 4) ? kp_index(row, col, P.M) : idx)) = o;
+          *reinterpret_cast<bf16x4*>((bf16*)P.c + kp_index(row, col, P.M)) = o;
         }
       }
     };
@@ -410,7 +419,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, (OCC * NWM * NWN + 3) / 4) void k_g
         const int rr = PR * (h % NPC) + RPP * p + lane / LPR;
         const int64_t row = wrow0 + PR * h + RPP * p + lane / LPR;
         if (row < P.M && col < P.N) {
-          const float4 v = *reinterpret_cast<const float4*>(slab + rr * EPLD + cc);
+          const float4 v = keep_cols(*reinterpret_cast<const float4*>(slab + rr * EPLD + cc), (int)(P.N - col));
           const int64_t idx = row * P.ldc + col;
           float4 e = ev[h % DB][p], q = qv[h % DB][p];
           bf16x4 o;
@@ -420,7 +429,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, (OCC * NWM * NWN + 3) / 4) void k_g
           o[3] = f2bf(adam_out(v.w, e.w, q.w, U.beta1, U.beta2, U.adam_eps, P.bc1, P.bc2));
           *reinterpret_cast<float4*>(P.e1 + idx) = e;
           *reinterpret_cast<float4*>(P.e2 + idx) = q;
-          *reinterpret_cast<bf16x4*>((bf16*)P.c + ((P.kp & 4) ? kp_index(row, col, P.M) : idx)) = o;
+          *reinterpret_cast<bf16x4*>((bf16*)P.c + kp_index(row, col, P.M)) = o;
         }
       }
     };
@@ -434,16 +443,20 @@ __global__ __launch_bounds__(64 * NWM * NWN, (OCC * NWM * NWN + 3) / 4) void k_g
       compute_piece(h);
     }
   } else {
-    // LPR lanes x 8 columns per row, RPP rows per pass, PPS passes per slab
+    // LPR lanes x 8 columns per row, RPP rows per pass, PPS passes per slab. W rows may start at
+    // any element; a wave whose columns end inside an 8-column group takes the general form (a
+    // tail test per group in the vector form cost the back-projection 5 % at every size).
     constexpr int LPR = WTN / 8, RPP = 64 / LPR, PPS = 32 / RPP;
     const int cc = 8 * (lane % LPR);
     const int64_t col = wcol0 + cc;
-    const bool one_mag = (U.B & 7) == 0;   // 8 aligned columns never straddle a block
-    if (U.weight_bf16 && one_mag) {
+    const int nin = (int)(P.N - col);                 // columns of this lane's group inside the row (if > 0)
+    const bool one_mag = !P.dM || (U.B & 7) == 0;     // 8 aligned columns never straddle a block
+    if (U.weight_bf16 && one_mag && ((P.N & 7) == 0 || wcol0 + WTN <= P.N)) {
       // W and magnitudes DB slabs ahead (register double buffer with one workgroup per CU)
       constexpr int DB = EPDB_UPD;
       bf16x8 wv[DB][PPS];
       float mg[DB][PPS];
+      const uint32_t mcol = P.dM ? (uint32_t)col / (uint32_t)U.B : 0u;
       auto load_w = [&](int mb) {
 #pragma unroll
         for (int p = 0; p < PPS; ++p) {
@@ -452,8 +465,8 @@ __global__ __launch_bounds__(64 * NWM * NWN, (OCC * NWM * NWN + 3) / 4) void k_g
           if (row < P.M && col < P.N) {
             // W is read and written once per step: non-temporal, as the moments above
             wv[mb % DB][p] = __builtin_bit_cast(
-                bf16x8, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>((const bf16*)P.c + row * P.ldc + col)));
-            if (P.dM) mg[mb % DB][p] = P.dM[row * P.dM_ld + col / U.B];
+                bf16x8, __builtin_nontemporal_load(reinterpret_cast<const u32x4_w2*>((const bf16*)P.c + row * P.ldc + col)));
+            if (P.dM) mg[mb % DB][p] = P.dM[row * P.dM_ld + mcol];
           }
         }
       };
@@ -474,51 +487,48 @@ __global__ __launch_bounds__(64 * NWM * NWN, (OCC * NWM * NWN + 3) / 4) void k_g
             bf16x8 o;
 #pragma unroll
             for (int q = 0; q < 8; ++q) o[q] = f2bf(bf2f(wv[mb % DB][p][q]) - U.lr * bf2f(f2bf(U.scale * (m * v[q]))));
-            __builtin_nontemporal_store(__builtin_bit_cast(u32x4, o), reinterpret_cast<u32x4*>((bf16*)P.c + row * P.ldc + col));
+            __builtin_nontemporal_store(__builtin_bit_cast(u32x4, o), reinterpret_cast<u32x4_w2*>((bf16*)P.c + row * P.ldc + col));
           }
         }
         if (mb + DB < MB) load_w(mb + DB);
       }
     } else {
-      // general form: fp32 W, or block sizes that split an 8-column group
+      // general form: fp32 W, or block sizes that split an 8-column group; four columns at a time
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
         stage_slab(mb);
 #pragma unroll 2
-        for (int p = 0; p < PPS; ++p) {
-          const int rr = RPP * p + lane / LPR;
+        for (int p = 0; p < 2 * PPS; ++p) {
+          const int rr = RPP * (p >> 1) + lane / LPR, h = 4 * (p & 1);
           const int64_t row = wrow0 + 32 * mb + rr;
-          if (row < P.M && col < P.N) {
-            const float4 v0 = *reinterpret_cast<const float4*>(slab + rr * EPLD + cc);
-            const float4 v1 = *reinterpret_cast<const float4*>(slab + rr * EPLD + cc + 4);
-            const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-            float mag[8];
-            if (P.dM) {
-              const float* dmr = P.dM + row * P.dM_ld;
+          if (row < P.M && nin > h) {
+            const float4 v4 = *reinterpret_cast<const float4*>(slab + rr * EPLD + cc + h);
+            const float v[4] = {v4.x, v4.y, v4.z, v4.w};
+            const bool full = nin >= h + 4;
+            float u[4];
 #pragma unroll
-              for (int q = 0; q < 8; ++q) mag[q] = dmr[(col + q) / U.B];
-            } else {
-#pragma unroll
-              for (int q = 0; q < 8; ++q) mag[q] = 1.f;
+            for (int q = 0; q < 4; ++q) {
+              const uint32_t c = (uint32_t)col + h + (h + q < nin ? q : 0);
+              u[q] = U.scale * ((P.dM ? P.dM[row * P.dM_ld + c / (uint32_t)U.B] : 1.f) * v[q]);
             }
-            const int64_t idx = row * P.ldc + col;
+            const int64_t idx = row * P.ldc + col + h;
             if (U.weight_bf16) {
               bf16* W = (bf16*)P.c + idx;
-              const bf16x8 w = *reinterpret_cast<const bf16x8*>(W);
-              bf16x8 o;
 #pragma unroll
-              for (int q = 0; q < 8; ++q) o[q] = f2bf(bf2f(w[q]) - U.lr * bf2f(f2bf(U.scale * (mag[q] * v[q]))));
-              *reinterpret_cast<bf16x8*>(W) = o;
+              for (int q = 0; q < 4; ++q)
+                if (h + q < nin) W[q] = f2bf(bf2f(W[q]) - U.lr * bf2f(f2bf(u[q])));
             } else {
               float* W = (float*)P.c + idx;
-              float4 w0 = *reinterpret_cast<const float4*>(W);
-              float4 w1 = *reinterpret_cast<const float4*>(W + 4);
-              w0.x -= U.lr * (U.scale * (mag[0] * v[0])); w0.y -= U.lr * (U.scale * (mag[1] * v[1]));
-              w0.z -= U.lr * (U.scale * (mag[2] * v[2])); w0.w -= U.lr * (U.scale * (mag[3] * v[3]));
-              w1.x -= U.lr * (U.scale * (mag[4] * v[4])); w1.y -= U.lr * (U.scale * (mag[5] * v[5]));
-              w1.z -= U.lr * (U.scale * (mag[6] * v[6])); w1.w -= U.lr * (U.scale * (mag[7] * v[7]));
-              *reinterpret_cast<float4*>(W) = w0;
-              *reinterpret_cast<float4*>(W + 4) = w1;
+              if (full) {
+                f32x4_w4 x = *reinterpret_cast<const f32x4_w4*>(W);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) x[q] -= U.lr * u[q];
+                *reinterpret_cast<f32x4_w4*>(W) = x;
+              } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                  if (h + q < nin) W[q] -= U.lr * u[q];
+              }
             }
           }
         }
@@ -572,24 +582,18 @@ uint32_t gemm_nt_tiles_m(int64_t M) { return (uint32_t)((M + TBM - 1) / TBM); }
 uint32_t gemm_nt_tiles_n(int64_t N) { return (uint32_t)((N + GEMM_NT_BN - 1) / GEMM_NT_BN); }
 
 bool gemm_nt_eligible(int ep, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc,
-                      const void* a, const void* b, const void* c, int weight_bf16) {
+                      const void* a, const void* b, const void* c) {
   if (M <= 0 || N <= 0 || K <= 0 || K % TBK) return false;
   if (lda % 8 || ldb % 8 || lda < K || ldb < K) return false;
   if (((uintptr_t)a & 15) || ((uintptr_t)b & 15)) return false;
   // byte extents must fit the 32-bit buffer offsets
   if ((M - 1) * lda * 2 + K * 2 > 0x7FFFFFFFLL || (N - 1) * ldb * 2 + K * 2 > 0x7FFFFFFFLL) return false;
-  // the epilogue operands are addressed through 32-bit buffer offsets as well
-  if (M * ldc * (ep == EP_ADAM ? 4 : 2) > 0x7FFFFFFFLL) return false;
+  if (M * ldc * 2 > 0x7FFFFFFFLL) return false;
   if (ep == EP_STORE || ep == EP_STORE_BF16) {   // 4-column groups, 16- (8-) byte aligned
     const int esz = ep == EP_STORE ? 4 : 2;
     if (N % 4 || ldc % 4 || ((uintptr_t)c & (4 * esz - 1))) return false;
-  } else if (ep == EP_ADAM) {   // moments and N: 4-column groups (library memory, aligned)
-    if (N % 4 || ldc % 4) return false;
-  } else {                      // W: 8-column groups, 16-byte aligned rows
-    const int esz = weight_bf16 ? 2 : 4;
-    if (N % 8 || ldc % 8 || ((uintptr_t)c & 15) || (ldc * esz) % 16) return false;
   }
-  return true;
+  return true;   // EP_UPDATE takes W at any element alignment
 }
 
 namespace {

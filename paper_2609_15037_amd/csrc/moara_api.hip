@@ -84,9 +84,12 @@ struct MatHost {
   void *exp1 = nullptr, *exp2 = nullptr;   // Optimizer_V moments, L x r, fp32 or bf16 (moment_dtype)
   float* P32 = nullptr;
   void *N = nullptr, *Pop = nullptr, *Ptop = nullptr;
-  bool vpath = false;    // the decomposition writes V in bf16 for the large-tile projection
-  void* V = nullptr;     // L x s bf16 direction workspace, blocked layout (kp_index, K = s)
-  bool kp = false;       // Ptop (K = s), Pop and N (K = r) in the blocked layout too
+  bool vpath = false;    // large-tile path: the decomposition writes V in bf16, and V, Ptop (K = s),
+                         // Pop and N (K = r) are in the blocked layout, K padded with zeros to 32
+  bool vref = false;     // ... and the refresh may iterate on V (no padding, see refresh_v_ok)
+  void* V = nullptr;     // L x s bf16 direction workspace
+  int64_t sp = 0, rp = 0;   // s and r rounded up to 32 (vpath), else s and r
+  int64_t ldr = 0;       // row stride of exp1 / exp2: r, rounded up to 4 on the large-tile path
 };
 
 struct TimedLaunch {
@@ -209,30 +212,52 @@ int32_t subspace_width(const moara_config& c, int64_t s, int32_t r) {
   return (int32_t)std::min<int64_t>(s, r + p);
 }
 
-// Shapes for which the decomposition materialises V in bf16 and the projection runs
-// on the large-tile bf16 GEMM (see decompose.hip / gemm_nt.hip for the limits).
+// Matrices whose step runs on the large-tile bf16 GEMM: the decomposition materialises V in
+// bf16 and every operand the library owns is stored in the blocked layout, its reduction
+// length padded with zeros to whole 32-wide panels, so s, r, n and the caller's alignment are
+// free. The limits are the block sizes a lane group can reduce (without the decomposition V
+// is G itself and any B does), the row-major decomposition's LDS and the GEMM's 32-bit buffer
+// extents. With 128 x 128 tiles that form V while staging it (before, for these sizes) six
+// d = 1000, ffn = 2666 layers took 938 us a step and now take 403, six d = 1024 layers without
+// the decomposition 422 and now 351.
+int64_t pad32(int64_t x) { return (x + 31) / 32 * 32; }
 bool vpath_shape_ok(const moara_config& c, int64_t m, int64_t n, int side, int32_t r) {
-  if (c.operand_dtype != MOARA_BF16 || !c.decompose) return false;
+  if (c.operand_dtype != MOARA_BF16) return false;
   const int B = c.block_size;
-  if (B < 4 || B > 256 || (B & (B - 1))) return false;
+  if (c.decompose) {
+    if (B < 4 || B > 256 || (B & (B - 1))) return false;
+    if (side == MOARA_SIDE_RIGHT && (n + B - 1) / B > DEC_ROW_MAX_K) return false;
+  }
+  const int64_t s = side == MOARA_SIDE_LEFT ? m : n, L = side == MOARA_SIDE_LEFT ? n : m;
+  const int64_t lim = 0x7FFFFFFFLL;
+  return 2 * L * pad32(s) <= lim && 4 * L * pad32(r) <= lim && 2 * s * pad32(r) <= lim && 2 * m * n <= lim;
+}
+// Of those, the matrices whose projector refresh may iterate on the bf16 V (given an aligned
+// gradient); the others' iterations are fp32 products on G, as their results have always been.
+bool refresh_v_ok(const moara_config& c, int64_t m, int64_t n, int side, int32_t r) {
+  if (!c.decompose || !vpath_shape_ok(c, m, n, side, r)) return false;
   if (n % 4 || r % 4) return false;
-  const int64_t k = (n + B - 1) / B;
-  if (2 * m * n > 0x7FFFFFFFLL) return false;
-  if (side == MOARA_SIDE_LEFT) return k <= DEC_VT_MAX_K && m % 32 == 0;
-  return k <= DEC_ROW_MAX_K && n % 32 == 0;
+  if (side == MOARA_SIDE_LEFT) return (n + c.block_size - 1) / c.block_size <= DEC_VT_MAX_K && m % 32 == 0;
+  return n % 32 == 0;
 }
 
+// Bytes of one matrix in the state's block: what the state holds, and, in *pad_ws, the step
+// workspace of a padded matrix (one on the large-tile path by its padding only: V, and the
+// panels' padding of N, Pop and Ptop).
 size_t mat_state_bytes(const moara_config& c, int64_t m, int64_t n, int side, int64_t s, int64_t L, int64_t k,
-                       int32_t r) {
+                       int32_t r, size_t* pad_ws) {
   const int ob = elem_bytes(c.operand_dtype);
-  size_t b = 0;
-  if (vpath_shape_ok(c, m, n, side, r)) b += align_up(2 * (size_t)m * n);   // V workspace
+  const bool vp = vpath_shape_ok(c, m, n, side, r), own = refresh_v_ok(c, m, n, side, r);
+  const int64_t sp = vp ? pad32(s) : s, rp = vp ? pad32(r) : r, ldr = vp ? (r + 3) / 4 * 4 : r;
+  size_t b = 0, ops = 0, ops_pad = 0;
   b += align_up(4 * m * k) * 4;          // inv, dM, mag1, mag2
-  b += align_up((size_t)elem_bytes(c.moment_dtype) * L * r) * 2;   // exp1, exp2
-  b += align_up((size_t)ob * L * r);     // N
+  b += align_up((size_t)elem_bytes(c.moment_dtype) * L * ldr) * 2;   // exp1, exp2
   b += align_up(4 * s * r);              // P32
-  b += align_up((size_t)ob * s * r) * 2; // Pop, Ptop
-  return b;
+  ops = align_up((size_t)ob * L * r) + 2 * align_up((size_t)ob * s * r);                                // N, Pop, Ptop
+  ops_pad = align_up((size_t)ob * L * rp) + align_up((size_t)ob * s * rp) + align_up((size_t)ob * r * sp);
+  const size_t v = vp ? align_up(2 * (size_t)L * sp) : 0;
+  if (pad_ws) *pad_ws = (own ? 0 : v) + (ops_pad - ops);
+  return b + ops + (own ? v : 0);
 }
 
 // bf: the matrix runs its early subspace iterations on the bf16 V (other orientation
@@ -431,8 +456,9 @@ GemmUniform make_uniform(const moara_state* st, float lr) {
 int run_decompose(moara_state* st, const std::vector<int>& idx, const void* const* grads, bool adam_m,
                   hipStream_t stream, const std::vector<char>* usev = nullptr) {
   if (idx.empty()) return MOARA_OK;
-  std::vector<MatDev> md, mvt;
-  uint32_t tiles = 0, tiles_vt = 0;
+  // four lists: row-major and transposed V, each split into plain and other matrices
+  std::vector<MatDev> md[4];
+  uint32_t tiles[4] = {0, 0, 0, 0};
   for (int i : idx) {
     const MatHost& h = st->mats[i];
     MatDev d{};
@@ -443,39 +469,34 @@ int run_decompose(moara_state* st, const std::vector<int>& idx, const void* cons
     d.bc1 = st->cfg.bias_correction ? (float)(1.0 - pow((double)st->cfg.beta1, t1)) : 1.f;
     d.bc2 = st->cfg.bias_correction ? (float)(1.0 - pow((double)st->cfg.beta2, t1)) : 1.f;
     const bool wv = usev && (*usev)[i];
-    if (wv && h.side == MOARA_SIDE_LEFT) {
-      d.Vb = (bf16*)h.V; d.vt = 1;
-      d.tile_dec = tiles_vt;
-      tiles_vt += (uint32_t)decompose_vt_tiles(h.m);
-      mvt.push_back(d);
-    } else {
-      d.Vb = wv ? (bf16*)h.V : nullptr; d.vt = 0;
-      d.tile_dec = tiles;
-      tiles += (uint32_t)decompose_tiles(h.m);
-      md.push_back(d);
-    }
+    if (!st->cfg.decompose && !wv) continue;   // V = G is read where it is
+    const bool vt = wv && h.side == MOARA_SIDE_LEFT;
+    d.Vb = wv ? (bf16*)h.V : nullptr;
+    d.vt = vt ? 1 : 0;
+    const int q = 2 * (vt ? 1 : 0) + (decompose_plain(d.G, h.n, h.k, st->cfg.decompose != 0, vt) ? 0 : 1);
+    d.tile_dec = tiles[q];
+    tiles[q] += (uint32_t)(vt ? decompose_vt_tiles(h.m) : decompose_tiles(h.m));
+    md[q].push_back(d);
   }
   Stager sg;
   int rc = begin_stage(st, sg);
   if (rc) return rc;
-  const size_t off = md.empty() ? 0 : sg.push(md.data(), md.size());
-  const size_t offv = mvt.empty() ? 0 : sg.push(mvt.data(), mvt.size());
-  if (off == (size_t)-1 || offv == (size_t)-1) return fail(MOARA_E_OOM, "descriptor arena too small");
+  size_t off[4] = {};
+  for (int q = 0; q < 4; ++q)
+    if (!md[q].empty() && (off[q] = sg.push(md[q].data(), md[q].size())) == (size_t)-1)
+      return fail(MOARA_E_OOM, "descriptor arena too small");
   rc = end_stage(st, sg, stream);
   if (rc) return rc;
   TimerScope ts(st, MOARA_KERN_DECOMPOSE, stream);
-  if (!mvt.empty()) {
+  for (int q = 3; q >= 0; --q) {
+    if (md[q].empty()) continue;
     StepParams p = make_params(st, 0.f);
-    p.nmat = (int)mvt.size();
-    p.total_dec = tiles_vt;
-    HIP_TRY(launch_decompose_vt((const MatDev*)(st->dev_arena + offv), p, adam_m ? 1 : 0, stream));
-  }
-  if (!md.empty()) {
-    StepParams p = make_params(st, 0.f);
-    p.nmat = (int)md.size();
-    p.total_dec = tiles;
-    const MatDev* dev = (const MatDev*)(st->dev_arena + off);
-    HIP_TRY(adam_m ? launch_decompose(dev, p, stream) : launch_decompose_inv_only(dev, p, stream));
+    p.nmat = (int)md[q].size();
+    p.total_dec = tiles[q];
+    const MatDev* dev = (const MatDev*)(st->dev_arena + off[q]);
+    const bool plain = (q & 1) == 0;
+    HIP_TRY(q >= 2 ? launch_decompose_vt(dev, p, adam_m ? 1 : 0, plain, stream)
+                   : launch_decompose(dev, p, adam_m ? 1 : 0, plain, stream));
   }
   return MOARA_OK;
 }
@@ -483,11 +504,9 @@ int run_decompose(moara_state* st, const std::vector<int>& idx, const void* cons
 // back_only (indexed by matrix, may be null): N was formed without a projection (zero
 // gradient); only the back-projection and update run for that matrix.
 int run_project_back(moara_state* st, const std::vector<int>& idx, void* const* weights, const void* const* grads,
-                     float lr, hipStream_t stream, const std::vector<char>* usev = nullptr,
-                     const std::vector<char>* back_only = nullptr) {
+                     float lr, hipStream_t stream, const std::vector<char>* back_only = nullptr) {
   const int ob = st->cfg.operand_dtype == MOARA_BF16;
   const int kind = ob ? KIND_BF16 : KIND_F32;
-  const int wbf = st->cfg.weight_dtype == MOARA_BF16;
   std::vector<GemmProb> left, right, back, pnt, bnt;
   uint32_t tl = 0, tr = 0, tb = 0, tpn = 0, tbn = 0;
   for (int i : idx) {
@@ -495,52 +514,42 @@ int run_project_back(moara_state* st, const std::vector<int>& idx, void* const* 
     const double t1 = (double)(h.t + 1);
     const float bc1 = st->cfg.bias_correction ? (float)(1.0 - pow((double)st->cfg.beta1, t1)) : 1.f;
     const float bc2 = st->cfg.bias_correction ? (float)(1.0 - pow((double)st->cfg.beta2, t1)) : 1.f;
-    bool proj_done = false;
-    if (usev && (*usev)[i] &&
-        gemm_nt_eligible(EP_ADAM, h.L, h.r, h.s, h.s, h.s, h.r, h.V, h.Ptop, h.N, wbf)) {
+    const bool skip_proj = back_only && (*back_only)[i];
+    if (h.vpath && !skip_proj) {
       // V was written by this step's decomposition: R^(T) (L x r) = V' (L x s) * Ptop^T
       GemmProb g{};
-      g.M = h.L; g.N = h.r; g.K = h.s;
-      g.a = h.V; g.lda = h.s;
-      g.b = h.Ptop; g.ldb = h.s;
-      g.c = h.N; g.ldc = h.r;
-      g.kp = 1 | (h.kp ? 2 | 4 : 0);
+      g.M = h.L; g.N = h.r; g.K = h.sp;
+      g.a = h.V; g.lda = h.sp;
+      g.b = h.Ptop; g.ldb = h.sp;
+      g.c = h.N; g.ldc = h.ldr;
+      g.kp = 1 | 2 | 4;
       g.e1 = (float*)h.exp1; g.e2 = (float*)h.exp2;
       g.bc1 = bc1; g.bc2 = bc2;
-      g.a_bytes = (uint32_t)(2 * (size_t)h.L * h.s);
-      g.b_bytes = (uint32_t)(2 * (size_t)h.r * h.s);
+      g.a_bytes = (uint32_t)(2 * (size_t)h.L * h.sp);
+      g.b_bytes = (uint32_t)(2 * (size_t)h.r * h.sp);
       g.tiles_n = gemm_nt_tiles_n(g.N);
       g.tile_start = tpn;
       tpn += gemm_nt_tiles_m(g.M) * g.tiles_n;
       pnt.push_back(g);
-      proj_done = true;
     }
     {
       const size_t rows_a = h.side == MOARA_SIDE_LEFT ? h.s : h.L, rows_b = h.side == MOARA_SIDE_LEFT ? h.L : h.s;
-      const void* ba = h.side == MOARA_SIDE_LEFT ? h.Pop : h.N;
-      const void* bb = h.side == MOARA_SIDE_LEFT ? h.N : h.Pop;
-      if (ob && gemm_nt_eligible(EP_UPDATE, h.m, h.n, h.r, h.r, h.r, h.n, ba, bb, weights[i], wbf)) {
-        GemmProb b{};
-        b.M = h.m; b.N = h.n; b.K = h.r;
-        b.a = ba; b.b = bb;
-        b.lda = h.r; b.ldb = h.r;
-        b.kp = h.kp ? 3 : 0;
-        b.c = weights[i]; b.ldc = h.n;
-        b.dM = st->cfg.decompose ? h.dM : nullptr; b.dM_ld = h.k;
-        b.a_bytes = (uint32_t)(2 * rows_a * h.r);
-        b.b_bytes = (uint32_t)(2 * rows_b * h.r);
+      GemmProb b{};
+      b.M = h.m; b.N = h.n; b.K = h.rp;
+      b.a = h.side == MOARA_SIDE_LEFT ? h.Pop : h.N;
+      b.b = h.side == MOARA_SIDE_LEFT ? h.N : h.Pop;
+      b.lda = h.rp; b.ldb = h.rp;
+      b.kp = h.vpath ? 3 : 0;
+      b.c = weights[i]; b.ldc = h.n;
+      b.dM = st->cfg.decompose ? h.dM : nullptr; b.dM_ld = h.k;
+      if (h.vpath || (ob && gemm_nt_eligible(EP_UPDATE, h.m, h.n, h.rp, h.rp, h.rp, h.n, b.a, b.b, weights[i]))) {
+        b.a_bytes = (uint32_t)(2 * rows_a * h.rp);
+        b.b_bytes = (uint32_t)(2 * rows_b * h.rp);
         b.tiles_n = gemm_nt_tiles_n(b.N);
         b.tile_start = tbn;
         tbn += gemm_nt_tiles_m(b.M) * b.tiles_n;
         bnt.push_back(b);
       } else {
-        GemmProb b{};
-        b.M = h.m; b.N = h.n; b.K = h.r;
-        b.a = ba; b.b = bb;
-        b.lda = h.r; b.ldb = h.r;
-        b.kp = h.kp ? 3 : 0;
-        b.c = weights[i]; b.ldc = h.n;
-        b.dM = st->cfg.decompose ? h.dM : nullptr; b.dM_ld = h.k;
         b.tiles_n = gemm_tiles_n(kind, b.N);
         b.vec = vec_flags_op(b.a, h.r, ob) | (vec_flags_op(b.b, h.r, ob) << 1);
         const size_t e = ob ? 2 : 4;
@@ -550,14 +559,13 @@ int run_project_back(moara_state* st, const std::vector<int>& idx, void* const* 
         back.push_back(b);
       }
     }
-    if (proj_done || (back_only && (*back_only)[i])) continue;
+    if (h.vpath || skip_proj) continue;
     GemmProb g{};
     g.M = h.L; g.N = h.r; g.K = h.s;
     g.a = grads[i]; g.lda = h.n;
     g.inv = st->cfg.decompose ? h.inv : nullptr; g.inv_ld = h.k;
     g.b = h.Ptop; g.ldb = h.s;
     g.c = h.N; g.ldc = h.r;
-    g.kp = h.kp ? 2 | 4 : 0;
     g.e1 = (float*)h.exp1; g.e2 = (float*)h.exp2;
     g.bc1 = bc1;
     g.bc2 = bc2;
@@ -618,7 +626,7 @@ int run_zero_grad(moara_state* st, const std::vector<int>& zidx, hipStream_t str
   for (int i : zidx) {
     MatHost& h = st->mats[i];
     if (T > 0 && h.t % T == 0 && !h.hasP) {
-      HIP_TRY(launch_canonical_projector(h.P32, h.Pop, h.Ptop, h.s, h.r, obf, h.kp ? 1 : 0, stream));
+      HIP_TRY(launch_canonical_projector(h.P32, h.Pop, h.Ptop, h.s, h.r, obf, h.vpath ? 1 : 0, stream));
       h.hasP = true;
     }
   }
@@ -629,9 +637,9 @@ int run_zero_grad(moara_state* st, const std::vector<int>& zidx, hipStream_t str
     MatDev d{};
     d.m = h.m; d.n = h.n; d.k = h.k; d.r = h.r; d.side = h.side; d.L = (int32_t)h.L; d.s = (int32_t)h.s;
     d.dM = h.dM; d.mag1 = h.mag1; d.mag2 = h.mag2;
-    d.exp1 = (float*)h.exp1; d.exp2 = (float*)h.exp2; d.N = h.N;
+    d.exp1 = (float*)h.exp1; d.exp2 = (float*)h.exp2; d.N = h.N; d.ldr = (int32_t)h.ldr;
     d.mom_bf16 = st->cfg.moment_dtype == MOARA_BF16;
-    d.n_bf16 = obf; d.n_kp = h.kp ? 1 : 0;
+    d.n_bf16 = obf; d.n_kp = h.vpath ? 1 : 0;
     const double t1 = (double)(h.t + 1);
     d.bc1 = st->cfg.bias_correction ? (float)(1.0 - pow((double)st->cfg.beta1, t1)) : 1.f;
     d.bc2 = st->cfg.bias_correction ? (float)(1.0 - pow((double)st->cfg.beta2, t1)) : 1.f;
@@ -729,9 +737,9 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
     x.w = subspace_width(c, h.s, h.r);
     x.wpad = (x.w + 63) / 64 * 64;
     x.bf = usev && (*usev)[i] && c.refresh_iters > REFRESH_F32_ITERS && x.w % 8 == 0 &&
-           gemm_nt_eligible(EP_STORE_BF16, x.w, h.L, h.s, h.s, h.s, h.L, h.V, h.V, h.V, 0) &&
-           gemm_nt_eligible(EP_STORE, h.s, x.w, h.L, h.L, h.L, x.w, h.V, h.V, h.V, 0) &&
-           gemm_nt_eligible(EP_STORE, h.L, x.w, h.s, h.s, h.s, x.w, h.V, h.V, h.V, 0);
+           gemm_nt_eligible(EP_STORE_BF16, x.w, h.L, h.s, h.s, h.s, h.L, h.V, h.V, h.V) &&
+           gemm_nt_eligible(EP_STORE, h.s, x.w, h.L, h.L, h.L, x.w, h.V, h.V, h.V) &&
+           gemm_nt_eligible(EP_STORE, h.L, x.w, h.s, h.s, h.s, x.w, h.V, h.V, h.V);
     need += mat_refresh_bytes(h.s, h.L, x.w, h.r, x.bf);
     rm.push_back(x);
   }
@@ -802,7 +810,7 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
     d.seed = c.refresh_seed * 0x9E3779B97F4A7C15ull + (uint64_t)(x.idx + 1) * 0xD1B54A32D192ED03ull;
     d.Z = x.Z2; d.Z0 = orth0 ? x.Z2 : x.Z; d.C = x.C; d.X = x.X; d.cmax = x.cmax; d.Rinv = x.Rinv; d.Zc = x.Zc;
     d.jl = x.w; d.Q = x.Z; d.Pw = x.Pw; d.Bt = x.Bt;
-    d.P32 = h.P32; d.Pop = h.Pop; d.Ptop = h.Ptop; d.kp = h.kp ? 1 : 0;
+    d.P32 = h.P32; d.Pop = h.Pop; d.Ptop = h.Ptop; d.kp = h.vpath ? 1 : 0;
     d.off = x.off; d.order = x.order; d.norms = x.norms;
     d.jconv = x.jconv; d.jmx = x.jmx; d.jmod = x.jmod;
     d.tile_gauss = tg; tg += gauss_tiles(x.s, x.w);
@@ -952,7 +960,7 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
     const MatHost& h = st->mats[x.idx];
     // (Z2's parts live in Y..Y2: 3 s <= 4 L, which the automatic side choice, s <= L, meets)
     use_qz = x.w % 32 == 0 && 3 * x.s <= 4 * x.L &&
-             gemm_nt_eligible(EP_STORE_BF16, x.w, h.s, x.w, x.w, x.w, h.s, h.V, h.V, h.V, 0);
+             gemm_nt_eligible(EP_STORE_BF16, x.w, h.s, x.w, x.w, x.w, h.s, h.V, h.V, h.V);
     if (!use_qz) break;
   }
   for (int q = 0; q < nm; ++q) {
@@ -1361,8 +1369,8 @@ struct NoallocView {
 int run_refresh(moara_state* st, const std::vector<int>& idx, const void* const* grads, hipStream_t stream) {
   if (idx.empty()) return MOARA_OK;
   std::vector<char> usev(st->n, 0);
-  for (int i : idx) usev[i] = st->mats[i].vpath && (((uintptr_t)grads[i] & 15) == 0);
-  int rc = run_decompose(st, idx, grads, false, stream, &usev);
+  for (int i : idx) usev[i] = st->mats[i].vref && (((uintptr_t)grads[i] & 15) == 0);
+  int rc = st->cfg.decompose ? run_decompose(st, idx, grads, false, stream, &usev) : MOARA_OK;
   if (rc) return rc;
   return refresh_in_chunks(st, idx, grads, stream, usev);
 }
@@ -1459,16 +1467,18 @@ int moara_state_bytes(const moara_config* cfg, const moara_matrix_desc* descs, i
   int rc = validate_all(cfg, descs, n, &ranks, &sides);
   if (rc) return rc;
   if (!out_state_bytes) return fail(MOARA_E_ARG, "out_state_bytes is NULL");
-  size_t tot = 0, ref = 0;
+  size_t tot = 0, ref = 0, pad = 0;
   for (int i = 0; i < n; ++i) {
     const Layout l = layout_of(descs[i], sides[i], cfg->block_size);
-    tot += mat_state_bytes(*cfg, descs[i].rows, descs[i].cols, sides[i], l.s, l.L, l.k, ranks[i]);
+    size_t pad_ws = 0;
+    tot += mat_state_bytes(*cfg, descs[i].rows, descs[i].cols, sides[i], l.s, l.L, l.k, ranks[i], &pad_ws);
+    pad += pad_ws;
     ref += mat_refresh_bytes(l.s, l.L, subspace_width(*cfg, l.s, ranks[i]), ranks[i],
-                             vpath_shape_ok(*cfg, descs[i].rows, descs[i].cols, sides[i], ranks[i]));
+                             refresh_v_ok(*cfg, descs[i].rows, descs[i].cols, sides[i], ranks[i]));
   }
   tot += align_up(16 * (size_t)n);   // refresh records
   *out_state_bytes = (int64_t)tot;
-  if (out_refresh_workspace_bytes) *out_refresh_workspace_bytes = (int64_t)std::min(ref, refresh_budget() + ref / (size_t)n);
+  if (out_refresh_workspace_bytes) *out_refresh_workspace_bytes = (int64_t)(std::min(ref, refresh_budget() + ref / (size_t)n) + pad);
   return MOARA_OK;
 }
 
@@ -1510,8 +1520,13 @@ int moara_create_state(const moara_config* cfg, const moara_matrix_desc* descs, 
     h.m = descs[i].rows; h.n = descs[i].cols; h.r = ranks[i]; h.side = sides[i];
     h.s = l.s; h.L = l.L; h.k = (int32_t)l.k;
     h.vpath = vpath_shape_ok(*cfg, h.m, h.n, h.side, h.r);
-    h.kp = h.vpath && cfg->operand_dtype == MOARA_BF16 && h.r % 32 == 0;
-    tot += mat_state_bytes(*cfg, h.m, h.n, h.side, h.s, h.L, h.k, h.r);
+    h.vref = refresh_v_ok(*cfg, h.m, h.n, h.side, h.r);
+    h.sp = h.vpath ? pad32(h.s) : h.s;
+    h.rp = h.vpath ? pad32(h.r) : h.r;
+    h.ldr = h.vpath ? (h.r + 3) / 4 * 4 : h.r;
+    size_t pad_ws = 0;
+    tot += mat_state_bytes(*cfg, h.m, h.n, h.side, h.s, h.L, h.k, h.r, &pad_ws);
+    tot += pad_ws;
   }
   tot += align_up(16 * (size_t)n);   // refresh records
   if (hipMalloc(&st->block, tot) != hipSuccess) { free_state(st); return fail(MOARA_E_OOM, "state of %zu bytes", tot); }
@@ -1524,16 +1539,16 @@ int moara_create_state(const moara_config* cfg, const moara_matrix_desc* descs, 
     h.dM = (float*)take(4 * h.m * h.k);
     h.mag1 = (float*)take(4 * h.m * h.k);
     h.mag2 = (float*)take(4 * h.m * h.k);
-    h.exp1 = take((size_t)elem_bytes(cfg->moment_dtype) * h.L * h.r);
-    h.exp2 = take((size_t)elem_bytes(cfg->moment_dtype) * h.L * h.r);
-    h.N = take((size_t)ob * h.L * h.r);
+    h.exp1 = take((size_t)elem_bytes(cfg->moment_dtype) * h.L * h.ldr);
+    h.exp2 = take((size_t)elem_bytes(cfg->moment_dtype) * h.L * h.ldr);
+    h.N = take((size_t)ob * h.L * h.rp);
     h.P32 = (float*)take(4 * h.s * h.r);
-    h.Pop = take((size_t)ob * h.s * h.r);
-    h.Ptop = take((size_t)ob * h.s * h.r);
-    if (h.vpath) h.V = take(2 * (size_t)h.m * h.n);
+    h.Pop = take((size_t)ob * h.s * h.rp);
+    h.Ptop = take((size_t)ob * h.r * h.sp);
+    if (h.vpath) h.V = take(2 * (size_t)h.L * h.sp);
   }
   st->info_dev = (int32_t*)take(16 * (size_t)n);
-  st->arena_bytes = 2 * align_up(sizeof(MatDev) * n) + 5 * align_up(sizeof(GemmProb) * n) + 8 * ALIGN;
+  st->arena_bytes = 2 * align_up(sizeof(MatDev) * n) + 4 * ALIGN + 5 * align_up(sizeof(GemmProb) * n) + 8 * ALIGN;
   if (hipMalloc(&st->dev_arena, st->arena_bytes) != hipSuccess ||
       hipHostMalloc(&st->host_ring, st->arena_bytes * moara_state::NSLOT) != hipSuccess) {
     free_state(st);
@@ -1707,7 +1722,7 @@ static int step_impl(moara_state* st, void* const* weights, const void* const* g
     for (int i : need) {
       const MatHost& h = st->mats[i];
       const int32_t w = subspace_width(st->cfg, h.s, h.r);
-      const bool bf = h.vpath && (((uintptr_t)grads[i] & 15) == 0);
+      const bool bf = h.vref && (((uintptr_t)grads[i] & 15) == 0);
       const size_t b = mat_refresh_bytes(h.s, h.L, w, h.r, bf);
       if (b > wcap)
         return fail(MOARA_E_UNSUPPORTED,
@@ -1719,17 +1734,19 @@ static int step_impl(moara_state* st, void* const* weights, const void* const* g
   ORDER_ON(st, hs);
   if (noalloc && g_scratch_ev_valid[st->device]) HIP_TRY(hipStreamWaitEvent(hs, g_scratch_ev[st->device], 0));
   NoallocView view(st, base, noalloc);
-  std::vector<char> usev(st->n, 0);
-  for (int i : idx) usev[i] = st->mats[i].vpath && (((uintptr_t)grads[i] & 15) == 0);
-  if (st->cfg.decompose) {
-    rc = run_decompose(st, idx, grads, true, hs, &usev);
-    if (rc) return rc;
+  // the decomposition writes V for the projection of every large-tile matrix; the refresh
+  // iterates on it where refresh_v_ok allows that and the gradient is aligned
+  std::vector<char> usev(st->n, 0), refv(st->n, 0);
+  for (int i : idx) {
+    usev[i] = st->mats[i].vpath;
+    refv[i] = st->mats[i].vref && (((uintptr_t)grads[i] & 15) == 0);
   }
-  if (!need.empty() && (rc = refresh_in_chunks(st, need, grads, hs, usev))) return rc;
+  if ((rc = run_decompose(st, idx, grads, st->cfg.decompose != 0, hs, &usev))) return rc;
+  if (!need.empty() && (rc = refresh_in_chunks(st, need, grads, hs, refv))) return rc;
   if ((rc = run_zero_grad(st, zidx, hs))) return rc;
   std::vector<int> all = idx;
   all.insert(all.end(), zidx.begin(), zidx.end());
-  rc = run_project_back(st, all, weights, grads, lr, hs, &usev, &zflag);
+  rc = run_project_back(st, all, weights, grads, lr, hs, &zflag);
   if (rc) return rc;
   for (int i : all) st->mats[i].t += 1;
   if (noalloc) {
@@ -1784,12 +1801,13 @@ int moara_get_tensor(moara_state* st, int32_t mat, int32_t which, void* host_dst
   const bool narrow = moment && st->cfg.moment_dtype == MOARA_BF16;
   ORDER_ON(st, hs);
   HIP_TRY(hipStreamSynchronize(hs));
-  if (!transpose && !narrow) {
+  const int64_t ld = moment ? h.ldr : 0;   // moments: L rows of r values, row stride ldr
+  if (!transpose && !narrow && (!moment || ld == h.r)) {
     HIP_TRY(hipMemcpyAsync(host_dst, src, need, hipMemcpyDeviceToHost, hs));
     HIP_TRY(hipStreamSynchronize(hs));
     return MOARA_OK;
   }
-  const size_t cnt = (size_t)h.L * h.r;
+  const size_t cnt = (size_t)h.L * ld;
   std::vector<float> tmp(cnt);
   if (narrow) {
     std::vector<uint16_t> raw(cnt);
@@ -1797,17 +1815,17 @@ int moara_get_tensor(moara_state* st, int32_t mat, int32_t which, void* host_dst
     HIP_TRY(hipStreamSynchronize(hs));
     for (size_t i = 0; i < cnt; ++i) tmp[i] = host_bf16_to_f32(raw[i]);
   } else {
-    HIP_TRY(hipMemcpyAsync(tmp.data(), src, need, hipMemcpyDeviceToHost, hs));
+    HIP_TRY(hipMemcpyAsync(tmp.data(), src, 4 * cnt, hipMemcpyDeviceToHost, hs));
     HIP_TRY(hipStreamSynchronize(hs));
   }
   float* o = (float*)host_dst;
   if (!transpose) {
-    memcpy(o, tmp.data(), need);
+    for (int64_t l = 0; l < h.L; ++l) memcpy(o + l * h.r, tmp.data() + l * ld, 4 * (size_t)h.r);
     return MOARA_OK;
   }
   // paper orientation r x n from the stored n x r
   for (int64_t l = 0; l < h.L; ++l)
-    for (int64_t j = 0; j < h.r; ++j) o[j * h.L + l] = tmp[l * h.r + j];
+    for (int64_t j = 0; j < h.r; ++j) o[j * h.L + l] = tmp[l * ld + j];
   return MOARA_OK;
 }
 
@@ -1837,15 +1855,17 @@ int moara_set_tensor(moara_state* st, int32_t mat, int32_t which, const void* ho
   std::vector<uint16_t> raw;
   const void* src = host_src;
   size_t dev_bytes = need;
-  if (transpose) {
-    tmp.resize((size_t)h.L * h.r);
+  const int64_t ld = moment ? h.ldr : 0;   // moments: L rows of r values, row stride ldr (zeros past r)
+  if (moment && (transpose || ld != h.r)) {
+    tmp.assign((size_t)h.L * ld, 0.f);
     const float* in = (const float*)host_src;
     for (int64_t l = 0; l < h.L; ++l)
-      for (int64_t j = 0; j < h.r; ++j) tmp[l * h.r + j] = in[j * h.L + l];
+      for (int64_t j = 0; j < h.r; ++j) tmp[l * ld + j] = transpose ? in[j * h.L + l] : in[l * h.r + j];
     src = tmp.data();
+    dev_bytes = 4 * tmp.size();
   }
   if (narrow) {
-    const size_t cnt = (size_t)h.L * h.r;
+    const size_t cnt = (size_t)h.L * ld;
     const float* in = (const float*)src;
     raw.resize(cnt);
     for (size_t i = 0; i < cnt; ++i) raw[i] = host_f32_to_bf16(in[i]);
@@ -1856,7 +1876,7 @@ int moara_set_tensor(moara_state* st, int32_t mat, int32_t which, const void* ho
   HIP_TRY(hipStreamSynchronize(hs));
   HIP_TRY(hipMemcpyAsync(dst, src, dev_bytes, hipMemcpyHostToDevice, hs));
   if (which == MOARA_T_P) {
-    HIP_TRY(launch_convert_projector(h.P32, h.Pop, h.Ptop, h.s, h.r, st->cfg.operand_dtype == MOARA_BF16, h.kp ? 1 : 0,
+    HIP_TRY(launch_convert_projector(h.P32, h.Pop, h.Ptop, h.s, h.r, st->cfg.operand_dtype == MOARA_BF16, h.vpath ? 1 : 0,
                                      hs));
     h.hasP = true;
   }
