@@ -96,21 +96,6 @@ __device__ __forceinline__ int fresh(int v) {
   return v;
 }
 
-// sqrt(v) and 1 / sqrt(v) of a positive v: the hardware's reciprocal square root refined by
-// two Goldschmidt iterations (g -> sqrt(v), 2 h -> 1 / sqrt(v)) and one residual step on g
-__device__ __forceinline__ void sqrt_rsqrt(double v, double& root, double& rinv) {
-  const double y = __builtin_amdgcn_rsq(v);
-  double g = v * y, h = 0.5 * y;
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const double e = fma(-h, g, 0.5);
-    g = fma(g, e, g);
-    h = fma(h, e, h);
-  }
-  root = fma(fma(-g, g, v), h, g);
-  rinv = 2.0 * h;
-}
-
 // One wave: factor the 16 x 16 sub-block (k, k) in place (R_kk, zero below its diagonal) and
 // write its inverse. Lane l works on column l % 16 (the four quarters of the wave alike).
 //   column j: R_jj = sqrt(D_jj) (0 for a dependent column), R_jc = D_jc / R_jj (c > j),

@@ -53,6 +53,21 @@ struct RefDev {
 // relative errors of order 1e-6), so their columns are completed to an orthonormal basis.
 constexpr double RITZ_NULL_REL = 1e-5;
 
+// sqrt(v) and 1 / sqrt(v) of a positive v: the hardware's reciprocal square root refined by
+// two Goldschmidt iterations (g -> sqrt(v), 2 h -> 1 / sqrt(v)) and one residual step on g
+__device__ __forceinline__ void sqrt_rsqrt(double v, double& root, double& rinv) {
+  const double y = __builtin_amdgcn_rsq(v);
+  double g = v * y, h = 0.5 * y;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+  }
+  root = fma(fma(-g, g, v), h, g);
+  rinv = 2.0 * h;
+}
+
 constexpr int JB = 32;   // Jacobi column block; a pair holds 2*JB columns
 
 // Gram problem: C = A^T A for A (rows x w, row stride lda), fp64 accumulation.

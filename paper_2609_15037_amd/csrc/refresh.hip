@@ -174,14 +174,6 @@ constexpr int PW = 2 * JB;   // 64 columns per pair
 #define MOARA_JAC_TOL 1e-7
 #endif
 constexpr double JAC_TOL = MOARA_JAC_TOL;
-// Inner Jacobi sweeps per pair visit. The pair's Gram need not be diagonalised
-// exactly on every visit: with one inner sweep the outer iteration needs about one
-// more sweep to reach the same off-diagonal level, but every visit is much cheaper
-// and the visits of one round take about the same time (measured fastest of 1-3).
-#ifndef JAC_INNER_SWEEPS
-#define JAC_INNER_SWEEPS 1
-#endif
-
 // LDS: two 64 x 65 fp64 regions. Region A holds the pair's Gram G during the inner
 // solve; during the column passes it holds the current 32-row chunk of the 64 columns
 // (rows 0-31) and, in the rotation pass, the rotated chunk (rows 32-63). Region B holds
@@ -332,21 +324,29 @@ __global__ __launch_bounds__(JNT, 2) void k_jacobi_round(const RefDev* __restric
     }
   }
   __syncthreads();
-  // convergence measure of this pair (before rotating): max |g_xy| / sqrt(g_xx g_yy)
+  // Convergence measure of this pair (before rotating): max |g_xy| / sqrt(g_xx g_yy).
+  const bool full = round == 0 || sweep == 0;   // all column pairs, see (2)
   {
-    double* red = &Jm[0][0];   // J is built after this reduction
-    double m = 0.0;
+    double* rn = &Jm[0][0];     // J is built after this: 1 / sqrt(g_xx) of the 64 columns,
+    double* red = &Jm[2][0];    // then the waves' maxima
+    if (tid < PW) {
+      const double g = Gm[tid][tid];
+      double root, rinv = 0.0;
+      if (g > 0.0) sqrt_rsqrt(g, root, rinv);
+      rn[tid] = rinv;
+    }
+    __syncthreads();
+    double mx = 0.0;
     for (int e = tid; e < PW * PW; e += JNT) {
       const int x = e / PW, y = e % PW;
-      if (x < y) {
-        const double den = sqrt(Gm[x][x] * Gm[y][y]);
-        if (den > 0.0) m = fmax(m, fabs(Gm[x][y]) / den);
-      }
+      if (x < y) mx = fmax(mx, fabs(Gm[x][y]) * rn[x] * rn[y]);
     }
-    red[tid] = m;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+    if (lane == 0) red[wave] = mx;
     __syncthreads();
-    for (int o = JNT / 2; o > 0; o >>= 1) { if (tid < o) red[tid] = fmax(red[tid], red[tid + o]); __syncthreads(); }
-    const double mx = red[0];
+#pragma unroll
+    for (int q = 0; q < JAC_WAVES; ++q) mx = fmax(mx, red[q]);
     const bool conv = mx < JAC_TOL;
     if (tid == 0) {
       atomicMax(&d.off[sweep], __float_as_uint((float)mx));
@@ -355,65 +355,85 @@ __global__ __launch_bounds__(JNT, 2) void k_jacobi_round(const RefDev* __restric
       if (!conv) { d.jmod[ba] = gnow + 1; d.jmod[bb] = gnow + 1; }
     }
     if (conv) return;   // already orthogonal: nothing to rotate (uniform branch)
-    __syncthreads();            // red[0] is read by every thread before J overwrites it
+    __syncthreads();            // red is read by every thread before J overwrites it
   }
   for (int e = tid; e < PW * PW; e += JNT) Jm[e / PW][e % PW] = (e / PW == e % PW) ? 1.0 : 0.0;
   __syncthreads();
 
-  // (2) JAC_INNER_SWEEPS sweeps of parallel cyclic Jacobi on the 64 x 64 Gram, in place.
-  // One round rotates 32 disjoint pairs (circle method) on both sides at once,
-  // G' = R^T G R: lanes 0-31 of wave 0 compute the 32 rotations from the current G into
-  // CS (once per round, not redundantly in every wave: the fp64 square roots and
-  // divisions were 40 % of a round); after a barrier (every rotation computed from G
-  // before any entry changes) each lane reads rotation beta = l % 32 and the rotations
-  // of its row pairs alpha from CS, rewrites 16 / JAC_WAVES 2 x 2 blocks of G, which no
-  // other lane touches, and applies rotation beta to 32 / JAC_WAVES rows of the
-  // accumulated J. The barrier closing the round orders these writes before the next
-  // round's reads of G and CS.
+  // (2) Parallel cyclic Jacobi on the 64 x 64 Gram, in place. A visit rotates the 32 x 32
+  // column pairs across its two blocks, in 32 rounds of 32 disjoint pairs (column i of the one
+  // with column i + round of the other); the visits of the first sweep and those of round 0,
+  // which meets every block once per sweep, run all 2016 pairs, in 63 rounds (circle method).
+  // Each column pair is then rotated once per later sweep, as in cyclic Jacobi, where rotating
+  // the pairs inside a block on every visit repeats work. A round is a serial chain (two
+  // barriers, the rotation parameters, an LDS pass over G and J), a visit that chain and
+  // three passes over its columns. All pairs on every visit: 7 to 8 sweeps and 116 ms of a
+  // Llama-2-7B-shaped layer's refresh (9.1 ms of four 300M-shaped ones'); this: 8 to 9 sweeps, 104
+  // ms (7.6 ms); all pairs in round 0 only: 8 to 9 sweeps, 103 ms, but 8.1 ms, and 1.9 instead of
+  // 1.4 ms of a d = 256 layer's.
+  // One round rotates on both sides at once, G' = R^T G R: lanes 0-31 of wave 0 compute the 32
+  // rotations from the current G into CS (once per round, not redundantly in every wave);
+  // after a barrier (every rotation computed from G before any entry changes) each lane reads
+  // rotation beta = l % 32 and the rotations of its row pairs alpha from CS, rewrites
+  // 16 / JAC_WAVES 2 x 2 blocks of G, which no other lane touches, and applies rotation beta to
+  // 32 / JAC_WAVES rows of the accumulated J. The barrier closing the round orders these
+  // writes before the next round's reads of G and CS.
   {
     const int beta = lane & 31, half = lane >> 5;
-    for (int isw = 0; isw < JAC_INNER_SWEEPS; ++isw) {
-      for (int rr = 0; rr < PW - 1; ++rr) {
-        int pb = circle(beta, rr, PW), qb = circle(PW - 1 - beta, rr, PW);
-        if (pb > qb) { const int tmp = pb; pb = qb; qb = tmp; }
-        if (tid < 32) {
-          double c = 1.0, sn = 0.0;
-          const double app = Gm[pb][pb], aqq = Gm[qb][qb], apq = Gm[pb][qb];
-          const double den = sqrt(app * aqq);
-          if (den > 0.0 && fabs(apq) > 1e-16 * den) {
-            const double zeta = (aqq - app) / (2.0 * apq);
-            const double tt = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-            c = 1.0 / sqrt(1.0 + tt * tt);
-            sn = c * tt;
-          }
-          CS[tid][0] = c;
-          CS[tid][1] = sn;
-        }
-        __syncthreads();
-        const double cb = CS[beta][0], sb = CS[beta][1];
-#pragma unroll
-        for (int i = 0; i < 16 / JAC_WAVES; ++i) {
-          const int alpha = 2 * (16 / JAC_WAVES * wave + i) + half;
-          int pa = circle(alpha, rr, PW), qa = circle(PW - 1 - alpha, rr, PW);
-          if (pa > qa) { const int tmp = pa; pa = qa; qa = tmp; }
-          const double ca = CS[alpha][0], sa = CS[alpha][1];
-          const double g_pp = Gm[pa][pb], g_pq = Gm[pa][qb], g_qp = Gm[qa][pb], g_qq = Gm[qa][qb];
-          const double r_pp = ca * g_pp - sa * g_qp, r_pq = ca * g_pq - sa * g_qq;   // rows
-          const double r_qp = sa * g_pp + ca * g_qp, r_qq = sa * g_pq + ca * g_qq;
-          Gm[pa][pb] = cb * r_pp - sb * r_pq;                                          // columns
-          Gm[pa][qb] = sb * r_pp + cb * r_pq;
-          Gm[qa][pb] = cb * r_qp - sb * r_qq;
-          Gm[qa][qb] = sb * r_qp + cb * r_qq;
-        }
-#pragma unroll
-        for (int i = 0; i < 32 / JAC_WAVES; ++i) {
-          const int a = half + 2 * (wave + JAC_WAVES * i);
-          const double jp = Jm[a][pb], jq = Jm[a][qb];
-          Jm[a][pb] = cb * jp - sb * jq;
-          Jm[a][qb] = sb * jp + cb * jq;
-        }
-        __syncthreads();
+    auto pair_of = [&](int i, int rr, int& x, int& y) {
+      if (full) {
+        x = circle(i, rr, PW);
+        y = circle(PW - 1 - i, rr, PW);
+        if (x > y) { const int tmp = x; x = y; y = tmp; }
+      } else {
+        x = i;
+        y = JB + ((i + rr) & (JB - 1));
       }
+    };
+    const int nrr = full ? PW - 1 : JB;
+    for (int rr = 0; rr < nrr; ++rr) {
+      int pb, qb;
+      pair_of(beta, rr, pb, qb);
+      if (tid < 32) {
+        // with h = g_qq - g_pp and g = 2 g_pq the rotation that zeroes g_pq has
+        // cos 2t = |h| / r, sin 2t = +-|g| / r, r = sqrt(h^2 + g^2): c = sqrt((1 + cos 2t) / 2)
+        double c = 1.0, sn = 0.0;
+        const double app = Gm[pb][pb], aqq = Gm[qb][qb], apq = Gm[pb][qb];
+        const double h = aqq - app, g = 2.0 * apq, r2 = fma(h, h, g * g);
+        if (apq * apq > 1e-32 * (app * aqq) && r2 > 1e-300) {
+          double r, ir, ic;
+          sqrt_rsqrt(r2, r, ir);
+          sqrt_rsqrt(fma(0.5 * fabs(h), ir, 0.5), c, ic);
+          sn = 0.5 * fabs(g) * ir * ic;
+          if ((h < 0.0) != (g < 0.0)) sn = -sn;
+        }
+        CS[tid][0] = c;
+        CS[tid][1] = sn;
+      }
+      __syncthreads();
+      const double cb = CS[beta][0], sb = CS[beta][1];
+#pragma unroll
+      for (int i = 0; i < 16 / JAC_WAVES; ++i) {
+        const int alpha = 2 * (16 / JAC_WAVES * wave + i) + half;
+        int pa, qa;
+        pair_of(alpha, rr, pa, qa);
+        const double ca = CS[alpha][0], sa = CS[alpha][1];
+        const double g_pp = Gm[pa][pb], g_pq = Gm[pa][qb], g_qp = Gm[qa][pb], g_qq = Gm[qa][qb];
+        const double r_pp = ca * g_pp - sa * g_qp, r_pq = ca * g_pq - sa * g_qq;   // rows
+        const double r_qp = sa * g_pp + ca * g_qp, r_qq = sa * g_pq + ca * g_qq;
+        Gm[pa][pb] = cb * r_pp - sb * r_pq;                                          // columns
+        Gm[pa][qb] = sb * r_pp + cb * r_pq;
+        Gm[qa][pb] = cb * r_qp - sb * r_qq;
+        Gm[qa][qb] = sb * r_qp + cb * r_qq;
+      }
+#pragma unroll
+      for (int i = 0; i < 32 / JAC_WAVES; ++i) {
+        const int a = half + 2 * (wave + JAC_WAVES * i);
+        const double jp = Jm[a][pb], jq = Jm[a][qb];
+        Jm[a][pb] = cb * jp - sb * jq;
+        Jm[a][qb] = sb * jp + cb * jq;
+      }
+      __syncthreads();
     }
   }
 
