@@ -118,6 +118,8 @@ __device__ __forceinline__ float adam_out_bf16(float x, bf16& e, bf16& q, float 
 // ---------------------------------------------------------------- launchers
 // All launchers return hipError_t from hipGetLastError after the launch.
 struct GemmProb;
+// pinned host memory -> device, 16-byte aligned, both blocks padded to 16 bytes
+hipError_t launch_upload(void* dst, const void* host_src, size_t bytes, hipStream_t st);
 // One launch covers matrices that are all plain (decompose_plain) or all not. adam_m: also run
 // Optimizer_M.
 bool decompose_plain(const float* G, int64_t n, int k, bool decompose, bool transposed);

@@ -309,7 +309,7 @@ int begin_stage(moara_state* st, Stager& sg) {
 
 int end_stage(moara_state* st, Stager& sg, hipStream_t stream) {
   const int s = st->slot;
-  if (sg.used) HIP_TRY(hipMemcpyAsync(st->dev_arena, sg.host, sg.used, hipMemcpyHostToDevice, stream));
+  if (sg.used) HIP_TRY(launch_upload(st->dev_arena, sg.host, sg.used, stream));
   HIP_TRY(hipEventRecord(st->slot_ev[s], stream));
   st->slot_used[s] = true;
   st->slot = (s + 1) % moara_state::NSLOT;
@@ -451,14 +451,28 @@ GemmUniform make_uniform(const moara_state* st, float lr) {
   return u;
 }
 
+// A call first lists the descriptors of all its launches, then uploads them at once (stage),
+// then launches: an upload per launch costs a small call about 10 us of an idle GPU each.
 // Decompose (inv, and optionally Optimizer_M) for the listed matrices.
 // usev (indexed by matrix, may be null): write the bf16 V for that matrix as well.
-int run_decompose(moara_state* st, const std::vector<int>& idx, const void* const* grads, bool adam_m,
-                  hipStream_t stream, const std::vector<char>* usev = nullptr) {
-  if (idx.empty()) return MOARA_OK;
+struct DecPlan {
   // four lists: row-major and transposed V, each split into plain and other matrices
   std::vector<MatDev> md[4];
   uint32_t tiles[4] = {0, 0, 0, 0};
+  size_t off[4] = {};
+  int stage(Stager& sg) {
+    for (int q = 0; q < 4; ++q)
+      if (!md[q].empty() && (off[q] = sg.push(md[q].data(), md[q].size())) == (size_t)-1)
+        return fail(MOARA_E_OOM, "descriptor arena too small");
+    return MOARA_OK;
+  }
+};
+
+DecPlan plan_decompose(const moara_state* st, const std::vector<int>& idx, const void* const* grads,
+                       const std::vector<char>* usev) {
+  DecPlan P;
+  auto& md = P.md;
+  auto& tiles = P.tiles;
   for (int i : idx) {
     const MatHost& h = st->mats[i];
     MatDev d{};
@@ -478,22 +492,18 @@ int run_decompose(moara_state* st, const std::vector<int>& idx, const void* cons
     tiles[q] += (uint32_t)(vt ? decompose_vt_tiles(h.m) : decompose_tiles(h.m));
     md[q].push_back(d);
   }
-  Stager sg;
-  int rc = begin_stage(st, sg);
-  if (rc) return rc;
-  size_t off[4] = {};
-  for (int q = 0; q < 4; ++q)
-    if (!md[q].empty() && (off[q] = sg.push(md[q].data(), md[q].size())) == (size_t)-1)
-      return fail(MOARA_E_OOM, "descriptor arena too small");
-  rc = end_stage(st, sg, stream);
-  if (rc) return rc;
+  return P;
+}
+
+int launch_plan(moara_state* st, const DecPlan& P, bool adam_m, hipStream_t stream) {
+  if (P.md[0].empty() && P.md[1].empty() && P.md[2].empty() && P.md[3].empty()) return MOARA_OK;
   TimerScope ts(st, MOARA_KERN_DECOMPOSE, stream);
   for (int q = 3; q >= 0; --q) {
-    if (md[q].empty()) continue;
+    if (P.md[q].empty()) continue;
     StepParams p = make_params(st, 0.f);
-    p.nmat = (int)md[q].size();
-    p.total_dec = tiles[q];
-    const MatDev* dev = (const MatDev*)(st->dev_arena + off[q]);
+    p.nmat = (int)P.md[q].size();
+    p.total_dec = P.tiles[q];
+    const MatDev* dev = (const MatDev*)(st->dev_arena + P.off[q]);
     const bool plain = (q & 1) == 0;
     HIP_TRY(q >= 2 ? launch_decompose_vt(dev, p, adam_m ? 1 : 0, plain, stream)
                    : launch_decompose(dev, p, adam_m ? 1 : 0, plain, stream));
@@ -501,14 +511,40 @@ int run_decompose(moara_state* st, const std::vector<int>& idx, const void* cons
   return MOARA_OK;
 }
 
+int run_decompose(moara_state* st, const std::vector<int>& idx, const void* const* grads, bool adam_m,
+                  hipStream_t stream, const std::vector<char>* usev = nullptr) {
+  if (idx.empty()) return MOARA_OK;
+  DecPlan P = plan_decompose(st, idx, grads, usev);
+  Stager sg;
+  int rc = begin_stage(st, sg);
+  if (rc || (rc = P.stage(sg)) || (rc = end_stage(st, sg, stream))) return rc;
+  return launch_plan(st, P, adam_m, stream);
+}
+
 // back_only (indexed by matrix, may be null): N was formed without a projection (zero
 // gradient); only the back-projection and update run for that matrix.
-int run_project_back(moara_state* st, const std::vector<int>& idx, void* const* weights, const void* const* grads,
-                     float lr, hipStream_t stream, const std::vector<char>* back_only = nullptr) {
-  const int ob = st->cfg.operand_dtype == MOARA_BF16;
-  const int kind = ob ? KIND_BF16 : KIND_F32;
+struct GemmPlan {
   std::vector<GemmProb> left, right, back, pnt, bnt;
   uint32_t tl = 0, tr = 0, tb = 0, tpn = 0, tbn = 0;
+  int til = 128, tir = 128, tib = 128;   // fp32 operands: the tile each list runs on
+  size_t ol = 0, orr = 0, obk = 0, opn = 0, obn = 0;
+  int stage(Stager& sg) {
+    auto put = [&](const std::vector<GemmProb>& v, size_t& off) {
+      if (!v.empty()) off = sg.push(v.data(), v.size());
+      return off != (size_t)-1;
+    };
+    if (put(left, ol) && put(right, orr) && put(back, obk) && put(pnt, opn) && put(bnt, obn)) return MOARA_OK;
+    return fail(MOARA_E_OOM, "descriptor arena too small");
+  }
+};
+
+GemmPlan plan_project_back(const moara_state* st, const std::vector<int>& idx, void* const* weights,
+                           const void* const* grads, const std::vector<char>* back_only) {
+  const int ob = st->cfg.operand_dtype == MOARA_BF16;
+  const int kind = ob ? KIND_BF16 : KIND_F32;
+  GemmPlan P;
+  auto &left = P.left, &right = P.right, &back = P.back, &pnt = P.pnt, &bnt = P.bnt;
+  auto &tl = P.tl, &tr = P.tr, &tb = P.tb, &tpn = P.tpn, &tbn = P.tbn;
   for (int i : idx) {
     const MatHost& h = st->mats[i];
     const double t1 = (double)(h.t + 1);
@@ -577,40 +613,31 @@ int run_project_back(moara_state* st, const std::vector<int>& idx, void* const* 
     if (h.side == MOARA_SIDE_LEFT) { g.tile_start = tl; tl += nt; left.push_back(g); }
     else { g.tile_start = tr; tr += nt; right.push_back(g); }
   }
-  int til = 128, tir = 128, tib = 128;   // fp32 operands: the tile each list runs on
   if (!ob) {
-    til = gemm_f32_fit(left.data(), (int)left.size(), &tl);
-    tir = gemm_f32_fit(right.data(), (int)right.size(), &tr);
-    tib = gemm_f32_fit(back.data(), (int)back.size(), &tb);
+    P.til = gemm_f32_fit(left.data(), (int)left.size(), &tl);
+    P.tir = gemm_f32_fit(right.data(), (int)right.size(), &tr);
+    P.tib = gemm_f32_fit(back.data(), (int)back.size(), &tb);
   }
-  Stager sg;
-  int rc = begin_stage(st, sg);
-  if (rc) return rc;
-  const size_t ol = left.empty() ? 0 : sg.push(left.data(), left.size());
-  const size_t orr = right.empty() ? 0 : sg.push(right.data(), right.size());
-  const size_t obk = back.empty() ? 0 : sg.push(back.data(), back.size());
-  const size_t opn = pnt.empty() ? 0 : sg.push(pnt.data(), pnt.size());
-  const size_t obn = bnt.empty() ? 0 : sg.push(bnt.data(), bnt.size());
-  if (ol == (size_t)-1 || orr == (size_t)-1 || obk == (size_t)-1 || opn == (size_t)-1 || obn == (size_t)-1)
-    return fail(MOARA_E_OOM, "descriptor arena too small");
-  rc = end_stage(st, sg, stream);
-  if (rc) return rc;
+  return P;
+}
+
+int launch_plan(moara_state* st, const GemmPlan& P, float lr, hipStream_t stream) {
+  const int kind = st->cfg.operand_dtype == MOARA_BF16 ? KIND_BF16 : KIND_F32;
+  auto dev = [&](size_t off) { return (const GemmProb*)(st->dev_arena + off); };
   const GemmUniform u = make_uniform(st, lr);
   {
     TimerScope ts(st, MOARA_KERN_PROJECT, stream);
-    if (!pnt.empty())
-      HIP_TRY(launch_gemm_nt(EP_ADAM, (const GemmProb*)(st->dev_arena + opn), (int)pnt.size(), tpn, u, stream));
-    if (!right.empty())
-      HIP_TRY(launch_gemm(kind, A_G_ROW, B_KC, EP_ADAM, (const GemmProb*)(st->dev_arena + orr), (int)right.size(), tr, u, stream, tir));
-    if (!left.empty())
-      HIP_TRY(launch_gemm(kind, A_G_TRANS, B_KC, EP_ADAM, (const GemmProb*)(st->dev_arena + ol), (int)left.size(), tl, u, stream, til));
+    if (!P.pnt.empty()) HIP_TRY(launch_gemm_nt(EP_ADAM, dev(P.opn), (int)P.pnt.size(), P.tpn, u, stream));
+    if (!P.right.empty())
+      HIP_TRY(launch_gemm(kind, A_G_ROW, B_KC, EP_ADAM, dev(P.orr), (int)P.right.size(), P.tr, u, stream, P.tir));
+    if (!P.left.empty())
+      HIP_TRY(launch_gemm(kind, A_G_TRANS, B_KC, EP_ADAM, dev(P.ol), (int)P.left.size(), P.tl, u, stream, P.til));
   }
   {
     TimerScope ts(st, MOARA_KERN_BACKPROJ, stream);
-    if (!bnt.empty())
-      HIP_TRY(launch_gemm_nt(EP_UPDATE, (const GemmProb*)(st->dev_arena + obn), (int)bnt.size(), tbn, u, stream));
-    if (!back.empty())
-      HIP_TRY(launch_gemm(kind, A_KC, B_KC, EP_UPDATE, (const GemmProb*)(st->dev_arena + obk), (int)back.size(), tb, u, stream, tib));
+    if (!P.bnt.empty()) HIP_TRY(launch_gemm_nt(EP_UPDATE, dev(P.obn), (int)P.bnt.size(), P.tbn, u, stream));
+    if (!P.back.empty())
+      HIP_TRY(launch_gemm(kind, A_KC, B_KC, EP_UPDATE, dev(P.obk), (int)P.back.size(), P.tb, u, stream, P.tib));
   }
   return MOARA_OK;
 }
@@ -618,20 +645,22 @@ int run_project_back(moara_state* st, const std::vector<int>& idx, void* const* 
 // Zero-gradient step (zero_grad_mode 1) for the listed matrices: a refresh that falls due
 // keeps the projector (V = 0), or sets the canonical one if there is none; then
 // Optimizer_M and Optimizer_V on zero inputs (k_zero_grad). The back-projection and the
-// update follow in run_project_back.
-int run_zero_grad(moara_state* st, const std::vector<int>& zidx, hipStream_t stream) {
-  if (zidx.empty()) return MOARA_OK;
-  const int T = st->cfg.refresh_interval;
-  const int obf = st->cfg.operand_dtype == MOARA_BF16;
-  for (int i : zidx) {
-    MatHost& h = st->mats[i];
-    if (T > 0 && h.t % T == 0 && !h.hasP) {
-      HIP_TRY(launch_canonical_projector(h.P32, h.Pop, h.Ptop, h.s, h.r, obf, h.vpath ? 1 : 0, stream));
-      h.hasP = true;
-    }
-  }
+// update follow with the other matrices'.
+struct ZeroPlan {
   std::vector<MatDev> md;
   uint32_t tiles = 0;
+  size_t off = 0;
+  int stage(Stager& sg) {
+    if (md.empty() || (off = sg.push(md.data(), md.size())) != (size_t)-1) return MOARA_OK;
+    return fail(MOARA_E_OOM, "descriptor arena too small");
+  }
+};
+
+ZeroPlan plan_zero_grad(const moara_state* st, const std::vector<int>& zidx) {
+  const int obf = st->cfg.operand_dtype == MOARA_BF16;
+  ZeroPlan P;
+  auto& md = P.md;
+  auto& tiles = P.tiles;
   for (int i : zidx) {
     const MatHost& h = st->mats[i];
     MatDev d{};
@@ -647,17 +676,25 @@ int run_zero_grad(moara_state* st, const std::vector<int>& zidx, hipStream_t str
     tiles += zero_grad_tiles(st->cfg.decompose ? h.m * h.k : 0, h.L * h.r);
     md.push_back(d);
   }
-  Stager sg;
-  int rc = begin_stage(st, sg);
-  if (rc) return rc;
-  const size_t off = sg.push(md.data(), md.size());
-  if (off == (size_t)-1) return fail(MOARA_E_OOM, "descriptor arena too small");
-  if ((rc = end_stage(st, sg, stream))) return rc;
+  return P;
+}
+
+int launch_plan(moara_state* st, const ZeroPlan& P, const std::vector<int>& zidx, hipStream_t stream) {
+  if (zidx.empty()) return MOARA_OK;
+  const int T = st->cfg.refresh_interval;
+  for (int i : zidx) {
+    MatHost& h = st->mats[i];
+    if (T > 0 && h.t % T == 0 && !h.hasP) {
+      HIP_TRY(launch_canonical_projector(h.P32, h.Pop, h.Ptop, h.s, h.r, st->cfg.operand_dtype == MOARA_BF16,
+                                         h.vpath ? 1 : 0, stream));
+      h.hasP = true;
+    }
+  }
   StepParams p = make_params(st, 0.f);
-  p.nmat = (int)md.size();
-  p.total_dec = tiles;
+  p.nmat = (int)P.md.size();
+  p.total_dec = P.tiles;
   TimerScope ts(st, MOARA_KERN_DECOMPOSE, stream);
-  HIP_TRY(launch_zero_grad((const MatDev*)(st->dev_arena + off), p, stream));
+  HIP_TRY(launch_zero_grad((const MatDev*)(st->dev_arena + P.off), p, stream));
   return MOARA_OK;
 }
 
@@ -1550,7 +1587,8 @@ int moara_create_state(const moara_config* cfg, const moara_matrix_desc* descs, 
   st->info_dev = (int32_t*)take(16 * (size_t)n);
   st->arena_bytes = 2 * align_up(sizeof(MatDev) * n) + 4 * ALIGN + 5 * align_up(sizeof(GemmProb) * n) + 8 * ALIGN;
   if (hipMalloc(&st->dev_arena, st->arena_bytes) != hipSuccess ||
-      hipHostMalloc(&st->host_ring, st->arena_bytes * moara_state::NSLOT) != hipSuccess) {
+      hipHostMalloc(&st->host_ring, st->arena_bytes * moara_state::NSLOT,
+                    hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
     free_state(st);
     return fail(MOARA_E_OOM, "descriptor arenas");
   }
@@ -1741,13 +1779,19 @@ static int step_impl(moara_state* st, void* const* weights, const void* const* g
     usev[i] = st->mats[i].vpath;
     refv[i] = st->mats[i].vref && (((uintptr_t)grads[i] & 15) == 0);
   }
-  if ((rc = run_decompose(st, idx, grads, st->cfg.decompose != 0, hs, &usev))) return rc;
-  if (!need.empty() && (rc = refresh_in_chunks(st, need, grads, hs, refv))) return rc;
-  if ((rc = run_zero_grad(st, zidx, hs))) return rc;
   std::vector<int> all = idx;
   all.insert(all.end(), zidx.begin(), zidx.end());
-  rc = run_project_back(st, all, weights, grads, lr, hs, &zflag);
-  if (rc) return rc;
+  DecPlan dec = plan_decompose(st, idx, grads, &usev);
+  ZeroPlan zero = plan_zero_grad(st, zidx);
+  GemmPlan gemm = plan_project_back(st, all, weights, grads, &zflag);
+  Stager sg;
+  if ((rc = begin_stage(st, sg)) || (rc = dec.stage(sg)) || (rc = zero.stage(sg)) || (rc = gemm.stage(sg)) ||
+      (rc = end_stage(st, sg, hs)))
+    return rc;
+  if ((rc = launch_plan(st, dec, st->cfg.decompose != 0, hs))) return rc;
+  if (!need.empty() && (rc = refresh_in_chunks(st, need, grads, hs, refv))) return rc;
+  if ((rc = launch_plan(st, zero, zidx, hs))) return rc;
+  if ((rc = launch_plan(st, gemm, lr, hs))) return rc;
   for (int i : all) st->mats[i].t += 1;
   if (noalloc) {
     HIP_TRY(hipEventRecord(g_scratch_ev[st->device], hs));
