@@ -96,11 +96,18 @@ __device__ __forceinline__ double wave_sum_d(double v) {
   return v;
 }
 
+// The multiply-adds below are written out: left to the compiler, their contraction depends on the
+// kernel they are inlined into, and a matrix's step must not depend (to the last bit) on which
+// kernel it takes.
+__device__ __forceinline__ float sumsq4(float4 v) {
+  return fmaf(v.w, v.w, fmaf(v.z, v.z, fmaf(v.y, v.y, v.x * v.x)));
+}
+
 // Adam step of Kingma & Ba with bias correction terms passed in (no weight decay).
 __device__ __forceinline__ float adam_out(float x, float& e, float& q, float b1, float b2,
                                           float eps, float bc1, float bc2) {
-  e = b1 * e + (1.0f - b1) * x;
-  q = b2 * q + (1.0f - b2) * x * x;
+  e = fmaf(b1, e, (1.0f - b1) * x);
+  q = fmaf((1.0f - b2) * x, x, b2 * q);
   return (e / bc1) / (sqrtf(q / bc2) + eps);
 }
 
@@ -108,8 +115,8 @@ __device__ __forceinline__ float adam_out(float x, float& e, float& q, float b1,
 // (nearest even) for storage and the output is formed from the stored values.
 __device__ __forceinline__ float adam_out_bf16(float x, bf16& e, bf16& q, float b1, float b2, float eps,
                                                float bc1, float bc2) {
-  const float e1 = bf2f(f2bf(b1 * bf2f(e) + (1.0f - b1) * x));
-  const float q1 = bf2f(f2bf(b2 * bf2f(q) + (1.0f - b2) * x * x));
+  const float e1 = bf2f(f2bf(fmaf(b1, bf2f(e), (1.0f - b1) * x)));
+  const float q1 = bf2f(f2bf(fmaf((1.0f - b2) * x, x, b2 * bf2f(q))));
   e = f2bf(e1);
   q = f2bf(q1);
   return (e1 / bc1) / (sqrtf(q1 / bc2) + eps);

@@ -139,7 +139,7 @@ __global__ __launch_bounds__(256) void k_decompose(const MatDev* __restrict__ ma
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
           const int64_t c = c00 + 128 * u + 4 * hl;
-          float ss = v[u].x * v[u].x + v[u].y * v[u].y + v[u].z * v[u].z + v[u].w * v[u].w;
+          float ss = sumsq4(v[u]);
           ss = group_sum(ss, gl);
           if (rok && c < n) {
             if (dec && (hl & (gl - 1)) == 0) sums[rr * k + (int)(c >> lgB)] = ss;
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256) void k_decompose(const MatDev* __restrict__ ma
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
           const int64_t c = c00 + 256 * u + 4 * lane;
-          float ss = v[u].x * v[u].x + v[u].y * v[u].y + v[u].z * v[u].z + v[u].w * v[u].w;
+          float ss = sumsq4(v[u]);
           ss = group_sum(ss, gl);
           if ((lane & (gl - 1)) == 0 && c < n) sums[rr * k + (int)(c >> lgB)] = ss;
           if (d.Vb && c < n) {
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(256) void k_decompose_vt(const MatDev* __restrict__
 #pragma unroll
     for (int i = 0; i < VT_RPW; ++i) {
       const int rr = wave + 4 * i;
-      float ss = v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
+      float ss = sumsq4(v[i]);
       ss = group_sum(ss, gl);
       if (dec && rr < rows && c < n && (lane & (gl - 1)) == 0) sums[rr * kc + (int)(c >> lgB) - kc0] = ss;
       const float inv = dec ? 1.0f / (sqrtf(ss) + p.decomp_eps) : 1.0f;

@@ -102,6 +102,34 @@ __device__ __forceinline__ void tile_coords(uint32_t lt, uint32_t tiles_m, uint3
   tn = idx / gsz;
 }
 
+// One matrix of the fused decomposition and projection (decproj.hip).
+struct FusedProb {
+  const float* G;      // m x n
+  int64_t m, n, s, L;
+  const void* P;       // Ptop: r x s, blocked (rows r, K = s padded to 32)
+  void* e1;            // Optimizer_V's moments, L x r, row stride ldr
+  void* e2;
+  void* N;             // Optimizer_V's output, blocked (rows L, K = r padded to 32)
+  float* ss;           // m x k block sums of squares (k_decproj -> k_opt_m)
+  float* mag1;         // Optimizer_M's moments and output, m x k
+  float* mag2;
+  float* dM;
+  int32_t side, r, k, ldr;
+  uint32_t p_bytes;
+  float bc1, bc2;
+  uint32_t tile_start, tile_m;   // workgroup prefixes of k_decproj and k_opt_m
+  uint32_t pad_;
+};
+constexpr uint32_t DECPROJ_MIN_TILES = 512;   // two workgroups on each of the 256 CUs
+bool decproj_fits(int64_t m, int64_t n, int32_t r, int B, bool decompose);
+uint32_t decproj_tiles(int side, int64_t L);
+uint32_t opt_m_tiles(int64_t mk);
+struct GemmUniform;
+// plain: every matrix of the list has n % 4 == 0 and a 16-byte aligned gradient
+hipError_t launch_decproj(const FusedProb* p, int n, uint32_t total, const GemmUniform& u, bool plain, bool decompose,
+                          hipStream_t st);
+hipError_t launch_opt_m(const FusedProb* p, int n, uint32_t total, const GemmUniform& u, hipStream_t st);
+
 // Host helpers (gemm.hip).
 uint32_t gemm_tiles_m(int kind, int64_t M);
 uint32_t gemm_tiles_n(int kind, int64_t N);

@@ -495,8 +495,9 @@ DecPlan plan_decompose(const moara_state* st, const std::vector<int>& idx, const
   return P;
 }
 
-int launch_plan(moara_state* st, const DecPlan& P, bool adam_m, hipStream_t stream) {
-  if (P.md[0].empty() && P.md[1].empty() && P.md[2].empty() && P.md[3].empty()) return MOARA_OK;
+// timed_empty: record the (empty) timing scope also when every matrix took the fused kernel
+int launch_plan(moara_state* st, const DecPlan& P, bool adam_m, hipStream_t stream, bool timed_empty = false) {
+  if (P.md[0].empty() && P.md[1].empty() && P.md[2].empty() && P.md[3].empty() && !timed_empty) return MOARA_OK;
   TimerScope ts(st, MOARA_KERN_DECOMPOSE, stream);
   for (int q = 3; q >= 0; --q) {
     if (P.md[q].empty()) continue;
@@ -521,8 +522,43 @@ int run_decompose(moara_state* st, const std::vector<int>& idx, const void* cons
   return launch_plan(st, P, adam_m, stream);
 }
 
-// back_only (indexed by matrix, may be null): N was formed without a projection (zero
-// gradient); only the back-projection and update run for that matrix.
+// Matrices whose decomposition and projection run in one kernel (decproj.hip), plain and other.
+struct FusedPlan {
+  std::vector<FusedProb> p[2];
+  uint32_t tiles[2] = {0, 0}, tiles_m[2] = {0, 0};
+  size_t off[2] = {};
+  int stage(Stager& sg) {
+    for (int q = 0; q < 2; ++q)
+      if (!p[q].empty() && (off[q] = sg.push(p[q].data(), p[q].size())) == (size_t)-1)
+        return fail(MOARA_E_OOM, "descriptor arena too small");
+    return MOARA_OK;
+  }
+};
+
+FusedPlan plan_fused(const moara_state* st, const std::vector<int>& idx, const void* const* grads) {
+  FusedPlan P;
+  for (int i : idx) {
+    const MatHost& h = st->mats[i];
+    const double t1 = (double)(h.t + 1);
+    const int q = ((h.n & 3) == 0 && ((uintptr_t)grads[i] & 15) == 0) ? 0 : 1;
+    FusedProb f{};
+    f.G = (const float*)grads[i];
+    f.m = h.m; f.n = h.n; f.s = h.s; f.L = h.L;
+    f.P = h.Ptop; f.p_bytes = (uint32_t)(2 * (size_t)h.r * h.sp);
+    f.e1 = h.exp1; f.e2 = h.exp2; f.N = h.N;
+    f.ss = h.inv; f.mag1 = h.mag1; f.mag2 = h.mag2; f.dM = h.dM;
+    f.side = h.side; f.r = h.r; f.k = h.k; f.ldr = (int32_t)h.ldr;
+    f.bc1 = st->cfg.bias_correction ? (float)(1.0 - pow((double)st->cfg.beta1, t1)) : 1.f;
+    f.bc2 = st->cfg.bias_correction ? (float)(1.0 - pow((double)st->cfg.beta2, t1)) : 1.f;
+    f.tile_start = P.tiles[q];
+    P.tiles[q] += decproj_tiles(h.side, h.L);
+    f.tile_m = P.tiles_m[q];
+    P.tiles_m[q] += opt_m_tiles(h.m * h.k);
+    P.p[q].push_back(f);
+  }
+  return P;
+}
+
 struct GemmPlan {
   std::vector<GemmProb> left, right, back, pnt, bnt;
   uint32_t tl = 0, tr = 0, tb = 0, tpn = 0, tbn = 0;
@@ -538,6 +574,8 @@ struct GemmPlan {
   }
 };
 
+// back_only (indexed by matrix): N is formed elsewhere (zero gradient, fused projection); only the
+// back-projection and update are listed for that matrix.
 GemmPlan plan_project_back(const moara_state* st, const std::vector<int>& idx, void* const* weights,
                            const void* const* grads, const std::vector<char>* back_only) {
   const int ob = st->cfg.operand_dtype == MOARA_BF16;
@@ -621,12 +659,21 @@ GemmPlan plan_project_back(const moara_state* st, const std::vector<int>& idx, v
   return P;
 }
 
-int launch_plan(moara_state* st, const GemmPlan& P, float lr, hipStream_t stream) {
+int launch_plan(moara_state* st, const GemmPlan& P, const FusedPlan& F, float lr, hipStream_t stream) {
   const int kind = st->cfg.operand_dtype == MOARA_BF16 ? KIND_BF16 : KIND_F32;
   auto dev = [&](size_t off) { return (const GemmProb*)(st->dev_arena + off); };
   const GemmUniform u = make_uniform(st, lr);
   {
     TimerScope ts(st, MOARA_KERN_PROJECT, stream);
+    for (int q = 0; q < 2; ++q) {
+      if (F.p[q].empty()) continue;
+      const FusedProb* fp = (const FusedProb*)(st->dev_arena + F.off[q]);
+      const bool dec = st->cfg.decompose != 0;
+      GemmUniform uf = u;
+      uf.decomp_eps = st->cfg.decomp_eps;
+      HIP_TRY(launch_decproj(fp, (int)F.p[q].size(), F.tiles[q], uf, q == 0, dec, stream));
+      if (dec) HIP_TRY(launch_opt_m(fp, (int)F.p[q].size(), F.tiles_m[q], uf, stream));
+    }
     if (!P.pnt.empty()) HIP_TRY(launch_gemm_nt(EP_ADAM, dev(P.opn), (int)P.pnt.size(), P.tpn, u, stream));
     if (!P.right.empty())
       HIP_TRY(launch_gemm(kind, A_G_ROW, B_KC, EP_ADAM, dev(P.orr), (int)P.right.size(), P.tr, u, stream, P.tir));
@@ -1585,7 +1632,7 @@ int moara_create_state(const moara_config* cfg, const moara_matrix_desc* descs, 
     if (h.vpath) h.V = take(2 * (size_t)h.L * h.sp);
   }
   st->info_dev = (int32_t*)take(16 * (size_t)n);
-  st->arena_bytes = 2 * align_up(sizeof(MatDev) * n) + 4 * ALIGN + 5 * align_up(sizeof(GemmProb) * n) + 8 * ALIGN;
+  st->arena_bytes = 2 * align_up(sizeof(MatDev) * n) + 6 * ALIGN + align_up(sizeof(FusedProb) * n) + 5 * align_up(sizeof(GemmProb) * n) + 8 * ALIGN;
   if (hipMalloc(&st->dev_arena, st->arena_bytes) != hipSuccess ||
       hipHostMalloc(&st->host_ring, st->arena_bytes * moara_state::NSLOT,
                     hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
@@ -1779,19 +1826,41 @@ static int step_impl(moara_state* st, void* const* weights, const void* const* g
     usev[i] = st->mats[i].vpath;
     refv[i] = st->mats[i].vref && (((uintptr_t)grads[i] & 15) == 0);
   }
+  // which matrices take the fused decomposition and projection: those it fits, except where a
+  // refresh that is due needs what the decomposition kernel writes (V, or 1 / (M + eps_d)), and
+  // except a handful beside larger matrices: fewer tiles than the 512 that run at once cost a
+  // launch of their own (four 512 x 3584 matrices 160 us), and next to nothing in the others'
+  std::vector<int> split, fused;
+  {
+    std::vector<char> due(st->n, 0);
+    for (int i : need) due[i] = 1;
+    uint32_t ftiles = 0;
+    for (int i : idx) {
+      const MatHost& h = st->mats[i];
+      const bool f = h.vpath && !due[i] && decproj_fits(h.m, h.n, h.r, st->cfg.block_size, st->cfg.decompose != 0);
+      (f ? fused : split).push_back(i);
+      if (f) ftiles += decproj_tiles(h.side, h.L);
+    }
+    if (!split.empty() && ftiles < DECPROJ_MIN_TILES) {
+      split = idx;
+      fused.clear();
+    }
+    for (int i : fused) zflag[i] = 1;
+  }
   std::vector<int> all = idx;
   all.insert(all.end(), zidx.begin(), zidx.end());
-  DecPlan dec = plan_decompose(st, idx, grads, &usev);
+  DecPlan dec = plan_decompose(st, split, grads, &usev);
   ZeroPlan zero = plan_zero_grad(st, zidx);
+  FusedPlan fu = plan_fused(st, fused, grads);
   GemmPlan gemm = plan_project_back(st, all, weights, grads, &zflag);
   Stager sg;
-  if ((rc = begin_stage(st, sg)) || (rc = dec.stage(sg)) || (rc = zero.stage(sg)) || (rc = gemm.stage(sg)) ||
-      (rc = end_stage(st, sg, hs)))
+  if ((rc = begin_stage(st, sg)) || (rc = dec.stage(sg)) || (rc = zero.stage(sg)) || (rc = fu.stage(sg)) ||
+      (rc = gemm.stage(sg)) || (rc = end_stage(st, sg, hs)))
     return rc;
-  if ((rc = launch_plan(st, dec, st->cfg.decompose != 0, hs))) return rc;
+  if ((rc = launch_plan(st, dec, st->cfg.decompose != 0, hs, st->cfg.decompose && !fused.empty()))) return rc;
   if (!need.empty() && (rc = refresh_in_chunks(st, need, grads, hs, refv))) return rc;
   if ((rc = launch_plan(st, zero, zidx, hs))) return rc;
-  if ((rc = launch_plan(st, gemm, lr, hs))) return rc;
+  if ((rc = launch_plan(st, gemm, fu, lr, hs))) return rc;
   for (int i : all) st->mats[i].t += 1;
   if (noalloc) {
     HIP_TRY(hipEventRecord(g_scratch_ev[st->device], hs));

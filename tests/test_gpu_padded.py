@@ -30,3 +30,59 @@ def test_padded_operands_and_unaligned_buffers(decompose, misalign):
     c = Case(shapes=SHAPES, ranks=RANKS, block_size=64, operand_dtype="bf16", weight_dtype="bf16", weight_std=0.02,
              decompose=decompose)
     step_parity(c, 2, misalign=misalign)
+
+
+# the one-pass decomposition and projection: tiles of 64 (RIGHT) and 128 (LEFT) rows, K chunks of
+# 128 and 64 and panels of 32, one past and one short of each; ranks at the edges of its 32-column
+# blocks and of its range; unaligned rows (n % 4 != 0) beside aligned ones
+FUSED = [(32, 128, WL.Q), (129, 32, WL.GATE), (96, 257, WL.K), (127, 128, WL.V), (260, 132, WL.UP), (191, 97, WL.O),
+         (256, 1000, WL.DOWN), (640, 256, WL.GATE), (130, 384, WL.Q)]
+FUSED_RANKS = [1, 31, 33, 64, 100, 97, 256, 255, 129]
+
+
+@pytest.mark.parametrize("B,wdt,mom", [(32, "bf16", "bf16"), (64, "f32", "f32"), (128, "bf16", "f32"),
+                                       (128, "f32", "bf16")])
+def test_one_pass_projection_from_a_restored_state(B, wdt, mom):
+    c = Case(shapes=FUSED, ranks=FUSED_RANKS, block_size=B, operand_dtype="bf16", weight_dtype=wdt, moment_dtype=mom,
+             weight_std=1e-2 if wdt == "bf16" else 1e-5)
+    history_parity(c, 2, 230 + B, _grad(c, 230 + B))
+
+
+@pytest.mark.parametrize("misalign", [False, True])
+@pytest.mark.parametrize("mom", ["f32", "bf16"])
+def test_one_pass_projection_without_the_decomposition(mom, misalign):
+    c = Case(shapes=FUSED, ranks=FUSED_RANKS, block_size=1, operand_dtype="bf16", weight_dtype="bf16", weight_std=0.02,
+             decompose=False, moment_dtype=mom)
+    step_parity(c, 2, misalign=misalign)
+
+
+def test_one_pass_and_two_pass_projection_are_bit_identical():
+    """A matrix whose rank exceeds the one-pass kernel's range sends a short list of matrices through
+    the two-pass kernels: the same matrices give the same bits with and without it beside them."""
+    import numpy as np
+    import torch
+    from paper_2609_15037_amd import moara as M
+    from tests.harness import gpu_state, rng, to_dev
+    shapes, ranks = FUSED, FUSED_RANKS
+    big, rbig = (300, 320, WL.V), 257
+    out = []
+    for extra in (False, True):
+        c = Case(shapes=shapes + ([big] if extra else []), ranks=ranks + ([rbig] if extra else []), block_size=64,
+                 operand_dtype="bf16", weight_dtype="bf16", weight_std=0.02, moment_dtype="bf16")
+        st = gpu_state(c)
+        W, G = [], []
+        for i, ((m, n, _), r) in enumerate(zip(c.shapes, c.ranks)):
+            W.append(to_dev(0.02 * rng(5, 1, i).standard_normal((m, n)), "bf16"))
+            G.append(to_dev(rng(5, 2, i).standard_normal((m, n)), "f32"))
+            P = np.linalg.qr(rng(5, 3, i).standard_normal((min(m, n), r)))[0]
+            M.moara_set_tensor(st, i, M.MOARA_T_P, P)
+        for _ in range(3):
+            M.moara_step(st, W, G, lr=1e-2)
+        torch.cuda.synchronize()
+        out.append([(W[i], *[M.moara_get_tensor(st, i, k) for k in
+                             (M.MOARA_T_EXP_AVG, M.MOARA_T_EXP_AVG_SQ, M.MOARA_T_MAG_AVG, M.MOARA_T_MAG_AVG_SQ)])
+                    for i in range(len(shapes))])
+    for i, (a, b) in enumerate(zip(*out)):
+        assert torch.equal(a[0], b[0]), f"matrix {i}: W differs"
+        for x, y in zip(a[1:], b[1:]):
+            assert np.array_equal(x, y), f"matrix {i}: a moment differs"
