@@ -98,9 +98,11 @@ __device__ __forceinline__ double wave_sum_d(double v) {
 
 // The multiply-adds below are written out: left to the compiler, their contraction depends on the
 // kernel they are inlined into, and a matrix's step must not depend (to the last bit) on which
-// kernel it takes.
+// kernel it takes. The sum of squares keeps the order that fp32 operands have always seen: a
+// refresh's first update is close to sign(R), so one element of R near zero turns an ulp of a
+// block norm into 1e-2 of a weight's root mean square.
 __device__ __forceinline__ float sumsq4(float4 v) {
-  return fmaf(v.w, v.w, fmaf(v.z, v.z, fmaf(v.y, v.y, v.x * v.x)));
+  return fmaf(v.w, v.w, fmaf(v.z, v.z, fmaf(v.x, v.x, v.y * v.y)));
 }
 
 // Adam step of Kingma & Ba with bias correction terms passed in (no weight decay).
