@@ -225,6 +225,18 @@ int moara_refresh_projector(moara_state* st, const void* const* grads, const uin
 int moara_step(moara_state* st, void* const* weights, const void* const* grads,
                const uint8_t* active, float lr, void* stream);
 
+/* moara_step on gradients of which some are bf16 (a bf16 model's own): the step, bit for bit, that
+ * moara_step makes on them converted to fp32 (an exact conversion), without reading and writing
+ * a converted copy where the step's kernel takes bf16 (matrices of rank up to 256 with n a multiple of
+ * 4, when no refresh is due).
+ * grad_bf16: host array of n flags; != 0: grads[i] points to an m x n row-major bf16 G.
+ * grads32:   host array of n device pointers to m x n fp32 buffers (may be NULL where grad_bf16[i]
+ *            is 0 or the matrix is inactive), the caller's, overwritten with the converted gradient
+ *            where the step needs it and otherwise left alone; same lifetime rule as W and G.
+ * The other arguments and the errors are moara_step's; MOARA_E_ARG also for a missing buffer. */
+int moara_step_mixed(moara_state* st, void* const* weights, const void* const* grads, const uint8_t* grad_bf16,
+                     float* const* grads32, const uint8_t* active, float lr, void* stream);
+
 /* moara_step for callers that cannot allocate device memory (allocation-free serving or
  * training loops, harnesses that forbid hipMalloc). It allocates nothing, but it is not
  * made for stream capture: like moara_step it stages each launch's descriptors through

@@ -129,6 +129,17 @@ __device__ __forceinline__ float adam_out_bf16(float x, bf16& e, bf16& q, float 
 struct GemmProb;
 // pinned host memory -> device, 16-byte aligned, both blocks padded to 16 bytes
 hipError_t launch_upload(void* dst, const void* host_src, size_t bytes, hipStream_t st);
+// bf16 -> fp32 (exact) of up to CAST_MAX buffers of any alignment in one launch
+constexpr int CAST_MAX = 64;
+struct CastList {
+  const void* src[CAST_MAX];
+  float* dst[CAST_MAX];
+  int64_t count[CAST_MAX];
+  uint32_t start[CAST_MAX];   // first workgroup
+  int n;
+};
+uint32_t cast_tiles(int64_t count);
+hipError_t launch_cast(const CastList& l, uint32_t total, hipStream_t st);
 // One launch covers matrices that are all plain (decompose_plain) or all not. adam_m: also run
 // Optimizer_M.
 bool decompose_plain(const float* G, int64_t n, int k, bool decompose, bool transposed);

@@ -370,7 +370,44 @@ __global__ __launch_bounds__(256) void k_zero_grad(const MatDev* __restrict__ ma
 __global__ __launch_bounds__(256) void k_upload(uint4* __restrict__ dst, const uint4* __restrict__ src, uint32_t n) {
   for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) dst[i] = src[i];
 }
+
+// bf16 gradients -> fp32 for the kernels that take fp32 only, all of a step's in a few launches
+// (one copy per matrix took 4 us each at 0.26 to 2.9 M elements, most of it the launch's own time).
+// Memory-bound, 6 bytes per element: eight elements per thread and pass.
+constexpr int CAST_PER_WG = 8192;
+__global__ __launch_bounds__(256) void k_cast(CastList L) {
+  typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+  const uint32_t t = blockIdx.x;
+  int lo = 0, hi = L.n - 1;
+  while (lo < hi) { const int mid = (lo + hi + 1) >> 1; if (L.start[mid] <= t) lo = mid; else hi = mid - 1; }
+  const unsigned short* src = (const unsigned short*)L.src[lo];
+  float* dst = L.dst[lo];
+  const int64_t e0 = (int64_t)(t - L.start[lo]) * CAST_PER_WG;
+  const int64_t e1 = e0 + CAST_PER_WG < L.count[lo] ? e0 + CAST_PER_WG : L.count[lo];
+  if ((((uintptr_t)src | (uintptr_t)dst) & 15) == 0) {
+    for (int64_t e = e0 + 8 * threadIdx.x; e + 8 <= e1; e += 8 * 256) {
+      const u16x8 v = *reinterpret_cast<const u16x8*>(src + e);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        *reinterpret_cast<float4*>(dst + e + 4 * h) =
+            make_float4(__uint_as_float((uint32_t)v[4 * h] << 16), __uint_as_float((uint32_t)v[4 * h + 1] << 16),
+                        __uint_as_float((uint32_t)v[4 * h + 2] << 16), __uint_as_float((uint32_t)v[4 * h + 3] << 16));
+    }
+    const int64_t e = e1 - ((e1 - e0) & 7) + threadIdx.x;   // the last elements of the buffer
+    if (e < e1) dst[e] = __uint_as_float((uint32_t)src[e] << 16);
+  } else {
+    for (int64_t e = e0 + threadIdx.x; e < e1; e += 256) dst[e] = __uint_as_float((uint32_t)src[e] << 16);
+  }
+}
 }  // namespace
+
+uint32_t cast_tiles(int64_t count) { return (uint32_t)((count + CAST_PER_WG - 1) / CAST_PER_WG); }
+
+hipError_t launch_cast(const CastList& l, uint32_t total, hipStream_t st) {
+  if (!total) return hipSuccess;
+  hipLaunchKernelGGL(k_cast, dim3(total), dim3(256), 0, st, l);
+  return hipGetLastError();
+}
 
 hipError_t launch_upload(void* dst, const void* host_src, size_t bytes, hipStream_t st) {
   const uint32_t n = (uint32_t)((bytes + 15) / 16);

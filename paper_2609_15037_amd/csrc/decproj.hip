@@ -86,9 +86,14 @@ __device__ __forceinline__ int fresh(int v) {
 
 // GL: lanes per block (B / 4), 0 without the decomposition. A kernel of its own for each: with the
 // choice made per row inside, the branches kept the loads of a chunk from staying in registers.
-template <bool PLAIN, bool MOM16, int GL>
+// G16: the gradient is bf16 (8-byte loads, widened exactly), PLAIN only. Half the bytes are worth
+// little here (24 layers of Qwen2.5-350M shapes 500 -> 460 us: a chunk's phases bound it); what
+// it saves is the fp32 copy, 168 launches and 665 us there.
+template <bool PLAIN, bool MOM16, int GL, bool G16>
 __global__ __launch_bounds__(FNT, 4) void k_decproj(const FusedProb* __restrict__ probs, GemmUniform U) {
   constexpr bool dec = GL > 0;
+  constexpr int GB = G16 ? 2 : 4;   // bytes per gradient element
+  static_assert(PLAIN || !G16, "bf16 gradients: four columns at a time, 8-byte aligned");
   constexpr int gl = dec ? GL : 32, lgB = gl == 8 ? 5 : gl == 16 ? 6 : 7;
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
   const uint32_t t = xcd_remap(blockIdx.x, gridDim.x);
@@ -121,7 +126,7 @@ __global__ __launch_bounds__(FNT, 4) void k_decproj(const FusedProb* __restrict_
 
   // ---- gradient chunk: thread (hw, hl) holds four columns of FU gradient rows,
   //   RIGHT: rows l0 + hw + 16 u, columns 128 c + 4 hl;  LEFT: rows 64 c + 4 hw + u, columns l0 + 4 hl
-  const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc((void*)P.G, (short)0, m * n * 4, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc((void*)P.G, (short)0, m * n * GB, 0x00020000);
   const int row_s = left ? 1 : 16;
   auto row_of = [&](int c, int tf) { return left ? L_KC * c + 4 * (tf >> 5) : (int)l0 + (tf >> 5); };
   auto col_of = [&](int c, int tf) { return (left ? (int)l0 : R_KC * c) + 4 * (tf & 31); };
@@ -129,14 +134,17 @@ __global__ __launch_bounds__(FNT, 4) void k_decproj(const FusedProb* __restrict_
   auto inside = [&](int c) {
     return left ? L_KC * (c + 1) <= m && (int)l0 + L_BM <= n : (int)l0 + R_BM <= m && R_KC * (c + 1) <= n;
   };
-  u32x4 graw[FU];   // the chunk in flight
+  using graw_t = std::conditional_t<G16, u32x2, u32x4>;
+  graw_t graw[FU];   // the chunk in flight
   auto load_g = [&](int c) {   // always FU loads per wave: the waits count them
     const int tf = fresh(tid), row = row_of(c, tf), col = col_of(c, tf);
     const int cc = PLAIN ? col : (col < n - 4 ? col : n - 4);   // the last group's load stays inside the row
-    const int off = (row * n + cc) * 4, st = row_s * n * 4;
+    const int off = (row * n + cc) * GB, st = row_s * n * GB;
 #pragma unroll
     for (int u = 0; u < FU; ++u) {
-      graw[u] = __builtin_amdgcn_raw_buffer_load_b128(rg, (row + row_s * u < m) & (col < n) ? off + u * st : 0, 0, 0);
+      const int o = (row + row_s * u < m) & (col < n) ? off + u * st : 0;
+      if constexpr (G16) graw[u] = __builtin_amdgcn_raw_buffer_load_b64(rg, o, 0, 0);
+      else graw[u] = __builtin_amdgcn_raw_buffer_load_b128(rg, o, 0, 0);
     }
   };
   // zero what load_g read out of place (rows past m, columns past n), shift a clamped last group
@@ -203,9 +211,14 @@ __global__ __launch_bounds__(FNT, 4) void k_decproj(const FusedProb* __restrict_
   for (int c = 0; c < nch; ++c) {
     float4 g[FU];
 #pragma unroll
-    for (int u = 0; u < FU; ++u)
-      g[u] = make_float4(__uint_as_float(graw[u].x), __uint_as_float(graw[u].y), __uint_as_float(graw[u].z),
-                         __uint_as_float(graw[u].w));
+    for (int u = 0; u < FU; ++u) {
+      const graw_t x = graw[u];
+      if constexpr (G16)
+        g[u] = make_float4(__uint_as_float(x.x << 16), __uint_as_float(x.x & 0xFFFF0000u), __uint_as_float(x.y << 16),
+                           __uint_as_float(x.y & 0xFFFF0000u));
+      else
+        g[u] = make_float4(__uint_as_float(x.x), __uint_as_float(x.y), __uint_as_float(x.z), __uint_as_float(x.w));
+    }
     if (!inside(c)) fix_g(c, g);
     // ---- block sums, V in bf16, into LDS
     float sel = 0.f;
@@ -374,23 +387,25 @@ uint32_t decproj_tiles(int side, int64_t L) {
 }
 uint32_t opt_m_tiles(int64_t mk) { return (uint32_t)((mk + OM_PER_WG - 1) / OM_PER_WG); }
 
-hipError_t launch_decproj(const FusedProb* p, int n, uint32_t total, const GemmUniform& u0, bool plain, bool decompose,
-                          hipStream_t st) {
+hipError_t launch_decproj(const FusedProb* p, int n, uint32_t total, const GemmUniform& u0, bool plain, bool g16,
+                          bool decompose, hipStream_t st) {
   if (!total) return hipSuccess;
   GemmUniform u = u0;
   u.nprob = n;
   const dim3 g(total), b(FNT);
   const int gl = decompose ? u.B >> 2 : 0;
-#define DECPROJ(PL, MO, G)                                                    \
-  if (plain == PL && (u.moment_bf16 != 0) == MO && gl == G) {                 \
-    hipLaunchKernelGGL((k_decproj<PL, MO, G>), g, b, 0, st, p, u);            \
-    return hipGetLastError();                                                 \
+#define DECPROJ(PL, MO, G, H)                                                        \
+  if (plain == PL && g16 == H && (u.moment_bf16 != 0) == MO && gl == G) {            \
+    hipLaunchKernelGGL((k_decproj<PL, MO, G, H>), g, b, 0, st, p, u);                \
+    return hipGetLastError();                                                        \
   }
-#define DECPROJ_G(PL, MO) DECPROJ(PL, MO, 0) DECPROJ(PL, MO, 8) DECPROJ(PL, MO, 16) DECPROJ(PL, MO, 32)
-  DECPROJ_G(true, true)
-  DECPROJ_G(true, false)
-  DECPROJ_G(false, true)
-  DECPROJ_G(false, false)
+#define DECPROJ_G(PL, MO, H) DECPROJ(PL, MO, 0, H) DECPROJ(PL, MO, 8, H) DECPROJ(PL, MO, 16, H) DECPROJ(PL, MO, 32, H)
+  DECPROJ_G(true, true, false)
+  DECPROJ_G(true, false, false)
+  DECPROJ_G(false, true, false)
+  DECPROJ_G(false, false, false)
+  DECPROJ_G(true, true, true)
+  DECPROJ_G(true, false, true)
 #undef DECPROJ_G
 #undef DECPROJ
   return hipErrorInvalidValue;

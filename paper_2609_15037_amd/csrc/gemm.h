@@ -104,7 +104,7 @@ __device__ __forceinline__ void tile_coords(uint32_t lt, uint32_t tiles_m, uint3
 
 // One matrix of the fused decomposition and projection (decproj.hip).
 struct FusedProb {
-  const float* G;      // m x n
+  const void* G;       // m x n, fp32 or bf16
   int64_t m, n, s, L;
   const void* P;       // Ptop: r x s, blocked (rows r, K = s padded to 32)
   void* e1;            // Optimizer_V's moments, L x r, row stride ldr
@@ -125,9 +125,10 @@ bool decproj_fits(int64_t m, int64_t n, int32_t r, int B, bool decompose);
 uint32_t decproj_tiles(int side, int64_t L);
 uint32_t opt_m_tiles(int64_t mk);
 struct GemmUniform;
-// plain: every matrix of the list has n % 4 == 0 and a 16-byte aligned gradient
-hipError_t launch_decproj(const FusedProb* p, int n, uint32_t total, const GemmUniform& u, bool plain, bool decompose,
-                          hipStream_t st);
+// plain: every matrix of the list has n % 4 == 0 and a 16-byte aligned gradient; g16 (plain only):
+// bf16 gradients, 8-byte aligned
+hipError_t launch_decproj(const FusedProb* p, int n, uint32_t total, const GemmUniform& u, bool plain, bool g16,
+                          bool decompose, hipStream_t st);
 hipError_t launch_opt_m(const FusedProb* p, int n, uint32_t total, const GemmUniform& u, hipStream_t st);
 
 // Host helpers (gemm.hip).

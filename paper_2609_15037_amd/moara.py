@@ -31,7 +31,8 @@ MOARA_NUM_KERNELS = 5
 
 EXPORTED = (
     "moara_default_config", "moara_allocate_ranks", "moara_resolve_matrix", "moara_state_bytes",
-    "moara_create_state", "moara_refresh_projector", "moara_step", "moara_step_noalloc", "moara_alignment",
+    "moara_create_state", "moara_refresh_projector", "moara_step", "moara_step_mixed", "moara_step_noalloc",
+    "moara_alignment",
     "moara_get_tensor",
     "moara_set_tensor", "moara_refresh_info",
     "moara_set_timing", "moara_kernel_stats", "moara_reset_kernel_stats", "moara_matrix_info",
@@ -91,6 +92,8 @@ def lib():
         "moara_create_state": (ctypes.c_int, [P(moara_config), P(moara_matrix_desc), i32, vp, P(vp)]),
         "moara_refresh_projector": (ctypes.c_int, [vp, P(vp), P(ctypes.c_uint8), vp]),
         "moara_step": (ctypes.c_int, [vp, P(vp), P(vp), P(ctypes.c_uint8), ctypes.c_float, vp]),
+        "moara_step_mixed": (ctypes.c_int, [vp, P(vp), P(vp), P(ctypes.c_uint8), P(vp), P(ctypes.c_uint8), ctypes.c_float,
+                                            vp]),
         "moara_step_noalloc": (ctypes.c_int, [vp, P(vp), P(vp), P(ctypes.c_uint8), ctypes.c_float, vp]),
         "moara_alignment": (ctypes.c_int, [vp, P(vp), P(ctypes.c_uint8), P(ctypes.c_double), vp]),
         "moara_get_tensor": (ctypes.c_int, [vp, i32, i32, vp, ctypes.c_size_t, vp]),
@@ -228,26 +231,25 @@ def moara_destroy_state(st: State):
 
 def _ptr_array(st: State, tensors, what: str, dtype_name: str, active):
     import torch
-    tdt = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype_name]
+    # the checks run on every call, so the usual case (a matrix as it is) is a few attribute reads
+    tdts = {"f32": (torch.float32,), "bf16": (torch.bfloat16,), "f32 or bf16": (torch.float32, torch.bfloat16)}[dtype_name]
     if len(tensors) != st.n:
         raise ValueError(f"{what}: expected {st.n} tensors, got {len(tensors)}")
-    arr = (ctypes.c_void_p * st.n)()
-    for i, t in enumerate(tensors):
-        if active is not None and not active[i]:
-            arr[i] = t.data_ptr() if t is not None else None
-            if t is None:
-                continue
+    ptrs = [None] * st.n
+    for i, (t, shape) in enumerate(zip(tensors, st.shapes)):
         if t is None:
+            if active is not None and not active[i]:
+                continue
             raise ValueError(f"{what}[{i}] is None for an active matrix")
-        if (not t.is_cuda or t.dtype != tdt or not t.is_contiguous() or t.dim() < 2
-                or flatten_shape(t.shape) != st.shapes[i]):
+        if (not t.is_cuda or t.dtype not in tdts or not t.is_contiguous()
+                or (t.shape != shape and (t.dim() < 2 or flatten_shape(t.shape) != shape))):
             raise ValueError(f"{what}[{i}]: need a contiguous {dtype_name} CUDA tensor of shape {st.shapes[i]} "
                              f"(or with that flattened shape), got {tuple(t.shape)} {t.dtype} cuda={t.is_cuda} "
                              f"contiguous={t.is_contiguous()}")
-        if t.device.index != st.device:   # the kernels would read another GPU's memory
+        if t.get_device() != st.device:   # the kernels would read another GPU's memory
             raise ValueError(f"{what}[{i}] is on {t.device}, the state lives on cuda:{st.device}")
-        arr[i] = t.data_ptr()
-    return arr
+        ptrs[i] = t.data_ptr()
+    return (ctypes.c_void_p * st.n)(*ptrs)
 
 
 def _active_array(st: State, active):
@@ -308,6 +310,20 @@ def moara_step(st: State, weights, grads, lr: float, active=None, stream=None, a
     act = active if isinstance(active, ctypes.Array) else _active_array(st, active)
     fn = lib().moara_step_noalloc if noalloc else lib().moara_step
     _check(fn(st.handle, w, g, act, ctypes.c_float(lr), _stream_ptr(stream)))
+
+
+def moara_step_mixed(st: State, weights, grads, grads32, lr: float, active=None, stream=None):
+    """moara_step_mixed of the C ABI: each gradient fp32 or bf16; grads32[i] an fp32 buffer of the
+    same shape for every bf16 gradient of an active matrix (None elsewhere)."""
+    import torch
+    wd = "bf16" if st.cfg.weight_dtype == MOARA_BF16 else "f32"
+    w = _ptr_array(st, weights, "weights", wd, None if st.cfg.zero_grad_mode == 1 else active)
+    g = _ptr_array(st, grads, "grads", "f32 or bf16", active)
+    mixed = [t is not None and t.dtype == torch.bfloat16 for t in grads]
+    g32 = _ptr_array(st, grads32, "grads32", "f32", [b and (active is None or active[i]) for i, b in enumerate(mixed)])
+    flags = (ctypes.c_uint8 * st.n)(*mixed)
+    _check(lib().moara_step_mixed(st.handle, w, g, flags, g32, _active_array(st, active), ctypes.c_float(lr),
+                                  _stream_ptr(stream)))
 
 
 def moara_step_noalloc(st: State, weights, grads, lr: float, active=None, stream=None, args: StepArgs = None):

@@ -20,8 +20,8 @@ before `step()`.
     sched = torch.optim.lr_scheduler.LambdaLR(opt, warmup_cosine(total_steps))
     loss.backward(); opt.step(); sched.step(); opt.zero_grad()
 
-Gradients of the projected weights must be fp32 for the library; for a bf16
-model the optimizer copies them into fp32 buffers it owns. The library's
+Gradients of a bf16 model's projected weights go to the library as they are, with fp32
+buffers the optimizer owns for the kernels that take fp32 only. The library's
 kernels do all the work on the projected weights; this module only marshals.
 """
 from __future__ import annotations
@@ -126,9 +126,13 @@ class MoARa(torch.optim.Optimizer):
         return self._st
 
     def _grads(self) -> List[Optional[torch.Tensor]]:
-        """fp32 contiguous gradients of the targets; None where a target has no gradient
-        (e.g. a routed expert no token reached this step: it is skipped, its state kept)."""
+        """Contiguous fp32 or bf16 gradients of the targets; None where a target has no gradient
+        (e.g. a routed expert no token reached this step: it is skipped, its state kept).
+        The library's step runs on the default stream: a bf16 gradient is handed to it there only,
+        elsewhere it is copied on the current stream first, which its memory belongs to."""
         out = []
+        on_default = torch.cuda.current_stream().cuda_stream == 0
+        bf16, strided = torch.bfloat16, torch.strided
         for i, p in enumerate(self.param_groups[0]["params"]):
             if p.grad is None:
                 out.append(None)
@@ -137,8 +141,9 @@ class MoARa(torch.optim.Optimizer):
             if g.dtype != torch.float32 or not g.is_contiguous():
                 if self._g32[i] is None:
                     self._g32[i] = torch.empty(p.shape, dtype=torch.float32, device=p.device)
-                self._g32[i].copy_(g)
-                g = self._g32[i]
+                if not (on_default and g.dtype == bf16 and g.layout == strided and g.is_contiguous()):
+                    self._g32[i].copy_(g)
+                    g = self._g32[i]
             out.append(g)
         return out
 
@@ -155,8 +160,8 @@ class MoARa(torch.optim.Optimizer):
             grads = self._grads()
             active = [g is not None for g in grads]
             if any(active):
-                M.moara_step(self._st, list(tg["params"]), grads, lr=float(tg["lr"]),
-                             active=None if all(active) else active)
+                M.moara_step_mixed(self._st, tg["params"], grads, self._g32, lr=float(tg["lr"]),
+                                   active=None if all(active) else active)
         if self._adamw is not None:
             og = self.param_groups[1]
             for g in self._adamw.param_groups:   # the schedule drives both groups

@@ -86,3 +86,53 @@ def test_one_pass_and_two_pass_projection_are_bit_identical():
         assert torch.equal(a[0], b[0]), f"matrix {i}: W differs"
         for x, y in zip(a[1:], b[1:]):
             assert np.array_equal(x, y), f"matrix {i}: a moment differs"
+
+
+@pytest.mark.parametrize("case", ["fused", "two_pass", "fp32_operands", "no_decompose", "refresh_due", "misaligned"])
+def test_bf16_gradients_step_as_their_fp32_copies(case):
+    """moara_step_mixed on bf16 gradients gives the bits of moara_step on the converted ones, on every
+    route: read by the one-pass kernel (n % 4 == 0 and 8-byte aligned), or converted first (other
+    widths and alignments, larger ranks, fp32 operands, a due refresh); inactive matrices stay."""
+    import numpy as np
+    import torch
+    from paper_2609_15037_amd import moara as M
+    from tests.harness import gpu_state, rng, to_dev
+    shapes, ranks = list(FUSED), list(FUSED_RANKS)
+    if case == "two_pass":
+        shapes, ranks = shapes + [(300, 320, WL.V)], ranks + [257]
+    operand = "f32" if case == "fp32_operands" else "bf16"
+    c = Case(shapes=shapes, ranks=ranks, block_size=64, operand_dtype=operand, weight_dtype="bf16", weight_std=0.02,
+             moment_dtype="bf16" if operand == "bf16" else "f32", decompose=case != "no_decompose")
+    active = [i != 3 for i in range(len(shapes))]
+    out = []
+    for mixed in (False, True):
+        st = gpu_state(c, refresh_interval=2 if case == "refresh_due" else 0)
+        W, G, B32 = [], [], []
+        for i, ((m, n, _), r) in enumerate(zip(c.shapes, c.ranks)):
+            W.append(to_dev(0.02 * rng(6, 1, i).standard_normal((m, n)), "bf16"))
+            g = to_dev(rng(6, 2, i).standard_normal((m, n)), "bf16")
+            if case == "misaligned":
+                buf = torch.zeros(m * n + 1 + i % 4, dtype=torch.bfloat16, device="cuda")
+                buf[1 + i % 4:] = g.flatten()
+                g = buf[1 + i % 4:].view(m, n)
+            # one in five is fp32 already
+            G.append(g if mixed and i % 5 else g.float())
+            B32.append(torch.full((m, n), float("nan"), device="cuda") if mixed and i % 5 else None)
+            P = np.linalg.qr(rng(6, 3, i).standard_normal((min(m, n), r)))[0]
+            M.moara_set_tensor(st, i, M.MOARA_T_P, P)
+        for _ in range(3):
+            if mixed:
+                M.moara_step_mixed(st, W, G, B32, lr=1e-2, active=active)
+            else:
+                M.moara_step(st, W, G, lr=1e-2, active=active)
+        torch.cuda.synchronize()
+        out.append([(W[i], *[M.moara_get_tensor(st, i, k) for k in
+                             (M.MOARA_T_P, M.MOARA_T_EXP_AVG, M.MOARA_T_EXP_AVG_SQ, M.MOARA_T_MAG_AVG,
+                              M.MOARA_T_MAG_AVG_SQ)]) for i in range(len(shapes))])
+        if mixed:
+            with pytest.raises(ValueError):   # no buffer for the bf16 gradients
+                M.moara_step_mixed(st, W, G, [None] * len(W), lr=1e-2)
+    for i, (a, b) in enumerate(zip(*out)):
+        assert torch.equal(a[0], b[0]), f"matrix {i}: W differs"
+        for x, y in zip(a[1:], b[1:]):
+            assert np.array_equal(x, y), f"matrix {i}: a moment or the projector differs"
