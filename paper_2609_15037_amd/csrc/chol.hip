@@ -2,8 +2,8 @@
 // matrices of a refresh batch (CholeskyQR: Z = Q R with R^T R = Z^T Z, then
 // Q = Z R^{-1}). 64 x 64 blocks; every launch covers all matrices of the batch:
 //   block row 0:   diag      factor C_00 = R_00^T R_00 and invert R_00 (one WG per matrix)
-//   block row k:   row(k)    C_kc -= sum_{j<k} R_jk^T R_jc for c >= k (one WG per block, k >= 1);
-//                            the WG of the diagonal block then factors C_kk and inverts
+//   block row k:   row(k)    C_ic -= R_{k-1,i}^T R_{k-1,c} for k <= i <= c (one WG per block, k >= 1);
+//                            the WG of the diagonal block (k, k) then factors C_kk and inverts
 //                            R_kk while the launch's other WGs still run
 //                  panel(k)  R_kc = R_kk^{-T} C_kc for c > k           (one WG per block)
 //   then X = R^{-1} by recursive doubling over the blocks (k_trtri).
@@ -72,7 +72,7 @@ __device__ __forceinline__ int mfma_col(int jt) { return 16 * jt + (threadIdx.x 
 // broadcast by v_readlane); everything between them is 16 x 16 x 16 products on fp64 MFMA.
 // Measured against the whole 64 x 64 block in one wave's registers (64 values per lane, rows
 // broadcast through LDS): a launch that factors one block 28 us instead of 74 (d = 256 layer),
-// k_chol_row over a Llama-2-7B-shaped layer 90 us on average instead of 151, its refresh 311
+// the left-looking k_chol_row over a Llama-2-7B-shaped layer 90 us on average instead of 151, its refresh 311
 // ms instead of 353 (four 300M-shaped layers 50.9 instead of 60.7, d = 256 10.5 instead of 13.4).
 constexpr int SB = 16, LDX = SB + 1;
 struct DiagLds {
@@ -304,93 +304,88 @@ __global__ __launch_bounds__(256, 4) void k_chol_panel(const RefDev* __restrict_
     }
 }
 
-// Left-looking update of block row k before its factorisation (k >= 1):
-//   C_kc -= sum_{j < k} R_jk^T R_jc     for every block column c >= k
-// One workgroup per (matrix, c); its K loop runs over the factored block rows j < k,
-// with the next pair of blocks loaded into registers while the current one is
-// multiplied (R_jc from LDS, R_jk's 16 columns of each wave straight into its MFMA
-// operand registers: A[i][t] = R_jk[t][16 w + i]). Every block of C is read and written
-// once here, where a right-looking update would rewrite the trailing matrix after every
-// panel; the factored rows R_j. are shared by all workgroups of a matrix (L2 hits).
+// Update of the trailing blocks by the factored block row k - 1 (k >= 1), and factorisation of
+// the diagonal block k:
+//   C_ic -= R_{k-1,i}^T R_{k-1,c}     for k <= i <= c
+// One workgroup per (matrix, block). What bounds a factorisation is its chain of launches, one per
+// block row, and in it the diagonal block's workgroup: one block product and diag_factor. A
+// left-looking update (all of sum_{j < k} in row k's own workgroups, every block of C read and
+// written once) put up to 31 block products before it at w = 2048: 90 us a launch on average in a
+// Llama-2-7B-shaped layer, now 35. The trailing blocks' traffic runs beside the diagonal block's
+// factorisation, when most CUs are idle; applying two or four block rows at a time (half or a
+// quarter of that traffic) measured the same and 2 % more at that size (refresh 290 -> 255, 255, 261 ms)
+// and 1.5 and 4 % more for four 300M-shaped layers (40.9 -> 39.5, 40.1, 40.9 ms).
+// R_{k-1,c} through LDS, R_{k-1,i}'s 16 columns of each wave straight into its MFMA operand
+// registers (A[a][t] = R_{k-1,i}[t][16 w + a]); the block itself is loaded before the product.
 __global__ __launch_bounds__(256, 2) void k_chol_row(const RefDev* __restrict__ ds, const uint32_t* __restrict__ pref,
                                                      int n, int k) {
   // workgroups 0 .. n-1: the diagonal block of matrix t (updated, then factored here);
-  // the rest: the blocks c > k, matrices by prefix
+  // the rest: the other blocks (i, c) row by row, matrices by prefix
   const uint32_t t = blockIdx.x;
   const bool diag = t < (uint32_t)n;
   const int mi = diag ? (int)t : find_pref(pref, n, t - n);
   const RefDev& d = ds[mi];
-  const int w = d.w;
-  if (diag && k >= nblk(w)) return;
-  const int c = diag ? k : k + 1 + (int)(t - n - pref[mi]);
+  const int w = d.w, nb = nblk(w);
+  if (diag && k >= nb) return;
+  int ib = k, c = k;
+  if (!diag) {
+    int rem = 1 + (int)(t - n - pref[mi]);
+    while (rem >= nb - ib) { rem -= nb - ib; ++ib; }
+    c = ib + rem;
+  }
   __shared__ DiagLds S;
   double (*Rb)[LDB] = S.D;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double av[NB / 4], an[NB / 4], pb[16];
-  auto fetch = [&](int j, double (&a)[NB / 4]) {
-    const int col = k * NB + 16 * wave + (lane & 15);
+  double av[NB / 4];
+  {
+    const int col = ib * NB + 16 * wave + (lane & 15);
 #pragma unroll
     for (int ks = 0; ks < NB / 4; ++ks) {
-      const int row = j * NB + 4 * ks + (lane >> 4);
-      a[ks] = (row < w && col < w) ? d.C[(int64_t)row * w + col] : 0.0;
+      const int row = (k - 1) * NB + 4 * ks + (lane >> 4);
+      av[ks] = (row < w && col < w) ? d.C[(int64_t)row * w + col] : 0.0;
     }
+  }
+  load_blk(Rb, d.C, w, k - 1, c);
+  double cv[4][4];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int e = threadIdx.x + 256 * q, i = e >> 6, jj = e & 63;
-      const int row = j * NB + i, col2 = c * NB + jj;
-      pb[q] = (row < w && col2 < w) ? d.C[(int64_t)row * w + col2] : 0.0;
-    }
-  };
-  auto publish = [&]() {
+  for (int jt = 0; jt < 4; ++jt)
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int e = threadIdx.x + 256 * q;
-      Rb[e >> 6][e & 63] = pb[q];
+    for (int r = 0; r < 4; ++r) {
+      const int row = ib * NB + mfma_row(r), col = c * NB + mfma_col(jt);
+      cv[jt][r] = (row < w && col < w) ? d.C[(int64_t)row * w + col] : 0.0;
     }
-  };
+  const double cmax = d.cmax[0];
+  __syncthreads();
   f64x4 acc[4];
 #pragma unroll
   for (int jt = 0; jt < 4; ++jt) acc[jt] = f64x4{0.0, 0.0, 0.0, 0.0};
-  fetch(0, av);
-  publish();
-  __syncthreads();
-  for (int j = 0; j < k; ++j) {
-    if (j + 1 < k) fetch(j + 1, an);
 #pragma unroll
-    for (int ks = 0; ks < NB / 4; ++ks) {
-      const int tr = 4 * ks + (lane >> 4);
+  for (int ks = 0; ks < NB / 4; ++ks) {
+    const int tr = 4 * ks + (lane >> 4);
 #pragma unroll
-      for (int jt = 0; jt < 4; ++jt)
-        acc[jt] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[ks], Rb[tr][16 * jt + (lane & 15)], acc[jt], 0, 0, 0);
-    }
-    __syncthreads();
-    if (j + 1 < k) {
-      publish();
-#pragma unroll
-      for (int ks = 0; ks < NB / 4; ++ks) av[ks] = an[ks];
-      __syncthreads();
-    }
+    for (int jt = 0; jt < 4; ++jt)
+      acc[jt] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[ks], Rb[tr][16 * jt + (lane & 15)], acc[jt], 0, 0, 0);
   }
   if (!diag) {
 #pragma unroll
     for (int jt = 0; jt < 4; ++jt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = k * NB + mfma_row(r), col = c * NB + mfma_col(jt);
-        if (row < w && col < w) d.C[(int64_t)row * w + col] -= acc[jt][r];
+        const int row = ib * NB + mfma_row(r), col = c * NB + mfma_col(jt);
+        if (row < w && col < w) d.C[(int64_t)row * w + col] = cv[jt][r] - acc[jt][r];
       }
     return;
   }
-  // diagonal block: the updated C_kk goes to LDS (free: the K loop ended with a barrier)
-  // and is factored while the other workgroups of the launch run on
-  const double cmax = d.cmax[0];
+  // diagonal block: the updated C_kk goes to LDS and is factored while the other workgroups of
+  // the launch run on
+  __syncthreads();
   const int kb = bsz(w, k);
 #pragma unroll
   for (int jt = 0; jt < 4; ++jt)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int i = mfma_row(r), j = mfma_col(jt), row = k * NB + i, col = k * NB + j;
-      Rb[i][j] = (cmax > 0.0 && i < kb && j < kb) ? d.C[(int64_t)row * w + col] - acc[jt][r] : (i == j ? 1.0 : 0.0);
+      const int i = mfma_row(r), j = mfma_col(jt);
+      Rb[i][j] = (cmax > 0.0 && i < kb && j < kb) ? cv[jt][r] - acc[jt][r] : (i == j ? 1.0 : 0.0);
     }
   __syncthreads();
   diag_factor(S, kb, cmax * 1e-13, d, k * NB);
@@ -492,6 +487,7 @@ __global__ __launch_bounds__(256, 2) void k_trtri(const RefDev* __restrict__ ds,
 }  // namespace
 
 int chol_blocks(int32_t w) { return (w + NB - 1) / NB; }
+uint32_t chol_row_tiles(int nb, int k) { return k >= 1 && k < nb ? (uint32_t)((nb - k) * (nb - k + 1) / 2 - 1) : 0; }
 
 hipError_t launch_chol_diag(const RefDev* d, int n, hipStream_t st) {
   if (!n) return hipSuccess;

@@ -994,8 +994,8 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
       const int T = std::max(0, nb - k - 1);
       pan_pref[(size_t)k * nm + q] = tp; tp += (uint32_t)T;
       // row(k), k >= 1: one workgroup per matrix for the diagonal block (numbered first),
-      // then the blocks c = k+1 .. nb-1 by prefix
-      upd_pref[(size_t)k * nm + q] = tu; tu += (uint32_t)(k >= 1 && k < nb ? nb - k - 1 : 0);
+      // then its other tiles by prefix
+      upd_pref[(size_t)k * nm + q] = tu; tu += chol_row_tiles(nb, k);
     }
     pan_tot[k] = tp; upd_tot[k] = k >= 1 ? (uint32_t)nm + tu : 0;
   }
