@@ -274,11 +274,98 @@ __global__ __launch_bounds__(JNT, 2) void k_jacobi_round(const RefDev* __restric
     if (c + 1 + JAC_RING < nch) load_chunk(c + 1 + JAC_RING, slot);
   };
 
-  // (1) Gram of the 64 columns on fp64 MFMA (v_mfma_f64_16x16x4: lane l supplies
+  // (1) Gram of the 64 columns. Round 0, which meets every block once per sweep, computes all of
+  // it. The other visits compute what only they can know, the 32 x 32 products across the two
+  // blocks and the column norms, and take the products inside a block from the block's last
+  // visit, which has them after its rotations (Gs: G' = R^T G R; an error there costs the angle of
+  // a rotation, not the orthogonality of J). Every column pair is still measured from the columns
+  // themselves once per sweep. 4 of 16 MFMA tiles instead of 10, which bounded the pass: a round of
+  // a Llama-2-7B-shaped layer 117 -> 100 us on average, the same 8 to 9 sweeps (its Jacobi 103 -> 89
+  // ms; the refresh 250 -> 234, of four 300M-shaped layers 39.2 -> 38.3 ms).
+  // Full form on fp64 MFMA (v_mfma_f64_16x16x4: lane l supplies
   // A[l%16][l/16] and B[l/16][l%16] and receives D[4r + l/16][l%16] in register r).
   // G is symmetric: only its ten 16 x 16 tiles (it, jt) with it <= jt are computed
   // (jac_gram_tiles) and mirrored when G is written.
-  {
+  const bool fresh = round == 0;
+  double* Gs = d.X;   // free since the factorisation's last use; nb * 1024 <= w * w doubles for nb > 2
+  constexpr int GPT = 2 * JB * JB / JNT;   // stored products per thread
+  auto gs_at = [&](int q, int& x, int& y) -> int64_t {   // element q of this thread: G[x][y] and its place
+    const int e = tid + JNT * q, b = e / (JB * JB), i = e / JB % JB, j = e % JB;
+    x = JB * b + i;
+    y = JB * b + j;
+    return (int64_t)(b ? bb : ba) * (JB * JB) + JB * i + j;
+  };
+  auto save_blocks = [&]() {
+    if (nb == 2) return;   // one pair: every visit is round 0's
+#pragma unroll
+    for (int q = 0; q < GPT; ++q) {
+      int x, y;
+      const int64_t g = gs_at(q, x, y);
+      Gs[g] = Gm[x][y];
+    }
+  };
+  if (!fresh) {
+    double gp[GPT], nsq[JEPT];
+#pragma unroll
+    for (int q = 0; q < GPT; ++q) {
+      int x, y;
+      gp[q] = Gs[gs_at(q, x, y)];
+    }
+#pragma unroll
+    for (int q = 0; q < JEPT; ++q) nsq[q] = 0.0;
+    // tile (it, jt) of the wave; with eight waves, w and w + 4 (one SIMD) halve the rows of a chunk
+    constexpr int KS = JR / 4 * 4 / JAC_WAVES;
+    const int it = wave >> 1 & 1, jt = 2 + (wave & 1), ks0 = wave >= 4 ? KS : 0;
+    f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
+    prime();
+    for (int c0 = 0; c0 < nch; c0 += JAC_RING) {
+#pragma unroll
+      for (int k = 0; k < JAC_RING; ++k) {
+        if (c0 + k >= nch) break;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const int kr = 4 * (ks0 + ks) + (lane >> 4);
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(T[kr][16 * it + (lane & 15)], T[kr][16 * jt + (lane & 15)], acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int q = 0; q < JEPT; ++q) {   // this thread's elements of the chunk, one column per q
+          const int e = tid + JNT * q;
+          const double v = T[e % JR][e / JR];
+          nsq[q] = fma(v, v, nsq[q]);
+        }
+        __syncthreads();
+        advance(c0 + k, pre[(k + 1) % JAC_RING]);
+        __syncthreads();
+      }
+    }
+    if (wave >= 4) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) Jm[16 * it + 4 * r + (lane >> 4)][16 * jt + (lane & 15)] = acc[r];
+    }
+#pragma unroll
+    for (int q = 0; q < GPT; ++q) {
+      int x, y;
+      gs_at(q, x, y);
+      if (x != y) Gm[x][y] = gp[q];
+    }
+#pragma unroll
+    for (int q = 0; q < JEPT; ++q) {
+#pragma unroll
+      for (int o = JR / 2; o > 0; o >>= 1) nsq[q] += __shfl_xor(nsq[q], o, 64);
+      const int e = tid + JNT * q, x = e / JR;
+      if (e % JR == 0) Gm[x][x] = nsq[q];
+    }
+    __syncthreads();
+    if (wave < 4) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * it + 4 * r + (lane >> 4), j = 16 * jt + (lane & 15);
+        const double v = JAC_WAVES == 8 ? acc[r] + Jm[i][j] : acc[r];
+        Gm[i][j] = v;
+        Gm[j][i] = v;
+      }
+    }
+  } else {
     const uint32_t tiles = jac_gram_tiles(wave);
     const int nt = ((tiles & 0xFF) != 0xFF) + ((tiles >> 8 & 0xFF) != 0xFF) + ((tiles >> 16 & 0xFF) != 0xFF);
     f64x4 acc[3];
@@ -325,7 +412,7 @@ __global__ __launch_bounds__(JNT, 2) void k_jacobi_round(const RefDev* __restric
   }
   __syncthreads();
   // Convergence measure of this pair (before rotating): max |g_xy| / sqrt(g_xx g_yy).
-  const bool full = round == 0 || sweep == 0;   // all column pairs, see (2)
+  const bool full = fresh || sweep == 0;   // all column pairs, see (2)
   {
     double* rn = &Jm[0][0];     // J is built after this: 1 / sqrt(g_xx) of the 64 columns,
     double* red = &Jm[2][0];    // then the waves' maxima
@@ -339,7 +426,7 @@ __global__ __launch_bounds__(JNT, 2) void k_jacobi_round(const RefDev* __restric
     double mx = 0.0;
     for (int e = tid; e < PW * PW; e += JNT) {
       const int x = e / PW, y = e % PW;
-      if (x < y) mx = fmax(mx, fabs(Gm[x][y]) * rn[x] * rn[y]);
+      if (x < y && (fresh || (x < JB && y >= JB))) mx = fmax(mx, fabs(Gm[x][y]) * rn[x] * rn[y]);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
@@ -354,7 +441,10 @@ __global__ __launch_bounds__(JNT, 2) void k_jacobi_round(const RefDev* __restric
       d.jmx[pidx] = (float)mx;
       if (!conv) { d.jmod[ba] = gnow + 1; d.jmod[bb] = gnow + 1; }
     }
-    if (conv) return;   // already orthogonal: nothing to rotate (uniform branch)
+    if (conv) {   // already orthogonal: nothing to rotate (uniform branch)
+      if (fresh) save_blocks();
+      return;
+    }
     __syncthreads();            // red is read by every thread before J overwrites it
   }
   for (int e = tid; e < PW * PW; e += JNT) Jm[e / PW][e % PW] = (e / PW == e % PW) ? 1.0 : 0.0;
@@ -437,6 +527,8 @@ __global__ __launch_bounds__(JNT, 2) void k_jacobi_round(const RefDev* __restric
     }
   }
 
+  save_blocks();
+  __syncthreads();   // region A is overwritten next
   // (3) rotate the 64 columns: Zc[:, pair] <- Zc[:, pair] J, JR rows at a time on
   // fp64 MFMA; wave w computes columns [16 (w % 4), +16) of the chunk's 16-row halves
   // h = w / 4, w / 4 + 4, ... (with four waves both halves share J's fragment). The
