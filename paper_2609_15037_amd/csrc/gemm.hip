@@ -636,7 +636,7 @@ __global__ __launch_bounds__(64 * BWM * BWN, 2) void k_gemm_bf16(const GemmProb*
   constexpr int BBM = 64 * BWM, BBN = 64 * BWN;
   __shared__ __attribute__((aligned(16))) bf16 As[2][BBM * BF_LD];
   __shared__ __attribute__((aligned(16))) bf16 Bs[2][BBN * BF_LD];
-  const uint32_t t = xcd_remap(blockIdx.x, gridDim.x);
+  const uint32_t t = xcd_remap_groups(blockIdx.x, gridDim.x);
   const GemmProb& P = probs[find_prob(probs, U.nprob, t)];
   uint32_t tm, tn;
   tile_coords(t - P.tile_start, (uint32_t)((P.M + BBM - 1) / BBM), P.tiles_n, tm, tn);
@@ -738,7 +738,7 @@ __global__ __launch_bounds__(FNT, BT == 64 ? 4 : 2) void k_gemm_f32(const GemmPr
   constexpr bool BTR = (BMODE == B_NC);
   __shared__ __attribute__((aligned(16))) float As[2][AT ? BK * F_LDT : BT * F_LDK];
   __shared__ __attribute__((aligned(16))) float Bs[2][BTR ? BK * F_LDT : BT * F_LDK];
-  const uint32_t t = xcd_remap(blockIdx.x, gridDim.x);
+  const uint32_t t = xcd_remap_groups(blockIdx.x, gridDim.x);
   const GemmProb& P = probs[find_prob(probs, U.nprob, t)];
   uint32_t tm, tn;
   tile_coords(t - P.tile_start, (uint32_t)((P.M + BT - 1) / BT), P.tiles_n, tm, tn);

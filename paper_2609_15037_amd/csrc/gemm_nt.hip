@@ -111,7 +111,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, (OCC * NWM * NWN + 3) / 4) void k_g
   constexpr int OPS = SA + SB;                        // DMA instructions per wave per stage
   constexpr int SMEM = NS * STAGEB > NW * EPWAVE * 4 ? NS * STAGEB : NW * EPWAVE * 4;
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
-  const uint32_t t = xcd_remap(blockIdx.x, gridDim.x);
+  const uint32_t t = xcd_remap_groups(blockIdx.x, gridDim.x);
   const GemmProb& P = probs[find_prob(probs, U.nprob, t)];
   uint32_t tm, tn;
   // the projection walks two tile rows per group (measured 1.6 % faster than eight on the
