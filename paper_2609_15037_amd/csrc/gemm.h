@@ -149,8 +149,10 @@ int gemm_f32_fit(GemmProb* probs, int n, uint32_t* total);
 // Large-tile bf16 path (gemm_nt.hip): A (M x K) and B (N x K) bf16, K-contiguous,
 // EP_ADAM, EP_UPDATE, EP_STORE or EP_STORE_BF16; 256-row tiles.
 uint32_t gemm_nt_tiles_m(int64_t M);
-uint32_t gemm_nt_tiles_n(int64_t N);
+uint32_t gemm_nt_tiles_n(int64_t N, bool narrow = false);
+// EP_UPDATE on 128-column tiles, two workgroups per CU: for lists whose every K (rank) is this small
+bool gemm_nt_update_narrow(int64_t K);
 bool gemm_nt_eligible(int ep, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc,
                       const void* a, const void* b, const void* c);
 hipError_t launch_gemm_nt(int ep, const GemmProb* probs_dev, int nprob, uint32_t total_tiles, const GemmUniform& u,
-                          hipStream_t st);
+                          hipStream_t st, bool narrow = false);

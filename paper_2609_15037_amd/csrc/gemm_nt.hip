@@ -579,7 +579,20 @@ constexpr int V_NWM = 4, V_NWN = 4, V_WTN = 64, V_NS = 4, V_NSU = 4, V_NSS = 5, 
 #endif
 constexpr int GEMM_NT_BN = V_NWN * V_WTN;
 uint32_t gemm_nt_tiles_m(int64_t M) { return (uint32_t)((M + TBM - 1) / TBM); }
-uint32_t gemm_nt_tiles_n(int64_t N) { return (uint32_t)((N + GEMM_NT_BN - 1) / GEMM_NT_BN); }
+// Narrow tiles (256 x 128, eight waves of 64 x 64, three stages, two workgroups per CU) for the update
+// at small K: with up to eight K steps a tile is mostly its epilogue's stream of W, and one workgroup's
+// loads run beside the other's products. Steps (us): 24 layers of 300M shapes (K = 128 to 256)
+// 860 -> 844, six ragged ones 350 -> 339, no decomposition 257 -> 254; from K = 512 the larger tile's
+// reuse wins (four 7B-shaped layers 4.06 -> 4.11 ms with narrow tiles at every K). A list with
+// both stays on large tiles: the small-K problems on their own cost a second last wave
+// (two Qwen2-7B-shaped layers 2.78 -> 2.79 ms, DeepSeek-MoE the same).
+constexpr int NARROW_BN = 128;
+constexpr int64_t NARROW_K = 256;
+uint32_t gemm_nt_tiles_n(int64_t N, bool narrow) {
+  const int bn = narrow ? NARROW_BN : GEMM_NT_BN;
+  return (uint32_t)((N + bn - 1) / bn);
+}
+bool gemm_nt_update_narrow(int64_t K) { return K <= NARROW_K; }
 
 bool gemm_nt_eligible(int ep, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc,
                       const void* a, const void* b, const void* c) {
@@ -612,9 +625,15 @@ hipError_t launch_nt(int ep, const GemmProb* probs_dev, uint32_t total_tiles, co
 }  // namespace
 
 hipError_t launch_gemm_nt(int ep, const GemmProb* probs_dev, int nprob, uint32_t total_tiles, const GemmUniform& u0,
-                          hipStream_t st) {
+                          hipStream_t st, bool narrow) {
   if (total_tiles == 0 || nprob == 0) return hipSuccess;
   GemmUniform u = u0;
   u.nprob = nprob;
+  if (narrow) {
+    if (ep != EP_UPDATE) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_gemm_nt<EP_UPDATE, 4, NARROW_BN / 64, 64, 3, 2>), dim3(total_tiles), dim3(256 * NARROW_BN / 64), 0, st,
+                       probs_dev, u);
+    return hipGetLastError();
+  }
   return launch_nt<V_NWM, V_NWN, V_WTN, V_NS, V_NSU, V_NSS, V_OCC>(ep, probs_dev, total_tiles, u, st);
 }

@@ -565,6 +565,7 @@ FusedPlan plan_fused(const moara_state* st, const std::vector<int>& idx, const v
 struct GemmPlan {
   std::vector<GemmProb> left, right, back, pnt, bnt;
   uint32_t tl = 0, tr = 0, tb = 0, tpn = 0, tbn = 0;
+  bool narrow = false;                   // bnt runs on 128-column tiles
   int til = 128, tir = 128, tib = 128;   // fp32 operands: the tile each list runs on
   size_t ol = 0, orr = 0, obk = 0, opn = 0, obn = 0;
   int stage(Stager& sg) {
@@ -584,6 +585,8 @@ GemmPlan plan_project_back(const moara_state* st, const std::vector<int>& idx, v
   const int ob = st->cfg.operand_dtype == MOARA_BF16;
   const int kind = ob ? KIND_BF16 : KIND_F32;
   GemmPlan P;
+  P.narrow = true;
+  for (int i : idx) P.narrow = P.narrow && gemm_nt_update_narrow(st->mats[i].r);
   auto &left = P.left, &right = P.right, &back = P.back, &pnt = P.pnt, &bnt = P.bnt;
   auto &tl = P.tl, &tr = P.tr, &tb = P.tb, &tpn = P.tpn, &tbn = P.tbn;
   for (int i : idx) {
@@ -622,7 +625,7 @@ GemmPlan plan_project_back(const moara_state* st, const std::vector<int>& idx, v
       if (h.vpath || (ob && gemm_nt_eligible(EP_UPDATE, h.m, h.n, h.rp, h.rp, h.rp, h.n, b.a, b.b, weights[i]))) {
         b.a_bytes = (uint32_t)(2 * rows_a * h.rp);
         b.b_bytes = (uint32_t)(2 * rows_b * h.rp);
-        b.tiles_n = gemm_nt_tiles_n(b.N);
+        b.tiles_n = gemm_nt_tiles_n(b.N, P.narrow);
         b.tile_start = tbn;
         tbn += gemm_nt_tiles_m(b.M) * b.tiles_n;
         bnt.push_back(b);
@@ -685,7 +688,7 @@ int launch_plan(moara_state* st, const GemmPlan& P, const FusedPlan& F, float lr
   }
   {
     TimerScope ts(st, MOARA_KERN_BACKPROJ, stream);
-    if (!P.bnt.empty()) HIP_TRY(launch_gemm_nt(EP_UPDATE, dev(P.obn), (int)P.bnt.size(), P.tbn, u, stream));
+    if (!P.bnt.empty()) HIP_TRY(launch_gemm_nt(EP_UPDATE, dev(P.obn), (int)P.bnt.size(), P.tbn, u, stream, P.narrow));
     if (!P.back.empty())
       HIP_TRY(launch_gemm(kind, A_KC, B_KC, EP_UPDATE, dev(P.obk), (int)P.back.size(), P.tb, u, stream, P.tib));
   }
