@@ -35,6 +35,7 @@ class Case:
     beta1: float = 0.9
     beta2: float = 0.999
     adam_eps: float = 1e-8
+    decomp_eps: float = 1e-12
     scale: float = 0.25
     lr: float = 1e-3
     weight_std: float = 1e-3
@@ -59,7 +60,8 @@ def case_from_workload(wl: WL.Workload, operand_dtype: Optional[str] = None) -> 
 
 def oracle_cfg(c: Case, i: int, refresh_interval: int = 0) -> O.OracleConfig:
     return O.OracleConfig(block_size=c.block_size, rank=c.ranks[i], beta1=c.beta1, beta2=c.beta2,
-                          adam_eps=c.adam_eps, scale=c.scale, refresh_interval=refresh_interval,
+                          adam_eps=c.adam_eps, decomp_eps=c.decomp_eps, scale=c.scale,
+                          refresh_interval=refresh_interval,
                           decompose=c.decompose, weight_dtype=c.weight_dtype, operand_dtype=c.operand_dtype,
                           moment_dtype=c.moment_dtype)
 
@@ -69,7 +71,8 @@ def gpu_state(c: Case, refresh_interval: int = 0, refresh_iters=None, oversample
     refresh_iters = c.refresh_iters if refresh_iters is None else refresh_iters
     oversample = c.refresh_oversample if oversample is None else oversample
     cfg = M.moara_default_config(
-        block_size=c.block_size, beta1=c.beta1, beta2=c.beta2, adam_eps=c.adam_eps, scale=c.scale,
+        block_size=c.block_size, beta1=c.beta1, beta2=c.beta2, adam_eps=c.adam_eps, decomp_eps=c.decomp_eps,
+        scale=c.scale,
         refresh_interval=refresh_interval, decompose=1 if c.decompose else 0,
         weight_dtype=M.MOARA_BF16 if c.weight_dtype == "bf16" else M.MOARA_F32,
         operand_dtype=M.MOARA_BF16 if c.operand_dtype == "bf16" else M.MOARA_F32,

@@ -56,6 +56,23 @@ def test_one_pass_projection_without_the_decomposition(mom, misalign):
     step_parity(c, 2, misalign=misalign)
 
 
+# decomp_eps = 0, and one so small that 1 / eps overflows fp32: the padding rows of a LEFT matrix's
+# last K panel are zero gradients, whose scale 1 / (0 + eps) is then infinite. m % 32 != 0, with
+# m % 8 zero and not (the transposed decomposition stores groups of 8 rows)
+LEFT_ROWS = [(33, 200, WL.Q), (129, 257, WL.V), (1000, 1032, WL.DOWN), (257, 33, WL.GATE)]
+LEFT_RANKS = [20, 100, 250, 33]
+
+
+@pytest.mark.parametrize("eps", [0.0, 1e-40])
+@pytest.mark.parametrize("two_pass", [False, True])
+def test_padding_stays_zero_when_the_decomposition_epsilon_is_zero(two_pass, eps):
+    """Finite dense gradients give the oracle's finite results on either route (a rank above 256
+    sends a short list through the two-pass kernels)."""
+    c = Case(shapes=LEFT_ROWS + ([(300, 320, WL.K)] if two_pass else []), ranks=LEFT_RANKS + ([257] if two_pass else []),
+             block_size=64, operand_dtype="bf16", weight_dtype="bf16", weight_std=1e-2, decomp_eps=eps)
+    history_parity(c, 2, 330, _grad(c, 330))
+
+
 def test_one_pass_and_two_pass_projection_are_bit_identical():
     """A matrix whose rank exceeds the one-pass kernel's range sends a short list of matrices through
     the two-pass kernels: the same matrices give the same bits with and without it beside them."""
