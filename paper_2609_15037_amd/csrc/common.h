@@ -77,11 +77,8 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t bid, uint32_t nblk) {
   return (xcd < rem) ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
 }
 // xcd_remap_groups: the XCDs take groups of XCD_GROUP tiles in turn, so that each gets a share of
-// every problem in a list. Problems differ in their work per tile (K from 128 to 4096 and more), and
-// with contiguous eighths an XCD that drew the light ones waits for the others. GEMM lists, one
-// against the other: alignment of a 7B-shaped layer 7.00 -> 6.53 ms, its refresh 234 -> 229, step of two
-// DeepSeek-MoE layers (K = 512 beside 128) 535 -> 507 us, of two Qwen2-7B-shaped ones 2.83 -> 2.78 ms,
-// lists of similar tiles unchanged; groups of 32 the same, of 64 235 ms and 2.79 ms. The one-pass
+// every problem in a list (the GEMM lists choose between the two by gemm_xcd_groups). Groups of 32
+// measured the same, of 64 235 instead of 229 ms (refresh of a 7B-shaped layer). The one-pass
 // projection streams the gradient and keeps the eighths (24 layers of 300M shapes 10 us faster).
 constexpr uint32_t XCD_GROUP = 16;
 __device__ __forceinline__ uint32_t xcd_remap_groups(uint32_t bid, uint32_t nblk) {

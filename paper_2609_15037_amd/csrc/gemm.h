@@ -6,6 +6,8 @@
 // layer stack); each workgroup finds its problem by binary search over the
 // problems' tile prefixes, then computes one BM x BN tile.
 #pragma once
+#include <vector>
+
 #include "common.h"
 
 enum { KIND_BF16 = 0, KIND_F32 = 1 };
@@ -81,6 +83,7 @@ struct GemmUniform {
   float lr, scale;
   int32_t moment_bf16;  // EP_ADAM: the moments are stored in bf16
   int32_t lgB;          // log2(B) when B is a power of two, else -1 (set by launch_gemm)
+  int32_t xcd_groups;   // tiles go round the XCDs in groups, see gemm_xcd_groups (set by the launchers)
 };
 
 template <int KIND> struct GemmTile;
@@ -134,8 +137,23 @@ hipError_t launch_opt_m(const FusedProb* p, int n, uint32_t total, const GemmUni
 // Host helpers (gemm.hip).
 uint32_t gemm_tiles_m(int kind, int64_t M);
 uint32_t gemm_tiles_n(int kind, int64_t N);
-hipError_t launch_gemm(int kind, int amode, int bmode, int ep, const GemmProb* probs_dev, int nprob,
-                       uint32_t total_tiles, const GemmUniform& u, hipStream_t st, int tile = 128);
+// `list` is the host copy of the problems at probs_dev.
+hipError_t launch_gemm(int kind, int amode, int bmode, int ep, const GemmProb* probs_dev,
+                       const std::vector<GemmProb>& list, uint32_t total_tiles, const GemmUniform& u, hipStream_t st,
+                       int tile = 128);
+// How a list's tiles are dealt to the XCDs: in groups (xcd_remap_groups) or in contiguous eighths
+// (xcd_remap). Problems differ in their work per tile (K from 128 to 11008, and an epilogue worth
+// about 256 of K), and with eighths the XCDs that drew the light ones wait for the others; but an
+// eighth shares more operand panels in its L2. gemm_xcd_groups: whether the eighths would give
+// some XCD over 3 % more than its share of the work. The fp32 lists, the projection and the
+// update on 256-column tiles go by it; the update on 128-column tiles and the refresh's
+// large-tile products always take groups. Eighths against groups:
+//   uneven  step of two DeepSeek-MoE layers (K = 512 beside 128) 536 -> 502 us, of two
+//           Qwen2-7B-shaped ones 2.81 -> 2.75 ms, alignment of a 7B-shaped layer 7.00 -> 6.53 ms;
+//   even    step of four 7B-shaped layers 4.07 -> 4.12 ms, fp32 products of their refresh 7.6 ->
+//           9.1 ms; but narrow updates, step of 24 layers of 300M shapes 846 -> 835 us, of six
+//           ragged ones 351 -> 341, and refresh products V Z of four 7B-shaped layers 105 -> 103 ms.
+bool gemm_xcd_groups(const std::vector<GemmProb>& list, uint32_t total_tiles);
 // fp32 kind: the tile (128 or 64) a list of problems, laid out for 128 x 128 tiles (`total` of
 // them), is launched with; for 64 the list's prefixes and the total are rewritten.
 // 64 up to 4096 tiles of 128 x 128 (eight rounds of the 512 that run at once): a short list leaves
@@ -154,5 +172,5 @@ uint32_t gemm_nt_tiles_n(int64_t N, bool narrow = false);
 bool gemm_nt_update_narrow(int64_t K);
 bool gemm_nt_eligible(int ep, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc,
                       const void* a, const void* b, const void* c);
-hipError_t launch_gemm_nt(int ep, const GemmProb* probs_dev, int nprob, uint32_t total_tiles, const GemmUniform& u,
-                          hipStream_t st, bool narrow = false);
+hipError_t launch_gemm_nt(int ep, const GemmProb* probs_dev, const std::vector<GemmProb>& list, uint32_t total_tiles,
+                          const GemmUniform& u, hipStream_t st, bool narrow = false);

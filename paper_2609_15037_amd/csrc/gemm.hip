@@ -636,7 +636,7 @@ __global__ __launch_bounds__(64 * BWM * BWN, 2) void k_gemm_bf16(const GemmProb*
   constexpr int BBM = 64 * BWM, BBN = 64 * BWN;
   __shared__ __attribute__((aligned(16))) bf16 As[2][BBM * BF_LD];
   __shared__ __attribute__((aligned(16))) bf16 Bs[2][BBN * BF_LD];
-  const uint32_t t = xcd_remap_groups(blockIdx.x, gridDim.x);
+  const uint32_t t = U.xcd_groups ? xcd_remap_groups(blockIdx.x, gridDim.x) : xcd_remap(blockIdx.x, gridDim.x);
   const GemmProb& P = probs[find_prob(probs, U.nprob, t)];
   uint32_t tm, tn;
   tile_coords(t - P.tile_start, (uint32_t)((P.M + BBM - 1) / BBM), P.tiles_n, tm, tn);
@@ -738,7 +738,7 @@ __global__ __launch_bounds__(FNT, BT == 64 ? 4 : 2) void k_gemm_f32(const GemmPr
   constexpr bool BTR = (BMODE == B_NC);
   __shared__ __attribute__((aligned(16))) float As[2][AT ? BK * F_LDT : BT * F_LDK];
   __shared__ __attribute__((aligned(16))) float Bs[2][BTR ? BK * F_LDT : BT * F_LDK];
-  const uint32_t t = xcd_remap_groups(blockIdx.x, gridDim.x);
+  const uint32_t t = U.xcd_groups ? xcd_remap_groups(blockIdx.x, gridDim.x) : xcd_remap(blockIdx.x, gridDim.x);
   const GemmProb& P = probs[find_prob(probs, U.nprob, t)];
   uint32_t tm, tn;
   tile_coords(t - P.tile_start, (uint32_t)((P.M + BT - 1) / BT), P.tiles_n, tm, tn);
@@ -786,11 +786,35 @@ int gemm_f32_fit(GemmProb* probs, int n, uint32_t* total) {
     return hipGetLastError();                                                                                            \
   }
 
-hipError_t launch_gemm(int kind, int amode, int bmode, int ep, const GemmProb* probs_dev, int nprob,
-                       uint32_t total_tiles, const GemmUniform& u0, hipStream_t st, int tile) {
-  if (total_tiles == 0 || nprob == 0) return hipSuccess;
+bool gemm_xcd_groups(const std::vector<GemmProb>& list, uint32_t total) {
+  constexpr uint32_t X = 8;
+  constexpr double EPILOGUE_K = 256, UNEVEN = 1.03;
+  const uint32_t per = total / X, rem = total % X;
+  double work[X] = {}, all = 0;
+  uint32_t x = 0, end = per + (rem > 0);   // the eighth that tile t lies in ends at tile `end`
+  for (size_t i = 0; i < list.size(); ++i) {
+    const uint32_t stop = i + 1 < list.size() ? list[i + 1].tile_start : total;
+    const double cost = EPILOGUE_K + (double)list[i].K * (list[i].nseg > 1 ? list[i].nseg : 1);
+    for (uint32_t t = list[i].tile_start; t < stop;) {
+      while (t >= end) { ++x; end += per + (x < rem); }
+      const uint32_t upto = stop < end ? stop : end;
+      work[x] += cost * (upto - t);
+      t = upto;
+    }
+    all += cost * (stop - list[i].tile_start);
+  }
+  double most = 0;
+  for (double w : work) most = w > most ? w : most;
+  return most * X > UNEVEN * all;
+}
+
+hipError_t launch_gemm(int kind, int amode, int bmode, int ep, const GemmProb* probs_dev,
+                       const std::vector<GemmProb>& list, uint32_t total_tiles, const GemmUniform& u0, hipStream_t st,
+                       int tile) {
+  if (total_tiles == 0 || list.empty()) return hipSuccess;
   GemmUniform u = u0;
-  u.nprob = nprob;
+  u.nprob = (int)list.size();
+  u.xcd_groups = gemm_xcd_groups(list, total_tiles);
   u.lgB = (u.B > 0 && (u.B & (u.B - 1)) == 0) ? __builtin_ctz(u.B) : -1;
   const dim3 grid(total_tiles);
   if (kind == KIND_BF16) {

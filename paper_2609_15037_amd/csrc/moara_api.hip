@@ -680,17 +680,17 @@ int launch_plan(moara_state* st, const GemmPlan& P, const FusedPlan& F, float lr
       HIP_TRY(launch_decproj(fp, (int)F.p[q].size(), F.tiles[q], uf, q != 1, q == 2, dec, stream));
       if (dec) HIP_TRY(launch_opt_m(fp, (int)F.p[q].size(), F.tiles_m[q], uf, stream));
     }
-    if (!P.pnt.empty()) HIP_TRY(launch_gemm_nt(EP_ADAM, dev(P.opn), (int)P.pnt.size(), P.tpn, u, stream));
+    if (!P.pnt.empty()) HIP_TRY(launch_gemm_nt(EP_ADAM, dev(P.opn), P.pnt, P.tpn, u, stream));
     if (!P.right.empty())
-      HIP_TRY(launch_gemm(kind, A_G_ROW, B_KC, EP_ADAM, dev(P.orr), (int)P.right.size(), P.tr, u, stream, P.tir));
+      HIP_TRY(launch_gemm(kind, A_G_ROW, B_KC, EP_ADAM, dev(P.orr), P.right, P.tr, u, stream, P.tir));
     if (!P.left.empty())
-      HIP_TRY(launch_gemm(kind, A_G_TRANS, B_KC, EP_ADAM, dev(P.ol), (int)P.left.size(), P.tl, u, stream, P.til));
+      HIP_TRY(launch_gemm(kind, A_G_TRANS, B_KC, EP_ADAM, dev(P.ol), P.left, P.tl, u, stream, P.til));
   }
   {
     TimerScope ts(st, MOARA_KERN_BACKPROJ, stream);
-    if (!P.bnt.empty()) HIP_TRY(launch_gemm_nt(EP_UPDATE, dev(P.obn), (int)P.bnt.size(), P.tbn, u, stream, P.narrow));
+    if (!P.bnt.empty()) HIP_TRY(launch_gemm_nt(EP_UPDATE, dev(P.obn), P.bnt, P.tbn, u, stream, P.narrow));
     if (!P.back.empty())
-      HIP_TRY(launch_gemm(kind, A_KC, B_KC, EP_UPDATE, dev(P.obk), (int)P.back.size(), P.tb, u, stream, P.tib));
+      HIP_TRY(launch_gemm(kind, A_KC, B_KC, EP_UPDATE, dev(P.obk), P.back, P.tb, u, stream, P.tib));
   }
   return MOARA_OK;
 }
@@ -1247,7 +1247,7 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
 
   auto gemm = [&](int am, int q, const GemmList& l) -> hipError_t {
     if (l.first.empty()) return hipSuccess;
-    return launch_gemm(kind, am, B_NC, EP_STORE, (const GemmProb*)D(q), (int)l.first.size(), l.second, u, stream, l.tile);
+    return launch_gemm(kind, am, B_NC, EP_STORE, (const GemmProb*)D(q), l.first, l.second, u, stream, l.tile);
   };
   const uint32_t* PAN = (const uint32_t*)D(11);
   const uint32_t* UPD = (const uint32_t*)D(12);
@@ -1275,7 +1275,7 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
     if (e == hipSuccess) e = gemm(A_KC, 31, aZf);
     if (e == hipSuccess) e = launch_transpose((const TransProb*)D(28), (int)tR.size(), ttr, stream);
     if (e == hipSuccess)
-      e = launch_gemm_nt(EP_STORE_BF16, (const GemmProb*)D(next_split ? 30 : 29), (int)qZ.size(), tqz, u, stream);
+      e = launch_gemm_nt(EP_STORE_BF16, (const GemmProb*)D(next_split ? 30 : 29), qZ, tqz, u, stream);
     return e;
   };
   TimerScope ts(st, MOARA_KERN_REFRESH, stream);
@@ -1304,16 +1304,16 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
     if (!nY.empty()) {
       if (it < q_bf) {
         if (!zt_ready) HIP_TRY(launch_transpose((const TransProb*)D(18), (int)tZ.size(), ttz, stream));
-        HIP_TRY(launch_gemm_nt(EP_STORE_BF16, (const GemmProb*)D(20), (int)nY.size(), tny, u, stream));
-        HIP_TRY(launch_gemm_nt(EP_STORE, (const GemmProb*)D(21), (int)nZ.size(), tnz, u, stream));
+        HIP_TRY(launch_gemm_nt(EP_STORE_BF16, (const GemmProb*)D(20), nY, tny, u, stream));
+        HIP_TRY(launch_gemm_nt(EP_STORE, (const GemmProb*)D(21), nZ, tnz, u, stream));
       } else {
         if (!zt_ready) HIP_TRY(launch_transpose((const TransProb*)D(15), (int)tZs.size(), ttz, stream));
         if (!last) {
           const bool five = it + REFRESH_SPLIT5_ITERS >= q_iters;
-          HIP_TRY(launch_gemm_nt(EP_STORE_BF16, (const GemmProb*)D(five ? 16 : 25), (int)nYs.size(), tny, u, stream));
-          HIP_TRY(launch_gemm_nt(EP_STORE, (const GemmProb*)D(five ? 17 : 26), (int)nZs.size(), tnz, u, stream));
+          HIP_TRY(launch_gemm_nt(EP_STORE_BF16, (const GemmProb*)D(five ? 16 : 25), five ? nYs : nYs3, tny, u, stream));
+          HIP_TRY(launch_gemm_nt(EP_STORE, (const GemmProb*)D(five ? 17 : 26), five ? nZs : nZs3, tnz, u, stream));
         } else {
-          HIP_TRY(launch_gemm_nt(EP_STORE, (const GemmProb*)D(23), (int)nYf.size(), tnyf, u, stream));
+          HIP_TRY(launch_gemm_nt(EP_STORE, (const GemmProb*)D(23), nYf, tnyf, u, stream));
         }
       }
     }
@@ -1327,7 +1327,7 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
       HIP_TRY(gemm(A_G_ROW, 10, xt2L));
       if (!nY.empty()) {
         HIP_TRY(launch_transpose((const TransProb*)D(24), (int)tY2.size(), tty2, stream));
-        HIP_TRY(launch_gemm_nt(EP_STORE, (const GemmProb*)D(27), (int)nZf.size(), tnz, u, stream));
+        HIP_TRY(launch_gemm_nt(EP_STORE, (const GemmProb*)D(27), nZf, tnz, u, stream));
       }
     }
   }
@@ -1338,7 +1338,7 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
   for (int sw = 0; sw < MAX_SWEEPS; ++sw)
     for (int rr = 0; rr < nb_max - 1; ++rr) HIP_TRY(launch_jacobi_round(RD, nm, tj, rr, sw, stream));
   HIP_TRY(launch_finalize_order(RD, nm, tnorm, stream));
-  HIP_TRY(launch_gemm(kind, A_KC, B_KC, EP_STORE, (const GemmProb*)D(22), nm, tpw, u, stream, tile_pw));
+  HIP_TRY(launch_gemm(kind, A_KC, B_KC, EP_STORE, (const GemmProb*)D(22), pwl, tpw, u, stream, tile_pw));
   int32_t rmax = 0;
   for (auto& x : rm) rmax = std::max(rmax, st->mats[x.idx].r);
   HIP_TRY(launch_finalize_out(RD, nm, rmax, stream));
@@ -1752,11 +1752,11 @@ int moara_alignment(moara_state* st, const void* const* grads, const uint8_t* ac
   {
     TimerScope ts(st, MOARA_KERN_ALIGN, hs);
     if (!projR.empty())
-      HIP_TRY(launch_gemm(KIND_F32, A_G_ROW, B_NC, EP_STORE, (const GemmProb*)(st->dev_arena + oR), (int)projR.size(), tR, u, hs, tiR));
+      HIP_TRY(launch_gemm(KIND_F32, A_G_ROW, B_NC, EP_STORE, (const GemmProb*)(st->dev_arena + oR), projR, tR, u, hs, tiR));
     if (!projL.empty())
-      HIP_TRY(launch_gemm(KIND_F32, A_G_TRANS, B_NC, EP_STORE, (const GemmProb*)(st->dev_arena + oL), (int)projL.size(), tL, u, hs, tiL));
+      HIP_TRY(launch_gemm(KIND_F32, A_G_TRANS, B_NC, EP_STORE, (const GemmProb*)(st->dev_arena + oL), projL, tL, u, hs, tiL));
     HIP_TRY(hipMemsetAsync(red, 0, 8 * 3 * idx.size(), hs));
-    HIP_TRY(launch_gemm(KIND_F32, A_KC, B_KC, EP_ALIGN, (const GemmProb*)(st->dev_arena + oB), (int)rec.size(), tr, u, hs, tiB));
+    HIP_TRY(launch_gemm(KIND_F32, A_KC, B_KC, EP_ALIGN, (const GemmProb*)(st->dev_arena + oB), rec, tr, u, hs, tiB));
   }
   std::vector<double> sums(3 * idx.size());
   HIP_TRY(hipMemcpyAsync(sums.data(), red, 8 * sums.size(), hipMemcpyDeviceToHost, hs));
