@@ -2,7 +2,7 @@
 // matrices of a refresh batch (CholeskyQR: Z = Q R with R^T R = Z^T Z, then
 // Q = Z R^{-1}). 64 x 64 blocks; every launch covers all matrices of the batch:
 //   block row 0:   diag      factor C_00 = R_00^T R_00 and invert R_00 (one WG per matrix)
-//   block row k:   row(k)    C_ic -= R_{k-1,i}^T R_{k-1,c} for k <= i <= c (one WG per block, k >= 1);
+//   block row k:   row(k)    apply R's factored rows to C, right- or left-looking (one WG per block, k >= 1);
 //                            the WG of the diagonal block (k, k) then factors C_kk and inverts
 //                            R_kk while the launch's other WGs still run
 //                  panel(k)  R_kc = R_kk^{-T} C_kc for c > k           (one WG per block)
@@ -304,23 +304,27 @@ __global__ __launch_bounds__(256, 4) void k_chol_panel(const RefDev* __restrict_
     }
 }
 
-// Update of the trailing blocks by the factored block row k - 1 (k >= 1), and factorisation of
-// the diagonal block k:
-//   C_ic -= R_{k-1,i}^T R_{k-1,c}     for k <= i <= c
-// One workgroup per (matrix, block). What bounds a factorisation is its chain of launches, one per
-// block row, and in it the diagonal block's workgroup: one block product and diag_factor. A
-// left-looking update (all of sum_{j < k} in row k's own workgroups, every block of C read and
-// written once) put up to 31 block products before it at w = 2048: 90 us a launch on average in a
-// Llama-2-7B-shaped layer, now 35. The trailing blocks' traffic runs beside the diagonal block's
-// factorisation, when most CUs are idle; applying two or four block rows at a time (half or a
-// quarter of that traffic) measured the same and 2 % more at that size (refresh 290 -> 255, 255, 261 ms)
-// and 1.5 and 4 % more for four 300M-shaped layers (40.9 -> 39.5, 40.1, 40.9 ms).
-// R_{k-1,c} through LDS, R_{k-1,i}'s 16 columns of each wave straight into its MFMA operand
-// registers (A[a][t] = R_{k-1,i}[t][16 w + a]); the block itself is loaded before the product.
+// Update before the factorisation of block row k (k >= 1), and factorisation of the diagonal
+// block k. One workgroup per (matrix, block), in one of two forms:
+//   right-looking:  C_ic -= R_{k-1,i}^T R_{k-1,c}              for k <= i <= c
+//   left-looking:   C_kc -= sum_{j < k} R_jk^T R_jc, j rising  for k <= c
+// Both apply the same MFMA steps to a block in the same order (the block itself is the accumulator,
+// and in memory between launches a double as well), so the factor does not depend on the form.
+// What bounds a factorisation of few matrices is its chain of launches, one per block row, and in it
+// the diagonal block's workgroup: right-looking, that is one block product and diag_factor, and
+// the trailing blocks' traffic runs beside it while most CUs are idle (35 us a launch on average
+// in a Llama-2-7B-shaped layer; left-looking, up to 31 products at w = 2048, 90 us). In a batch whose
+// trailing blocks keep the chip busy by themselves that traffic is what counts, and left-looking
+// reads and writes every block of C once (32 such layers: 345 ms of a refresh against 201). See
+// chol_left_looking. Applying two or four block rows at a time, right-looking, measured 0 and 2 %
+// more at one 7B-shaped layer (refresh 255, 255, 261 ms) and 1.5 and 4 % at four 300M-shaped ones.
+// R_jc through LDS, R_ji's 16 columns of each wave straight into its MFMA operand registers
+// (A[a][t] = R_ji[t][16 w + a]), the next pair loaded while the current one is multiplied.
+template <bool LEFT>
 __global__ __launch_bounds__(256, 2) void k_chol_row(const RefDev* __restrict__ ds, const uint32_t* __restrict__ pref,
                                                      int n, int k) {
   // workgroups 0 .. n-1: the diagonal block of matrix t (updated, then factored here);
-  // the rest: the other blocks (i, c) row by row, matrices by prefix
+  // the rest: the other blocks (i, c) row by row (LEFT: of row k only), matrices by prefix
   const uint32_t t = blockIdx.x;
   const bool diag = t < (uint32_t)n;
   const int mi = diag ? (int)t : find_pref(pref, n, t - n);
@@ -330,41 +334,70 @@ __global__ __launch_bounds__(256, 2) void k_chol_row(const RefDev* __restrict__ 
   int ib = k, c = k;
   if (!diag) {
     int rem = 1 + (int)(t - n - pref[mi]);
-    while (rem >= nb - ib) { rem -= nb - ib; ++ib; }
+    if (!LEFT)
+      while (rem >= nb - ib) { rem -= nb - ib; ++ib; }
     c = ib + rem;
   }
   __shared__ DiagLds S;
   double (*Rb)[LDB] = S.D;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double av[NB / 4];
-  {
+  double av[NB / 4], pb[16];
+  auto fetch_a = [&](int j, double (&a)[NB / 4]) {
     const int col = ib * NB + 16 * wave + (lane & 15);
 #pragma unroll
     for (int ks = 0; ks < NB / 4; ++ks) {
-      const int row = (k - 1) * NB + 4 * ks + (lane >> 4);
-      av[ks] = (row < w && col < w) ? d.C[(int64_t)row * w + col] : 0.0;
+      const int row = j * NB + 4 * ks + (lane >> 4);
+      a[ks] = (row < w && col < w) ? d.C[(int64_t)row * w + col] : 0.0;
     }
-  }
-  load_blk(Rb, d.C, w, k - 1, c);
-  double cv[4][4];
+  };
+  auto fetch_b = [&](int j) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int e = threadIdx.x + 256 * q, row = j * NB + (e >> 6), col = c * NB + (e & 63);
+      pb[q] = (row < w && col < w) ? d.C[(int64_t)row * w + col] : 0.0;
+    }
+  };
+  auto publish_b = [&]() {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int e = threadIdx.x + 256 * q;
+      Rb[e >> 6][e & 63] = pb[q];
+    }
+  };
+  const int j0 = LEFT ? 0 : k - 1;
+  fetch_a(j0, av);
+  fetch_b(j0);
+  f64x4 acc[4];
 #pragma unroll
   for (int jt = 0; jt < 4; ++jt)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int row = ib * NB + mfma_row(r), col = c * NB + mfma_col(jt);
-      cv[jt][r] = (row < w && col < w) ? d.C[(int64_t)row * w + col] : 0.0;
+      acc[jt][r] = (row < w && col < w) ? d.C[(int64_t)row * w + col] : 0.0;
     }
+  publish_b();
   const double cmax = d.cmax[0];
   __syncthreads();
-  f64x4 acc[4];
+  for (int j = j0; j < k; ++j) {
+    double an[NB / 4];
+    if (LEFT && j + 1 < k) {
+      fetch_a(j + 1, an);
+      fetch_b(j + 1);
+    }
 #pragma unroll
-  for (int jt = 0; jt < 4; ++jt) acc[jt] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int ks = 0; ks < NB / 4; ++ks) {
+      const int tr = 4 * ks + (lane >> 4);
 #pragma unroll
-  for (int ks = 0; ks < NB / 4; ++ks) {
-    const int tr = 4 * ks + (lane >> 4);
+      for (int jt = 0; jt < 4; ++jt)
+        acc[jt] = __builtin_amdgcn_mfma_f64_16x16x4f64(-av[ks], Rb[tr][16 * jt + (lane & 15)], acc[jt], 0, 0, 0);
+    }
+    if (LEFT && j + 1 < k) {
+      __syncthreads();
+      publish_b();
 #pragma unroll
-    for (int jt = 0; jt < 4; ++jt)
-      acc[jt] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[ks], Rb[tr][16 * jt + (lane & 15)], acc[jt], 0, 0, 0);
+      for (int ks = 0; ks < NB / 4; ++ks) av[ks] = an[ks];
+      __syncthreads();
+    }
   }
   if (!diag) {
 #pragma unroll
@@ -372,7 +405,7 @@ __global__ __launch_bounds__(256, 2) void k_chol_row(const RefDev* __restrict__ 
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = ib * NB + mfma_row(r), col = c * NB + mfma_col(jt);
-        if (row < w && col < w) d.C[(int64_t)row * w + col] = cv[jt][r] - acc[jt][r];
+        if (row < w && col < w) d.C[(int64_t)row * w + col] = acc[jt][r];
       }
     return;
   }
@@ -385,7 +418,7 @@ __global__ __launch_bounds__(256, 2) void k_chol_row(const RefDev* __restrict__ 
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int i = mfma_row(r), j = mfma_col(jt);
-      Rb[i][j] = (cmax > 0.0 && i < kb && j < kb) ? cv[jt][r] - acc[jt][r] : (i == j ? 1.0 : 0.0);
+      Rb[i][j] = (cmax > 0.0 && i < kb && j < kb) ? acc[jt][r] : (i == j ? 1.0 : 0.0);
     }
   __syncthreads();
   diag_factor(S, kb, cmax * 1e-13, d, k * NB);
@@ -487,7 +520,16 @@ __global__ __launch_bounds__(256, 2) void k_trtri(const RefDev* __restrict__ ds,
 }  // namespace
 
 int chol_blocks(int32_t w) { return (w + NB - 1) / NB; }
-uint32_t chol_row_tiles(int nb, int k) { return k >= 1 && k < nb ? (uint32_t)((nb - k) * (nb - k + 1) / 2 - 1) : 0; }
+uint32_t chol_row_tiles(int nb, int k, bool left) {
+  if (k < 1 || k >= nb) return 0;
+  return left ? (uint32_t)(nb - k - 1) : (uint32_t)((nb - k) * (nb - k + 1) / 2 - 1);
+}
+// What the right-looking form adds is traffic, all trailing blocks once per block row (sum over the
+// matrices of nb^3 / 3 block updates); what the left-looking one adds is a chain of nbmax^2 / 2
+// block products before the diagonal blocks. Refresh, right against left (ms): a d = 256 layer 7.1 and
+// 7.2; 24 layers of 300M shapes (ratio 675) 135.7 and 137.0; 1, 4, 8, 16, 32 layers of Llama-2-7B
+// shapes (ratio 112 each) 228 and 266, 626 and 655, 1131 and 1143, 2160 and 2151, 4234 and 4181.
+bool chol_left_looking(int64_t sum_nb3, int nbmax) { return sum_nb3 > 1300 * (int64_t)nbmax * nbmax; }
 
 hipError_t launch_chol_diag(const RefDev* d, int n, hipStream_t st) {
   if (!n) return hipSuccess;
@@ -499,9 +541,11 @@ hipError_t launch_chol_panel(const RefDev* d, const uint32_t* pref, int n, uint3
   hipLaunchKernelGGL(k_chol_panel, dim3(total), dim3(256), 0, st, d, pref, n, k);
   return hipGetLastError();
 }
-hipError_t launch_chol_row(const RefDev* d, const uint32_t* pref, int n, uint32_t total, int k, hipStream_t st) {
+hipError_t launch_chol_row(const RefDev* d, const uint32_t* pref, int n, uint32_t total, int k, bool left,
+                           hipStream_t st) {
   if (!n || k < 1 || total < (uint32_t)n) return hipSuccess;
-  hipLaunchKernelGGL(k_chol_row, dim3(total), dim3(256), 0, st, d, pref, n, k);
+  if (left) hipLaunchKernelGGL(k_chol_row<true>, dim3(total), dim3(256), 0, st, d, pref, n, k);
+  else hipLaunchKernelGGL(k_chol_row<false>, dim3(total), dim3(256), 0, st, d, pref, n, k);
   return hipGetLastError();
 }
 int trtri_levels(int32_t nbmax) { int l = 0; while ((1 << l) < nbmax) ++l; return l; }

@@ -986,7 +986,13 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
   };
   // workgroup prefixes of the blocked Cholesky / inverse launches (same for every orth of the chunk)
   int nbmax = 1;
-  for (auto& x : rm) nbmax = std::max(nbmax, chol_blocks(x.w));
+  int64_t nb3 = 0;
+  for (auto& x : rm) {
+    const int64_t nb = chol_blocks(x.w);
+    nbmax = std::max(nbmax, (int)nb);
+    nb3 += nb * nb * nb;
+  }
+  const bool chol_left = chol_left_looking(nb3, nbmax);
   const int nlev = trtri_levels(nbmax);
   std::vector<uint32_t> pan_pref((size_t)nbmax * nm), upd_pref((size_t)nbmax * nm), inv_pref((size_t)std::max(1, nlev) * nm);
   std::vector<uint32_t> pan_tot(nbmax), upd_tot(nbmax), inv_tot(std::max(1, nlev));
@@ -998,7 +1004,7 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
       pan_pref[(size_t)k * nm + q] = tp; tp += (uint32_t)T;
       // row(k), k >= 1: one workgroup per matrix for the diagonal block (numbered first),
       // then its other tiles by prefix
-      upd_pref[(size_t)k * nm + q] = tu; tu += chol_row_tiles(nb, k);
+      upd_pref[(size_t)k * nm + q] = tu; tu += chol_row_tiles(nb, k, chol_left);
     }
     pan_tot[k] = tp; upd_tot[k] = k >= 1 ? (uint32_t)nm + tu : 0;
   }
@@ -1255,7 +1261,8 @@ int refresh_chunk(moara_state* st, const std::vector<int>& idx, const void* cons
   auto chol_inv = [&]() -> hipError_t {      // C -> R (in place), X = R^{-1}, Rinv = fp32(X)
     hipError_t e = hipSuccess;
     for (int k = 0; k < nbmax && e == hipSuccess; ++k) {
-      e = k == 0 ? launch_chol_diag(RD, nm, stream) : launch_chol_row(RD, UPD + (size_t)k * nm, nm, upd_tot[k], k, stream);
+      e = k == 0 ? launch_chol_diag(RD, nm, stream)
+                 : launch_chol_row(RD, UPD + (size_t)k * nm, nm, upd_tot[k], k, chol_left, stream);
       if (e == hipSuccess) e = launch_chol_panel(RD, PAN + (size_t)k * nm, nm, pan_tot[k], k, stream);
     }
     for (int l = 1; l <= nlev && e == hipSuccess; ++l)

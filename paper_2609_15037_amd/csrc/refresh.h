@@ -116,10 +116,12 @@ hipError_t launch_split_lo(const SplitProb* p, int n, uint32_t total, hipStream_
 hipError_t launch_gauss(const RefDev* d, int n, uint32_t total, hipStream_t st);
 hipError_t launch_gram(const GramProb* g, int n, uint32_t total, hipStream_t st);
 int chol_blocks(int32_t w);
-uint32_t chol_row_tiles(int nb, int k);   // workgroups of k_chol_row beside the diagonal block's
+uint32_t chol_row_tiles(int nb, int k, bool left);   // workgroups of k_chol_row beside the diagonal block's
+// the form of a batch: sum_nb3 = sum of the cubed block counts of its matrices, nbmax the largest count
+bool chol_left_looking(int64_t sum_nb3, int nbmax);
 hipError_t launch_chol_diag(const RefDev* d, int n, hipStream_t st);   // block 0
 hipError_t launch_chol_panel(const RefDev* d, const uint32_t* pref, int n, uint32_t total, int k, hipStream_t st);
-hipError_t launch_chol_row(const RefDev* d, const uint32_t* pref, int n, uint32_t total, int k,
+hipError_t launch_chol_row(const RefDev* d, const uint32_t* pref, int n, uint32_t total, int k, bool left,
                            hipStream_t st);   // k >= 1, factors block k too
 int trtri_levels(int32_t nbmax);
 uint32_t trtri_tiles(int32_t w, int l);
