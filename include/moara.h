@@ -170,10 +170,9 @@ int moara_resolve_matrix(const moara_config* cfg, const moara_matrix_desc* desc,
  * the per-step workspace; the refresh workspace is reported separately because
  * it is sized per refresh batch: a refresh works through its matrices in chunks
  * of at most 128 GiB of workspace, so the figure is the smaller of the whole
- * batch's need and that bound plus the average matrix's share). Where the bf16
- * operands of a matrix have to be padded to whole panels (sizes that are no
- * multiple of 32, decompose = 0), its direction workspace (2 m n bytes) and the
- * padding are part of the second figure; a state allocates them when created. The environment
+ * batch's need and that bound plus the average matrix's share). With bf16
+ * operands the first figure holds a direction workspace of 2 m n bytes per matrix and
+ * the padding of the operands to whole 32-wide panels. The environment
  * variable MOARA_REFRESH_CHUNK_MIB, when set to a positive integer, replaces the
  * bound (in MiB) for this call and for later refreshes. Errors as
  * moara_create_state's validation. */

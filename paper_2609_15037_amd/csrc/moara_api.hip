@@ -241,23 +241,20 @@ bool refresh_v_ok(const moara_config& c, int64_t m, int64_t n, int side, int32_t
   return n % 32 == 0;
 }
 
-// Bytes of one matrix in the state's block: what the state holds, and, in *pad_ws, the step
-// workspace of a padded matrix (one on the large-tile path by its padding only: V, and the
-// panels' padding of N, Pop and Ptop).
+// Bytes of one matrix in the state's block (the allocations of moara_create_state).
 size_t mat_state_bytes(const moara_config& c, int64_t m, int64_t n, int side, int64_t s, int64_t L, int64_t k,
-                       int32_t r, size_t* pad_ws) {
+                       int32_t r) {
   const int ob = elem_bytes(c.operand_dtype);
-  const bool vp = vpath_shape_ok(c, m, n, side, r), own = refresh_v_ok(c, m, n, side, r);
+  const bool vp = vpath_shape_ok(c, m, n, side, r);
   const int64_t sp = vp ? pad32(s) : s, rp = vp ? pad32(r) : r, ldr = vp ? (r + 3) / 4 * 4 : r;
-  size_t b = 0, ops = 0, ops_pad = 0;
-  b += align_up(4 * m * k) * 4;          // inv, dM, mag1, mag2
+  size_t b = 0;
+  if (vp) b += align_up(2 * (size_t)L * sp);                         // V
+  b += align_up(4 * m * k) * 4;                                      // inv, dM, mag1, mag2
   b += align_up((size_t)elem_bytes(c.moment_dtype) * L * ldr) * 2;   // exp1, exp2
-  b += align_up(4 * s * r);              // P32
-  ops = align_up((size_t)ob * L * r) + 2 * align_up((size_t)ob * s * r);                                // N, Pop, Ptop
-  ops_pad = align_up((size_t)ob * L * rp) + align_up((size_t)ob * s * rp) + align_up((size_t)ob * r * sp);
-  const size_t v = vp ? align_up(2 * (size_t)L * sp) : 0;
-  if (pad_ws) *pad_ws = (own ? 0 : v) + (ops_pad - ops);
-  return b + ops + (own ? v : 0);
+  b += align_up((size_t)ob * L * rp);                                // N
+  b += align_up(4 * s * r);                                          // P32
+  b += align_up((size_t)ob * s * rp) + align_up((size_t)ob * r * sp);   // Pop, Ptop
+  return b;
 }
 
 // bf: the matrix runs its early subspace iterations on the bf16 V (other orientation
@@ -1564,18 +1561,16 @@ int moara_state_bytes(const moara_config* cfg, const moara_matrix_desc* descs, i
   int rc = validate_all(cfg, descs, n, &ranks, &sides);
   if (rc) return rc;
   if (!out_state_bytes) return fail(MOARA_E_ARG, "out_state_bytes is NULL");
-  size_t tot = 0, ref = 0, pad = 0;
+  size_t tot = 0, ref = 0;
   for (int i = 0; i < n; ++i) {
     const Layout l = layout_of(descs[i], sides[i], cfg->block_size);
-    size_t pad_ws = 0;
-    tot += mat_state_bytes(*cfg, descs[i].rows, descs[i].cols, sides[i], l.s, l.L, l.k, ranks[i], &pad_ws);
-    pad += pad_ws;
+    tot += mat_state_bytes(*cfg, descs[i].rows, descs[i].cols, sides[i], l.s, l.L, l.k, ranks[i]);
     ref += mat_refresh_bytes(l.s, l.L, subspace_width(*cfg, l.s, ranks[i]), ranks[i],
                              refresh_v_ok(*cfg, descs[i].rows, descs[i].cols, sides[i], ranks[i]));
   }
   tot += align_up(16 * (size_t)n);   // refresh records
   *out_state_bytes = (int64_t)tot;
-  if (out_refresh_workspace_bytes) *out_refresh_workspace_bytes = (int64_t)(std::min(ref, refresh_budget() + ref / (size_t)n) + pad);
+  if (out_refresh_workspace_bytes) *out_refresh_workspace_bytes = (int64_t)std::min(ref, refresh_budget() + ref / (size_t)n);
   return MOARA_OK;
 }
 
@@ -1621,9 +1616,7 @@ int moara_create_state(const moara_config* cfg, const moara_matrix_desc* descs, 
     h.sp = h.vpath ? pad32(h.s) : h.s;
     h.rp = h.vpath ? pad32(h.r) : h.r;
     h.ldr = h.vpath ? (h.r + 3) / 4 * 4 : h.r;
-    size_t pad_ws = 0;
-    tot += mat_state_bytes(*cfg, h.m, h.n, h.side, h.s, h.L, h.k, h.r, &pad_ws);
-    tot += pad_ws;
+    tot += mat_state_bytes(*cfg, h.m, h.n, h.side, h.s, h.L, h.k, h.r);
   }
   tot += align_up(16 * (size_t)n);   // refresh records
   if (hipMalloc(&st->block, tot) != hipSuccess) { free_state(st); return fail(MOARA_E_OOM, "state of %zu bytes", tot); }
