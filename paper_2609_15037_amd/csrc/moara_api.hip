@@ -230,7 +230,7 @@ bool vpath_shape_ok(const moara_config& c, int64_t m, int64_t n, int side, int32
   }
   const int64_t s = side == MOARA_SIDE_LEFT ? m : n, L = side == MOARA_SIDE_LEFT ? n : m;
   const int64_t lim = 0x7FFFFFFFLL;
-  return 2 * L * pad32(s) <= lim && 4 * L * pad32(r) <= lim && 2 * s * pad32(r) <= lim && 2 * m * n <= lim;
+  return 2 * L * pad32(s) <= lim && 2 * L * pad32(r) <= lim && 2 * s * pad32(r) <= lim && 2 * m * n <= lim;
 }
 // Of those, the matrices whose projector refresh may iterate on the bf16 V (given an aligned
 // gradient); the others' iterations are fp32 products on G, as their results have always been.

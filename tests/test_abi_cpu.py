@@ -180,6 +180,18 @@ def test_state_bytes_counts_fp32_moments_projector_copies_and_v_workspace():
     assert sbm == sb - sum(2 * al(4 * max(m, n) * 64) - 2 * al(2 * max(m, n) * 64) for m, n in shapes)
 
 
+def test_v_workspace_reaches_to_the_operands_own_extents():
+    """V is kept up to 2^31 bytes per bf16 operand, whatever the moments' bytes (here 4 L r > 2^31)."""
+    _lib()
+    m, n, r = 530000, 1024, 1024
+    cfg = M.moara_default_config(block_size=64, operand_dtype=M.MOARA_BF16)
+    sb, _ = M.moara_state_bytes(cfg, M.make_descs([(m, n, M.MOARA_UP, r)]))
+    al = lambda x: (x + 255) // 256 * 256
+    assert 4 * m * r > 2 ** 31 > 2 * m * n
+    assert sb == (4 * al(4 * m * (n // 64)) + 2 * al(4 * m * r) + al(2 * m * r) + al(4 * n * r) + 2 * al(2 * n * r) +
+                  al(2 * m * n) + al(16))
+
+
 def test_default_config_keeps_fp32_direction_moments():
     _lib()
     assert M.moara_default_config().moment_dtype == M.MOARA_F32

@@ -32,6 +32,38 @@ def test_padded_operands_and_unaligned_buffers(decompose, misalign):
     step_parity(c, 2, misalign=misalign)
 
 
+def test_moments_beyond_two_gib_on_the_large_tile_path():
+    """A tall matrix whose fp32 moments pass 2^31 bytes (its bf16 operands do not): one step's first
+    moment and weights on rows from its start, middle and end against the oracle (a RIGHT matrix's
+    rows are independent given P)."""
+    import dataclasses
+    import numpy as np
+    import torch
+    from oracle import moara_oracle as O
+    from paper_2609_15037_amd import moara as M
+    from tests.harness import TOL_BF16, compare, gpu_state, oracle_cfg, rng, to_np
+    m, n, r = 530000, 1024, 1024
+    c = Case(shapes=[(m, n, WL.UP)], ranks=[r], block_size=64, operand_dtype="bf16", weight_dtype="bf16")
+    rows = torch.cat([torch.arange(400), torch.arange(m // 2, m // 2 + 300), torch.arange(m - 400, m)])
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    G = torch.randn(m, n, device="cuda", generator=gen) * 1e-3
+    W = (torch.randn(m, n, device="cuda", generator=gen) * 0.02).bfloat16()
+    P = O.round_f32(np.linalg.qr(rng(8, 1).standard_normal((n, r)))[0])
+    st = gpu_state(c)
+    M.moara_set_tensor(st, 0, M.MOARA_T_P, P)
+    Gs, Ws = to_np(G[rows.cuda()]), to_np(W[rows.cuda()])
+    M.moara_step(st, [W], [G], lr=c.lr)
+    torch.cuda.synchronize()
+    ocfg = oracle_cfg(dataclasses.replace(c, shapes=[(len(rows), n, WL.UP)]), 0)
+    ost = O.init_state(len(rows), n, ocfg)
+    assert ost.side == O.RIGHT
+    ost.P = P
+    Wo = O.step(Ws, Gs, ost, ocfg, c.lr)
+    report = {}
+    compare("exp_avg", M.moara_get_tensor(st, 0, M.MOARA_T_EXP_AVG)[rows.numpy()], ost.exp_avg, TOL_BF16, report)
+    compare("W", to_np(W[rows.cuda()]), Wo, TOL_BF16, report)
+
+
 # the one-pass decomposition and projection: tiles of 64 (RIGHT) and 128 (LEFT) rows, K chunks of
 # 128 and 64 and panels of 32, one past and one short of each; ranks at the edges of its 32-column
 # blocks and of its range; unaligned rows (n % 4 != 0) beside aligned ones
