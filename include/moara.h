@@ -171,8 +171,9 @@ int moara_resolve_matrix(const moara_config* cfg, const moara_matrix_desc* desc,
  * it is sized per refresh batch: a refresh works through its matrices in chunks
  * of at most 128 GiB of workspace, so the figure is the smaller of the whole
  * batch's need and that bound plus the average matrix's share). With bf16
- * operands the first figure holds a direction workspace of 2 m n bytes per matrix and
- * the padding of the operands to whole 32-wide panels. The environment
+ * operands the first figure holds a direction workspace of 2 m n bytes per matrix (none
+ * with decompose = 0 and every rank up to 256) and the padding of the operands to whole
+ * 32-wide panels. The environment
  * variable MOARA_REFRESH_CHUNK_MIB, when set to a positive integer, replaces the
  * bound (in MiB) for this call and for later refreshes. Errors as
  * moara_create_state's validation. */

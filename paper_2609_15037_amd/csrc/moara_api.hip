@@ -87,7 +87,7 @@ struct MatHost {
   bool vpath = false;    // large-tile path: the decomposition writes V in bf16, and V, Ptop (K = s),
                          // Pop and N (K = r) are in the blocked layout, K padded with zeros to 32
   bool vref = false;     // ... and the refresh may iterate on V (no padding, see refresh_v_ok)
-  void* V = nullptr;     // L x s bf16 direction workspace
+  void* V = nullptr;     // L x s bf16 direction workspace (vpath; null where needs_v says so)
   int64_t sp = 0, rp = 0;   // s and r rounded up to 32 (vpath), else s and r
   int64_t ldr = 0;       // row stride of exp1 / exp2: r, rounded up to 4 on the large-tile path
 };
@@ -241,14 +241,29 @@ bool refresh_v_ok(const moara_config& c, int64_t m, int64_t n, int side, int32_t
   return n % 32 == 0;
 }
 
+// Which matrices of a state need the workspace V: those on the large-tile path, except where it
+// would never be written. Without the decomposition no kernel but the projection reads V, and a
+// state whose matrices all fit the one-pass kernel has no step that takes another.
+std::vector<char> needs_v(const moara_config& c, const moara_matrix_desc* descs, int n,
+                          const std::vector<int32_t>& ranks, const std::vector<int32_t>& sides) {
+  std::vector<char> v(n);
+  bool all_fit = !c.decompose;
+  for (int i = 0; i < n; ++i) {
+    v[i] = vpath_shape_ok(c, descs[i].rows, descs[i].cols, sides[i], ranks[i]);
+    all_fit = all_fit && v[i] && decproj_fits(descs[i].rows, descs[i].cols, ranks[i], c.block_size, false);
+  }
+  if (all_fit) std::fill(v.begin(), v.end(), 0);
+  return v;
+}
+
 // Bytes of one matrix in the state's block (the allocations of moara_create_state).
 size_t mat_state_bytes(const moara_config& c, int64_t m, int64_t n, int side, int64_t s, int64_t L, int64_t k,
-                       int32_t r) {
+                       int32_t r, bool with_v) {
   const int ob = elem_bytes(c.operand_dtype);
   const bool vp = vpath_shape_ok(c, m, n, side, r);
   const int64_t sp = vp ? pad32(s) : s, rp = vp ? pad32(r) : r, ldr = vp ? (r + 3) / 4 * 4 : r;
   size_t b = 0;
-  if (vp) b += align_up(2 * (size_t)L * sp);                         // V
+  if (with_v) b += align_up(2 * (size_t)L * sp);                     // V
   b += align_up(4 * m * k) * 4;                                      // inv, dM, mag1, mag2
   b += align_up((size_t)elem_bytes(c.moment_dtype) * L * ldr) * 2;   // exp1, exp2
   b += align_up((size_t)ob * L * rp);                                // N
@@ -1562,9 +1577,10 @@ int moara_state_bytes(const moara_config* cfg, const moara_matrix_desc* descs, i
   if (rc) return rc;
   if (!out_state_bytes) return fail(MOARA_E_ARG, "out_state_bytes is NULL");
   size_t tot = 0, ref = 0;
+  const std::vector<char> with_v = needs_v(*cfg, descs, n, ranks, sides);
   for (int i = 0; i < n; ++i) {
     const Layout l = layout_of(descs[i], sides[i], cfg->block_size);
-    tot += mat_state_bytes(*cfg, descs[i].rows, descs[i].cols, sides[i], l.s, l.L, l.k, ranks[i]);
+    tot += mat_state_bytes(*cfg, descs[i].rows, descs[i].cols, sides[i], l.s, l.L, l.k, ranks[i], with_v[i]);
     ref += mat_refresh_bytes(l.s, l.L, subspace_width(*cfg, l.s, ranks[i]), ranks[i],
                              refresh_v_ok(*cfg, descs[i].rows, descs[i].cols, sides[i], ranks[i]));
   }
@@ -1606,6 +1622,7 @@ int moara_create_state(const moara_config* cfg, const moara_matrix_desc* descs, 
   if ((rc = scratch_init(st->device))) { free_state(st); return rc; }   // this GPU's scratch address, once
   st->mats.resize(n);
   size_t tot = 0;
+  const std::vector<char> with_v = needs_v(*cfg, descs, n, ranks, sides);
   for (int i = 0; i < n; ++i) {
     const Layout l = layout_of(descs[i], sides[i], cfg->block_size);
     MatHost& h = st->mats[i];
@@ -1616,7 +1633,7 @@ int moara_create_state(const moara_config* cfg, const moara_matrix_desc* descs, 
     h.sp = h.vpath ? pad32(h.s) : h.s;
     h.rp = h.vpath ? pad32(h.r) : h.r;
     h.ldr = h.vpath ? (h.r + 3) / 4 * 4 : h.r;
-    tot += mat_state_bytes(*cfg, h.m, h.n, h.side, h.s, h.L, h.k, h.r);
+    tot += mat_state_bytes(*cfg, h.m, h.n, h.side, h.s, h.L, h.k, h.r, with_v[i]);
   }
   tot += align_up(16 * (size_t)n);   // refresh records
   if (hipMalloc(&st->block, tot) != hipSuccess) { free_state(st); return fail(MOARA_E_OOM, "state of %zu bytes", tot); }
@@ -1624,7 +1641,8 @@ int moara_create_state(const moara_config* cfg, const moara_matrix_desc* descs, 
   const int ob = elem_bytes(cfg->operand_dtype);
   char* p = st->block;
   auto take = [&](size_t b) { char* q = p; p += align_up(b); return q; };
-  for (auto& h : st->mats) {
+  for (int i = 0; i < n; ++i) {
+    MatHost& h = st->mats[i];
     h.inv = (float*)take(4 * h.m * h.k);
     h.dM = (float*)take(4 * h.m * h.k);
     h.mag1 = (float*)take(4 * h.m * h.k);
@@ -1635,7 +1653,7 @@ int moara_create_state(const moara_config* cfg, const moara_matrix_desc* descs, 
     h.P32 = (float*)take(4 * h.s * h.r);
     h.Pop = take((size_t)ob * h.s * h.rp);
     h.Ptop = take((size_t)ob * h.r * h.sp);
-    if (h.vpath) h.V = take(2 * (size_t)h.L * h.sp);
+    if (with_v[i]) h.V = take(2 * (size_t)h.L * h.sp);
   }
   st->info_dev = (int32_t*)take(16 * (size_t)n);
   st->arena_bytes = 2 * align_up(sizeof(MatDev) * n) + 6 * ALIGN + align_up(sizeof(FusedProb) * n) + 5 * align_up(sizeof(GemmProb) * n) + 8 * ALIGN;
@@ -1847,17 +1865,19 @@ static int step_impl(moara_state* st, void* const* weights, const void* const* g
     refv[i] = st->mats[i].vref && (((uintptr_t)grads[i] & 15) == 0);
   }
   // which matrices take the fused decomposition and projection: those it fits, except where a
-  // refresh that is due needs what the decomposition kernel writes (V, or 1 / (M + eps_d)), and
-  // except a handful beside larger matrices: fewer tiles than the 512 that run at once cost a
-  // launch of their own (four 512 x 3584 matrices 160 us), and next to nothing in the others'
+  // refresh that is due needs what the decomposition kernel writes (V, or 1 / (M + eps_d); without
+  // the decomposition it reads G, and runs before the projection either way), and except a handful
+  // beside larger matrices: fewer tiles than the 512 that run at once cost a launch of their own
+  // (four 512 x 3584 matrices 160 us), and next to nothing in the others'
   std::vector<int> split, fused;
+  std::vector<char> due(st->n, 0);
   {
-    std::vector<char> due(st->n, 0);
     for (int i : need) due[i] = 1;
+    const bool dec = st->cfg.decompose != 0;
     uint32_t ftiles = 0;
     for (int i : idx) {
       const MatHost& h = st->mats[i];
-      const bool f = h.vpath && !due[i] && decproj_fits(h.m, h.n, h.r, st->cfg.block_size, st->cfg.decompose != 0);
+      const bool f = h.vpath && !(dec && due[i]) && decproj_fits(h.m, h.n, h.r, st->cfg.block_size, dec);
       (f ? fused : split).push_back(i);
       if (f) ftiles += decproj_tiles(h.side, h.L);
     }
@@ -1869,11 +1889,11 @@ static int step_impl(moara_state* st, void* const* weights, const void* const* g
   }
   // bf16 gradients: the fused kernel reads whole 4-column groups of them itself (2 bytes per element
   // instead of the 2 + 4 + 4 of a copy: 24 layers of Qwen2.5-350M shapes 1474 -> 805 us a step);
-  // every other kernel takes the fp32 copy
+  // every other kernel, the refresh's among them, takes the fp32 copy
   std::vector<char> direct(st->n, 0);
   if (grad_bf16) {
     for (int i : fused) {
-      direct[i] = grad_bf16[i] && (st->mats[i].n & 3) == 0 && ((uintptr_t)grads_in[i] & 7) == 0;
+      direct[i] = grad_bf16[i] && !due[i] && (st->mats[i].n & 3) == 0 && ((uintptr_t)grads_in[i] & 7) == 0;
       if (direct[i]) g32[i] = grads_in[i];
     }
     CastList cl{};

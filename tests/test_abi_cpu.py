@@ -180,6 +180,22 @@ def test_state_bytes_counts_fp32_moments_projector_copies_and_v_workspace():
     assert sbm == sb - sum(2 * al(4 * max(m, n) * 64) - 2 * al(2 * max(m, n) * 64) for m, n in shapes)
 
 
+def test_no_v_workspace_without_the_decomposition_at_ranks_up_to_256():
+    """decompose = 0 and every matrix in the one-pass kernel's range: nothing ever writes V."""
+    _lib()
+    al = lambda x: (x + 255) // 256 * 256
+    for ranks, v in (((64, 256), False), ((64, 288), True)):
+        cfg = M.moara_default_config(block_size=64, operand_dtype=M.MOARA_BF16, decompose=0)
+        shapes = [(1024, 2048), (640, 512)]
+        sb, _ = M.moara_state_bytes(cfg, M.make_descs([(m, n, 4, r) for (m, n), r in zip(shapes, ranks)]))
+        exp = al(16 * 2)
+        for (m, n), r in zip(shapes, ranks):
+            s, L = min(m, n), max(m, n)
+            exp += 4 * al(4 * m * (n // 64)) + 2 * al(4 * L * r) + al(2 * L * r) + al(4 * s * r) + 2 * al(2 * s * r)
+            exp += al(2 * m * n) if v else 0
+        assert sb == exp, (ranks, sb, exp)
+
+
 def test_v_workspace_reaches_to_the_operands_own_extents():
     """V is kept up to 2^31 bytes per bf16 operand, whatever the moments' bytes (here 4 L r > 2^31)."""
     _lib()

@@ -137,7 +137,30 @@ def test_one_pass_and_two_pass_projection_are_bit_identical():
             assert np.array_equal(x, y), f"matrix {i}: a moment differs"
 
 
-@pytest.mark.parametrize("case", ["fused", "two_pass", "fp32_operands", "no_decompose", "refresh_due", "misaligned"])
+@pytest.mark.parametrize("two_pass", [False, True])
+def test_refresh_in_the_step_without_the_decomposition(two_pass):
+    """decompose = 0: a step whose refresh is due gives the bits of an explicit refresh and a step,
+    with the projection in the one-pass kernel (a state that has no V) and in the two-pass ones."""
+    import torch
+    from paper_2609_15037_amd import moara as M
+    from tests.harness import assert_same_state, explicit_refresh, gpu_state, rng, to_dev
+    extra = [(300, 320, WL.V)] if two_pass else []
+    c = Case(shapes=FUSED + extra, ranks=FUSED_RANKS + [257] * len(extra), block_size=64, operand_dtype="bf16",
+             weight_dtype="bf16", decompose=False, refresh_iters=6)
+    n = len(c.shapes)
+    A, B = gpu_state(c, refresh_interval=2), gpu_state(c)
+    WA, WB = [[to_dev(0.02 * rng(9, 1, i).standard_normal(s[:2]), "bf16") for i, s in enumerate(c.shapes)] for _ in "AB"]
+    for t in range(3):
+        G = [to_dev(rng(9, 2, t, i).standard_normal(s[:2]), "f32") for i, s in enumerate(c.shapes)]
+        explicit_refresh(M, B, G, [t % 2 == 0] * n)
+        M.moara_step(A, WA, G, lr=1e-2)
+        M.moara_step(B, WB, G, lr=1e-2)
+        torch.cuda.synchronize()
+        assert_same_state(M, A, B, WA, WB, range(n), f"step {t}:")
+
+
+@pytest.mark.parametrize("case", ["fused", "two_pass", "fp32_operands", "no_decompose", "refresh_due", "refresh_due_no_decompose",
+                                  "misaligned"])
 def test_bf16_gradients_step_as_their_fp32_copies(case):
     """moara_step_mixed on bf16 gradients gives the bits of moara_step on the converted ones, on every
     route: read by the one-pass kernel (n % 4 == 0 and 8-byte aligned), or converted first (other
@@ -151,11 +174,11 @@ def test_bf16_gradients_step_as_their_fp32_copies(case):
         shapes, ranks = shapes + [(300, 320, WL.V)], ranks + [257]
     operand = "f32" if case == "fp32_operands" else "bf16"
     c = Case(shapes=shapes, ranks=ranks, block_size=64, operand_dtype=operand, weight_dtype="bf16", weight_std=0.02,
-             moment_dtype="bf16" if operand == "bf16" else "f32", decompose=case != "no_decompose")
+             moment_dtype="bf16" if operand == "bf16" else "f32", decompose="no_decompose" not in case)
     active = [i != 3 for i in range(len(shapes))]
     out = []
     for mixed in (False, True):
-        st = gpu_state(c, refresh_interval=2 if case == "refresh_due" else 0)
+        st = gpu_state(c, refresh_interval=2 if "refresh_due" in case else 0)
         W, G, B32 = [], [], []
         for i, ((m, n, _), r) in enumerate(zip(c.shapes, c.ranks)):
             W.append(to_dev(0.02 * rng(6, 1, i).standard_normal((m, n)), "bf16"))
