@@ -59,20 +59,36 @@ def parse():
 
 
 def v_path(wl, m, operand: str) -> bool:
-    """Whether the library materialises V in bf16 for this matrix (the large-tile projection
-    path): the shape rule of the library's state layout."""
+    """Whether the matrix is on the library's large-tile path (the shape rule of its state
+    layout: bf16 operands padded to 32-wide panels): its step either materialises V in bf16
+    or takes the one-pass kernel (one_pass)."""
     if operand != "bf16":
         return False
     B = wl.block_size
     if B < 4 or B > 256 or (B & (B - 1)):
         return False
-    r = wl.rank_of(m)
-    if m.cols % 4 or r % 4:
+    if m.rows > m.cols and -(-m.cols // B) > 512:
         return False
-    k = -(-m.cols // B)
-    if m.rows <= m.cols:
-        return k <= 160 and m.rows % 32 == 0
-    return k <= 512 and m.cols % 32 == 0
+    r = wl.rank_of(m)
+    s, L = min(m.rows, m.cols), max(m.rows, m.cols)
+    up = lambda x: -(-x // 32) * 32
+    return max(2 * L * up(s), 2 * L * up(r), 2 * s * up(r), 2 * m.rows * m.cols) < 2 ** 31
+
+
+def one_pass(wl, operand: str, mask=None):
+    """Which matrices of a step (those in `mask`, all if None) run the decomposition and the
+    projection in one kernel: rank up to 256, blocks of 32 to 128 columns, and, beside other
+    matrices, at least 512 tiles of 64 (RIGHT) or 128 (LEFT) rows together."""
+    fits, tiles, others = [], 0, False
+    for i, m in enumerate(wl.matrices):
+        on = mask is None or bool(mask[i])
+        f = (on and v_path(wl, m, operand) and wl.rank_of(m) <= 256 and min(m.rows, m.cols) >= 32
+             and wl.block_size in (32, 64, 128) and 4 * m.rows * m.cols < 2 ** 31)
+        fits.append(f)
+        others = others or (on and not f)
+        if f:
+            tiles += -(-m.cols // 128) if m.rows <= m.cols else -(-m.rows // 64)
+    return fits if not others or tiles >= 512 else [False] * len(fits)
 
 
 def algorithmic_cost(wl, operand: str, weight_bytes: int, mask=None, moment_bytes: int = 4):
@@ -80,6 +96,7 @@ def algorithmic_cost(wl, operand: str, weight_bytes: int, mask=None, moment_byte
     move or compute, given its inputs and outputs), over the matrices in `mask` (all if None)."""
     ob = 2 if operand == "bf16" else 4
     cost = {"decompose": [0, 0], "project": [0, 0], "backproject": [0, 0]}
+    fused = one_pass(wl, operand, mask)
     for i, m in enumerate(wl.matrices):
         if mask is not None and not mask[i]:
             continue
@@ -89,12 +106,13 @@ def algorithmic_cost(wl, operand: str, weight_bytes: int, mask=None, moment_byte
         k = -(-N // wl.block_size)
         vp = v_path(wl, m, operand)
         # decompose + Optimizer_M: read G; write inv and dM; read+write two magnitude moments;
-        # write V in bf16 on the large-tile path
-        cost["decompose"][0] += 4 * M * N + 4 * M * k * 6 + (2 * M * N if vp else 0)
-        # projection + Optimizer_V: read V (or G and inv), read P, read+write the two direction
-        # moments (fp32 or bf16), write N
-        cost["project"][0] += ((2 * M * N if vp else 4 * M * N + 4 * M * k) + ob * s * r + 4 * moment_bytes * L * r
-                               + ob * L * r)
+        # write V in bf16 on the large-tile path. One-pass kernel: Optimizer_M alone, which reads
+        # the block sums (where the others write inv)
+        cost["decompose"][0] += 4 * M * k * 6 + (0 if fused[i] else 4 * M * N + (2 * M * N if vp else 0))
+        # projection + Optimizer_V: read V (or G and inv; one-pass kernel: read G, write the block
+        # sums), read P, read+write the two direction moments (fp32 or bf16), write N
+        cost["project"][0] += ((2 * M * N if vp and not fused[i] else 4 * M * N + 4 * M * k) + ob * s * r
+                               + 4 * moment_bytes * L * r + ob * L * r)
         cost["project"][1] += 2 * M * N * r
         # back-projection + update: read N and P, read dM, read+write W
         cost["backproject"][0] += ob * L * r + ob * s * r + 4 * M * k + 2 * weight_bytes * M * N

@@ -326,7 +326,10 @@ int moara_refresh_info(moara_state* st, int32_t mat, int32_t* out_sweeps, int32_
 /* Per-kernel timing for measurement: when enabled, moara_step and
  * moara_refresh_projector bracket each kernel launch with HIP events on the
  * caller's stream and accumulate the elapsed time per kernel id when
- * moara_kernel_stats is called (which synchronises the stream). */
+ * moara_kernel_stats is called (which synchronises the stream). Matrices whose
+ * decomposition and projection are one kernel (bf16 operands, rank up to 256) run it
+ * under MOARA_KERN_PROJECT and Optimizer_M in a bracket of its own under
+ * MOARA_KERN_DECOMPOSE: a step with both kinds of matrices counts two brackets there. */
 enum {
   MOARA_KERN_DECOMPOSE = 0, /* decompose + Optimizer_M                 */
   MOARA_KERN_PROJECT = 1,   /* projection GEMM + Optimizer_V epilogue  */

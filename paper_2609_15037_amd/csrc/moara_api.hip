@@ -507,9 +507,8 @@ DecPlan plan_decompose(const moara_state* st, const std::vector<int>& idx, const
   return P;
 }
 
-// timed_empty: record the (empty) timing scope also when every matrix took the fused kernel
-int launch_plan(moara_state* st, const DecPlan& P, bool adam_m, hipStream_t stream, bool timed_empty = false) {
-  if (P.md[0].empty() && P.md[1].empty() && P.md[2].empty() && P.md[3].empty() && !timed_empty) return MOARA_OK;
+int launch_plan(moara_state* st, const DecPlan& P, bool adam_m, hipStream_t stream) {
+  if (P.md[0].empty() && P.md[1].empty() && P.md[2].empty() && P.md[3].empty()) return MOARA_OK;
   TimerScope ts(st, MOARA_KERN_DECOMPOSE, stream);
   for (int q = 3; q >= 0; --q) {
     if (P.md[q].empty()) continue;
@@ -681,22 +680,25 @@ int launch_plan(moara_state* st, const GemmPlan& P, const FusedPlan& F, float lr
   const int kind = st->cfg.operand_dtype == MOARA_BF16 ? KIND_BF16 : KIND_F32;
   auto dev = [&](size_t off) { return (const GemmProb*)(st->dev_arena + off); };
   const GemmUniform u = make_uniform(st, lr);
+  const bool dec = st->cfg.decompose != 0;
+  auto fdev = [&](int q) { return (const FusedProb*)(st->dev_arena + F.off[q]); };
   {
     TimerScope ts(st, MOARA_KERN_PROJECT, stream);
-    for (int q = 0; q < 3; ++q) {
-      if (F.p[q].empty()) continue;
-      const FusedProb* fp = (const FusedProb*)(st->dev_arena + F.off[q]);
-      const bool dec = st->cfg.decompose != 0;
-      GemmUniform uf = u;
-      uf.decomp_eps = st->cfg.decomp_eps;
-      HIP_TRY(launch_decproj(fp, (int)F.p[q].size(), F.tiles[q], uf, q != 1, q == 2, dec, stream));
-      if (dec) HIP_TRY(launch_opt_m(fp, (int)F.p[q].size(), F.tiles_m[q], uf, stream));
-    }
+    GemmUniform uf = u;
+    uf.decomp_eps = st->cfg.decomp_eps;
+    for (int q = 0; q < 3; ++q)
+      if (!F.p[q].empty())
+        HIP_TRY(launch_decproj(fdev(q), (int)F.p[q].size(), F.tiles[q], uf, q != 1, q == 2, dec, stream));
     if (!P.pnt.empty()) HIP_TRY(launch_gemm_nt(EP_ADAM, dev(P.opn), P.pnt, P.tpn, u, stream));
     if (!P.right.empty())
       HIP_TRY(launch_gemm(kind, A_G_ROW, B_KC, EP_ADAM, dev(P.orr), P.right, P.tr, u, stream, P.tir));
     if (!P.left.empty())
       HIP_TRY(launch_gemm(kind, A_G_TRANS, B_KC, EP_ADAM, dev(P.ol), P.left, P.tl, u, stream, P.til));
+  }
+  if (dec && !(F.p[0].empty() && F.p[1].empty() && F.p[2].empty())) {
+    TimerScope ts(st, MOARA_KERN_DECOMPOSE, stream);
+    for (int q = 0; q < 3; ++q)
+      if (!F.p[q].empty()) HIP_TRY(launch_opt_m(fdev(q), (int)F.p[q].size(), F.tiles_m[q], u, stream));
   }
   {
     TimerScope ts(st, MOARA_KERN_BACKPROJ, stream);
@@ -1923,7 +1925,7 @@ static int step_impl(moara_state* st, void* const* weights, const void* const* g
   if ((rc = begin_stage(st, sg)) || (rc = dec.stage(sg)) || (rc = zero.stage(sg)) || (rc = fu.stage(sg)) ||
       (rc = gemm.stage(sg)) || (rc = end_stage(st, sg, hs)))
     return rc;
-  if ((rc = launch_plan(st, dec, st->cfg.decompose != 0, hs, st->cfg.decompose && !fused.empty()))) return rc;
+  if ((rc = launch_plan(st, dec, st->cfg.decompose != 0, hs))) return rc;
   if (!need.empty() && (rc = refresh_in_chunks(st, need, grads, hs, refv))) return rc;
   if ((rc = launch_plan(st, zero, zidx, hs))) return rc;
   if ((rc = launch_plan(st, gemm, fu, lr, hs))) return rc;

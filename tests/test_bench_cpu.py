@@ -70,6 +70,24 @@ def test_step_accounting_prices_the_direction_moments_by_their_storage(operand):
     assert m4 - m2 == 8 * r * L and f4 == f2
 
 
+def test_step_accounting_follows_the_one_pass_kernel():
+    # rank up to 256: G is read by the projection's kernel, Optimizer_M reads the block sums, V is
+    # never written; rank 257 to 1024: G read and V written by the decomposition, V read back
+    for rank, fused in ((256, True), (288, False)):
+        wl = dataclasses.replace(_one_matrix(300, 1000, rank), block_size=64)
+        M, N, k = 300, 1000, 16
+        c = bench.algorithmic_cost(wl, "bf16", 2, moment_bytes=2)
+        base = 2 * M * rank + 8 * N * rank + 2 * N * rank
+        assert c["decompose"][0] == 24 * M * k + (0 if fused else 6 * M * N)
+        assert c["project"][0] == base + (4 * M * N + 4 * M * k if fused else 2 * M * N)
+    # a handful of small-rank matrices beside a larger one, and enough of them
+    wl = WL.WORKLOADS["qwen2_7b"]
+    for layers, kv_fused in ((1, False), (28, True)):
+        sub = WL.subset(wl, list(range(layers)))
+        got = {sub.rank_of(m) for m, f in zip(sub.matrices, bench.one_pass(sub, "bf16")) if f}
+        assert got == ({r for r in wl.rank_table if 0 < r <= 256} if kv_fused else set()), (layers, got)
+
+
 def test_measured_traffic_only_for_the_profiled_sources_and_workload(tmp_path, monkeypatch):
     """The roofline's measured HBM traffic comes from the committed counter summary only
     while the kernel sources hash to the value recorded there and the workload is the
