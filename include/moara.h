@@ -239,8 +239,8 @@ int moara_step_mixed(moara_state* st, void* const* weights, const void* const* g
 
 /* moara_step for callers that cannot allocate device memory (allocation-free serving or
  * training loops, harnesses that forbid hipMalloc). It allocates nothing, but it is not
- * made for stream capture: like moara_step it stages each launch's descriptors through
- * the state's pinned host ring (a host-to-device copy on `stream`, and a host wait before
+ * made for stream capture: like moara_step it stages the call's descriptors through
+ * the state's pinned host ring (read by one kernel on `stream`, and a host wait before
  * a ring slot is reused), so a graph captured from it would not replay correctly.
  * Same arguments, semantics and results as moara_step, bit for bit, but it calls no
  * hipMalloc, hipFree, hipHostMalloc or other device/pinned allocator: the step's

@@ -22,7 +22,7 @@ struct MatDev {
   int32_t r;           // rank
   int32_t side;        // SIDE_LEFT (P is m x r) or SIDE_RIGHT (Q is n x r)
   int32_t L, s;        // L = uncompressed state dim, s = projected dim
-  float* inv;          // m x k: 1 / (M + eps_d)
+  float* inv;          // m x k: 1 / (M + eps_d) (the one-pass kernel leaves block sums of squares here)
   float* dM;           // m x k: Optimizer_M output
   float* mag1;         // m x k: Optimizer_M moments
   float* mag2;

@@ -613,7 +613,7 @@ GemmPlan plan_project_back(const moara_state* st, const std::vector<int>& idx, v
       g.a = h.V; g.lda = h.sp;
       g.b = h.Ptop; g.ldb = h.sp;
       g.c = h.N; g.ldc = h.ldr;
-      g.kp = 1 | 2 | 4;
+      g.kp = 1 | 2;
       g.e1 = (float*)h.exp1; g.e2 = (float*)h.exp2;
       g.bc1 = bc1; g.bc2 = bc2;
       g.a_bytes = (uint32_t)(2 * (size_t)h.L * h.sp);
