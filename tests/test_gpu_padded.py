@@ -105,9 +105,12 @@ def test_padding_stays_zero_when_the_decomposition_epsilon_is_zero(two_pass, eps
     history_parity(c, 2, 330, _grad(c, 330))
 
 
-def test_one_pass_and_two_pass_projection_are_bit_identical():
+@pytest.mark.parametrize("block", [64, 256])
+def test_one_pass_and_two_pass_projection_are_bit_identical(block):
     """A matrix whose rank exceeds the one-pass kernel's range sends a short list of matrices through
-    the two-pass kernels: the same matrices give the same bits with and without it beside them."""
+    the two-pass kernels, and its update through 256-column tiles: the same matrices give the same
+    bits with and without it beside them. Blocks of 256 columns take the two-pass kernels either
+    way, so there only the update's tiles differ."""
     import numpy as np
     import torch
     from paper_2609_15037_amd import moara as M
@@ -116,7 +119,7 @@ def test_one_pass_and_two_pass_projection_are_bit_identical():
     big, rbig = (300, 320, WL.V), 257
     out = []
     for extra in (False, True):
-        c = Case(shapes=shapes + ([big] if extra else []), ranks=ranks + ([rbig] if extra else []), block_size=64,
+        c = Case(shapes=shapes + ([big] if extra else []), ranks=ranks + ([rbig] if extra else []), block_size=block,
                  operand_dtype="bf16", weight_dtype="bf16", weight_std=0.02, moment_dtype="bf16")
         st = gpu_state(c)
         W, G = [], []
@@ -160,11 +163,13 @@ def test_refresh_in_the_step_without_the_decomposition(two_pass):
 
 
 @pytest.mark.parametrize("case", ["fused", "two_pass", "fp32_operands", "no_decompose", "refresh_due", "refresh_due_no_decompose",
-                                  "misaligned"])
+                                  "misaligned", "fused-f32-32", "fused-f32-64", "fused-f32-128", "fused-bf16-32",
+                                  "fused-bf16-128", "many"])
 def test_bf16_gradients_step_as_their_fp32_copies(case):
     """moara_step_mixed on bf16 gradients gives the bits of moara_step on the converted ones, on every
-    route: read by the one-pass kernel (n % 4 == 0 and 8-byte aligned), or converted first (other
-    widths and alignments, larger ranks, fp32 operands, a due refresh); inactive matrices stay."""
+    route: read by the one-pass kernel (n % 4 == 0 and 8-byte aligned; every moment type and block
+    size), or converted first (other widths and alignments, larger ranks, fp32 operands, a due
+    refresh; "many": more buffers than one conversion launch holds); inactive matrices stay."""
     import numpy as np
     import torch
     from paper_2609_15037_amd import moara as M
@@ -172,9 +177,13 @@ def test_bf16_gradients_step_as_their_fp32_copies(case):
     shapes, ranks = list(FUSED), list(FUSED_RANKS)
     if case == "two_pass":
         shapes, ranks = shapes + [(300, 320, WL.V)], ranks + [257]
-    operand = "f32" if case == "fp32_operands" else "bf16"
-    c = Case(shapes=shapes, ranks=ranks, block_size=64, operand_dtype=operand, weight_dtype="bf16", weight_std=0.02,
-             moment_dtype="bf16" if operand == "bf16" else "f32", decompose="no_decompose" not in case)
+    if case == "many":   # 150 buffers, 64 to a launch; counts that are and are not multiples of 8
+        shapes = [(33 + i % 7, 41 + i % 5, WL.Q) for i in range(188)]
+        ranks = [8] * len(shapes)
+    operand = "f32" if case in ("fp32_operands", "many") else "bf16"
+    mom, block = case.split("-")[1:] if case.startswith("fused-") else ("bf16" if operand == "bf16" else "f32", 64)
+    c = Case(shapes=shapes, ranks=ranks, block_size=int(block), operand_dtype=operand, weight_dtype="bf16",
+             weight_std=0.02, moment_dtype=mom, decompose="no_decompose" not in case)
     active = [i != 3 for i in range(len(shapes))]
     out = []
     for mixed in (False, True):
@@ -208,3 +217,35 @@ def test_bf16_gradients_step_as_their_fp32_copies(case):
         assert torch.equal(a[0], b[0]), f"matrix {i}: W differs"
         for x, y in zip(a[1:], b[1:]):
             assert np.array_equal(x, y), f"matrix {i}: a moment or the projector differs"
+
+
+def test_fp32_tiles_of_either_size_give_the_same_bits():
+    """fp32 operands: lists of more than 4096 tiles of 128 x 128 run on those, shorter ones on 64 x 64
+    tiles. Matrices stepped all at once (both projections and the update past the line) and one by one."""
+    import numpy as np
+    import torch
+    from paper_2609_15037_amd import moara as M
+    from tests.harness import assert_same_state, gpu_state, rng, to_dev
+    k = 66
+    shapes, ranks = [(1000, 1024, WL.Q)] * k + [(1152, 1024, WL.GATE)] * k, [1000] * k + [1024] * k
+    c = Case(shapes=shapes, ranks=ranks, block_size=64, weight_std=0.02)
+    assert min(8 * 8, 9 * 8) * k > 4096
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    G = [torch.randn(m, n, device="cuda", generator=gen) for m, n, _ in shapes]
+    out = []
+    for each in (False, True):
+        st = gpu_state(c)
+        gw = torch.Generator(device="cuda").manual_seed(6)
+        W = [0.02 * torch.randn(m, n, device="cuda", generator=gw) for m, n, _ in shapes]
+        for i in range(2 * k):   # any fixed P will do
+            P = np.zeros((min(shapes[i][:2]), ranks[i]), dtype=np.float32)
+            P[np.arange(ranks[i]), np.arange(ranks[i])[::-1]] = 0.75
+            P[0] += 0.01
+            M.moara_set_tensor(st, i, M.MOARA_T_P, P)
+        for one in (range(2 * k) if each else [None]):
+            M.moara_step(st, W, G, lr=1e-2, active=None if one is None else [j == one for j in range(2 * k)])
+        torch.cuda.synchronize()
+        out.append((st, W))
+    (sa, Wa), (sb, Wb) = out
+    assert_same_state(M, sa, sb, Wa, Wb, [0, 1, k - 1, k, 2 * k - 1])
+    assert all(torch.equal(a, b) for a, b in zip(Wa, Wb))
