@@ -72,21 +72,22 @@ __device__ __forceinline__ bf16 f2bf(float x) { return (bf16)x; }   // round to 
 // xcd_remap: each XCD takes one contiguous eighth of the tiles.
 __device__ __forceinline__ uint32_t xcd_remap(uint32_t bid, uint32_t nblk) {
   const uint32_t X = 8;
-  uint32_t xcd = bid % X, idx = bid / X;
-  uint32_t per = nblk / X, rem = nblk % X;
-  return (xcd < rem) ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
+  const uint32_t xcd = bid % X, per = nblk / X, rem = nblk % X;
+  return xcd * per + (xcd < rem ? xcd : rem) + bid / X;
 }
-// xcd_remap_groups: the XCDs take groups of XCD_GROUP tiles in turn, so that each gets a share of
-// every problem in a list (the GEMM lists choose between the two by gemm_xcd_groups). Groups of 32
-// measured the same, of 64 235 instead of 229 ms (refresh of a 7B-shaped layer). The one-pass
-// projection streams the gradient and keeps the eighths (24 layers of 300M shapes 10 us faster).
+// xcd_remap_list: with `groups` the XCDs take groups of XCD_GROUP tiles in turn (what is left past
+// whole rounds in eighths), so that each gets a share of every problem in a list; the GEMM lists
+// choose by gemm_xcd_groups. Groups of 32 measured the same, of 64 235 instead of 229 ms (refresh
+// of a 7B-shaped layer). The one-pass projection streams the gradient and keeps the eighths (24
+// layers of 300M shapes 10 us faster).
 constexpr uint32_t XCD_GROUP = 16;
-__device__ __forceinline__ uint32_t xcd_remap_groups(uint32_t bid, uint32_t nblk) {
+__device__ __forceinline__ uint32_t xcd_remap_list(uint32_t bid, uint32_t nblk, int groups) {
   const uint32_t X = 8, G = XCD_GROUP;
-  const uint32_t full = nblk / (X * G) * (X * G);
-  if (bid >= full) return full + xcd_remap(bid - full, nblk - full);
+  const uint32_t full = groups ? nblk / (X * G) * (X * G) : 0;   // tiles in groups
   const uint32_t i = bid / X;
-  return ((i / G) * X + bid % X) * G + i % G;
+  const uint32_t in_groups = ((i / G) * X + bid % X) * G + i % G;
+  const uint32_t in_eighths = full + xcd_remap(bid - full, nblk - full);   // full: a multiple of X
+  return bid < full ? in_groups : in_eighths;
 }
 
 // Largest i with prefix(i) <= t, prefix read through a member pointer of MatDev.

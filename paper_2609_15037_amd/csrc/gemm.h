@@ -76,14 +76,14 @@ struct GemmProb {
 
 struct GemmUniform {
   int32_t B;            // decomposition block size (A_G_* scaling, EP_UPDATE)
-  int32_t nprob;
+  int32_t nprob;        // (nprob and xcd_groups are what a workgroup needs first: one load)
+  int32_t xcd_groups;   // tiles go round the XCDs in groups, see gemm_xcd_groups (set by the launchers)
   int32_t weight_bf16;  // EP_UPDATE
   float decomp_eps;     // EP_ALIGN
   float beta1, beta2, adam_eps;
   float lr, scale;
   int32_t moment_bf16;  // EP_ADAM: the moments are stored in bf16
   int32_t lgB;          // log2(B) when B is a power of two, else -1 (set by launch_gemm)
-  int32_t xcd_groups;   // tiles go round the XCDs in groups, see gemm_xcd_groups (set by the launchers)
 };
 
 template <int KIND> struct GemmTile;
@@ -141,19 +141,22 @@ uint32_t gemm_tiles_n(int kind, int64_t N);
 hipError_t launch_gemm(int kind, int amode, int bmode, int ep, const GemmProb* probs_dev,
                        const std::vector<GemmProb>& list, uint32_t total_tiles, const GemmUniform& u, hipStream_t st,
                        int tile = 128);
-// How a list's tiles are dealt to the XCDs: in groups (xcd_remap_groups) or in contiguous eighths
+// How a list's tiles are dealt to the XCDs (xcd_remap_list): in groups or in contiguous eighths
 // (xcd_remap). Problems differ in their work per tile (K from 128 to 11008, and an epilogue worth
 // about 256 of K), and with eighths the XCDs that drew the light ones wait for the others; but an
-// eighth shares more operand panels in its L2. gemm_xcd_groups: whether the eighths would give
-// some XCD over 3 % more than its share of the work. The fp32 lists, the projection and the
-// update on 256-column tiles go by it; the update on 128-column tiles and the refresh's
-// large-tile products always take groups. Eighths against groups:
+// eighth shares more operand panels, and the alignment's sums of one problem, in its L2.
+// gemm_xcd_groups: groups where the eighths would give some XCD over 3 % more than its share of the
+// work, and for updates whose tiles have a mean K below 512 (mostly their epilogue's stream of W,
+// which shares nothing). Besides, the refresh's large-tile products and the 64-wide fp32 tiles but
+// the alignment's sums always take groups. Eighths against groups:
 //   uneven  step of two DeepSeek-MoE layers (K = 512 beside 128) 536 -> 502 us, of two
-//           Qwen2-7B-shaped ones 2.81 -> 2.75 ms, alignment of a 7B-shaped layer 7.00 -> 6.53 ms;
-//   even    step of four 7B-shaped layers 4.07 -> 4.12 ms, fp32 products of their refresh 7.6 ->
-//           9.1 ms; but narrow updates, step of 24 layers of 300M shapes 846 -> 835 us, of six
-//           ragged ones 351 -> 341, and refresh products V Z of four 7B-shaped layers 105 -> 103 ms.
-bool gemm_xcd_groups(const std::vector<GemmProb>& list, uint32_t total_tiles);
+//           Qwen2-7B-shaped ones 2.81 -> 2.75 ms;
+//   even    step of four 7B-shaped layers 4.04 -> 4.09 ms, fp32 products of their refresh 7.6 ->
+//           9.1 ms, alignment of four layers d = 1600 2.10 -> 2.31 ms, of 13 layers d = 384 387 -> 475 us;
+//           small-K updates: step of 24 layers of 300M shapes 846 -> 835 us, of 12 layers d = 1216
+//           (K about 300) 899 -> 890; refresh products V Z of four 7B-shaped layers 105 -> 103 ms;
+//           64-wide fp32 tiles: step of 24 layers d = 192 112 -> 110 us.
+bool gemm_xcd_groups(const std::vector<GemmProb>& list, uint32_t total_tiles, int ep);
 // fp32 kind: the tile (128 or 64) a list of problems, laid out for 128 x 128 tiles (`total` of
 // them), is launched with; for 64 the list's prefixes and the total are rewritten.
 // 64 up to 4096 tiles of 128 x 128 (eight rounds of the 512 that run at once): a short list leaves

@@ -634,7 +634,7 @@ __global__ __launch_bounds__(64 * BWM * BWN, 2) void k_gemm_bf16(const GemmProb*
   constexpr int BBM = 64 * BWM, BBN = 64 * BWN;
   __shared__ __attribute__((aligned(16))) bf16 As[2][BBM * BF_LD];
   __shared__ __attribute__((aligned(16))) bf16 Bs[2][BBN * BF_LD];
-  const uint32_t t = U.xcd_groups ? xcd_remap_groups(blockIdx.x, gridDim.x) : xcd_remap(blockIdx.x, gridDim.x);
+  const uint32_t t = xcd_remap_list(blockIdx.x, gridDim.x, U.xcd_groups);
   const GemmProb& P = probs[find_prob(probs, U.nprob, t)];
   uint32_t tm, tn;
   tile_coords(t - P.tile_start, (uint32_t)((P.M + BBM - 1) / BBM), P.tiles_n, tm, tn);
@@ -736,7 +736,7 @@ __global__ __launch_bounds__(FNT, BT == 64 ? 4 : 2) void k_gemm_f32(const GemmPr
   constexpr bool BTR = (BMODE == B_NC);
   __shared__ __attribute__((aligned(16))) float As[2][AT ? BK * F_LDT : BT * F_LDK];
   __shared__ __attribute__((aligned(16))) float Bs[2][BTR ? BK * F_LDT : BT * F_LDK];
-  const uint32_t t = U.xcd_groups ? xcd_remap_groups(blockIdx.x, gridDim.x) : xcd_remap(blockIdx.x, gridDim.x);
+  const uint32_t t = xcd_remap_list(blockIdx.x, gridDim.x, U.xcd_groups);
   const GemmProb& P = probs[find_prob(probs, U.nprob, t)];
   uint32_t tm, tn;
   tile_coords(t - P.tile_start, (uint32_t)((P.M + BT - 1) / BT), P.tiles_n, tm, tn);
@@ -784,9 +784,9 @@ int gemm_f32_fit(GemmProb* probs, int n, uint32_t* total) {
     return hipGetLastError();                                                                                            \
   }
 
-bool gemm_xcd_groups(const std::vector<GemmProb>& list, uint32_t total) {
+bool gemm_xcd_groups(const std::vector<GemmProb>& list, uint32_t total, int ep) {
   constexpr uint32_t X = 8;
-  constexpr double EPILOGUE_K = 256, UNEVEN = 1.03;
+  constexpr double EPILOGUE_K = 256, UNEVEN = 1.03, SMALL_K = 512;
   const uint32_t per = total / X, rem = total % X;
   double work[X] = {}, all = 0;
   uint32_t x = 0, end = per + (rem > 0);   // the eighth that tile t lies in ends at tile `end`
@@ -801,6 +801,7 @@ bool gemm_xcd_groups(const std::vector<GemmProb>& list, uint32_t total) {
     }
     all += cost * (stop - list[i].tile_start);
   }
+  if (ep == EP_UPDATE && all < (EPILOGUE_K + SMALL_K) * total) return true;
   double most = 0;
   for (double w : work) most = w > most ? w : most;
   return most * X > UNEVEN * all;
@@ -812,7 +813,7 @@ hipError_t launch_gemm(int kind, int amode, int bmode, int ep, const GemmProb* p
   if (total_tiles == 0 || list.empty()) return hipSuccess;
   GemmUniform u = u0;
   u.nprob = (int)list.size();
-  u.xcd_groups = gemm_xcd_groups(list, total_tiles);
+  u.xcd_groups = (tile == 64 && ep != EP_ALIGN) || gemm_xcd_groups(list, total_tiles, ep);
   u.lgB = (u.B > 0 && (u.B & (u.B - 1)) == 0) ? __builtin_ctz(u.B) : -1;
   const dim3 grid(total_tiles);
   if (kind == KIND_BF16) {

@@ -111,7 +111,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, (OCC * NWM * NWN + 3) / 4) void k_g
   constexpr int OPS = SA + SB;                        // DMA instructions per wave per stage
   constexpr int SMEM = NS * STAGEB > NW * EPWAVE * 4 ? NS * STAGEB : NW * EPWAVE * 4;
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
-  const uint32_t t = U.xcd_groups ? xcd_remap_groups(blockIdx.x, gridDim.x) : xcd_remap(blockIdx.x, gridDim.x);
+  const uint32_t t = xcd_remap_list(blockIdx.x, gridDim.x, U.xcd_groups);
   const GemmProb& P = probs[find_prob(probs, U.nprob, t)];
   uint32_t tm, tn;
   // the projection walks two tile rows per group (measured 1.6 % faster than eight on the
@@ -629,7 +629,7 @@ hipError_t launch_gemm_nt(int ep, const GemmProb* probs_dev, const std::vector<G
   if (total_tiles == 0 || list.empty()) return hipSuccess;
   GemmUniform u = u0;
   u.nprob = (int)list.size();
-  u.xcd_groups = narrow || ep == EP_STORE || ep == EP_STORE_BF16 || gemm_xcd_groups(list, total_tiles);
+  u.xcd_groups = ep == EP_STORE || ep == EP_STORE_BF16 || gemm_xcd_groups(list, total_tiles, ep);
   if (narrow) {
     if (ep != EP_UPDATE) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_gemm_nt<EP_UPDATE, 4, NARROW_BN / 64, 64, 3, 2>), dim3(total_tiles), dim3(256 * NARROW_BN / 64), 0, st,

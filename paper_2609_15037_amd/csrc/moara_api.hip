@@ -218,8 +218,8 @@ int32_t subspace_width(const moara_config& c, int64_t s, int32_t r) {
 // free. The limits are the block sizes a lane group can reduce (without the decomposition V
 // is G itself and any B does), the row-major decomposition's LDS and the GEMM's 32-bit buffer
 // extents. With 128 x 128 tiles that form V while staging it (before, for these sizes) six
-// d = 1000, ffn = 2666 layers took 938 us a step and now take 403, six d = 1024 layers without
-// the decomposition 422 and now 351.
+// d = 1000, ffn = 2666 layers took 938 us a step, with this path 403 (341 with the one-pass kernel
+// and the update's narrow tiles), six d = 1024 layers without the decomposition 422, 351 and 254.
 int64_t pad32(int64_t x) { return (x + 31) / 32 * 32; }
 bool vpath_shape_ok(const moara_config& c, int64_t m, int64_t n, int side, int32_t r) {
   if (c.operand_dtype != MOARA_BF16) return false;
