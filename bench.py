@@ -71,8 +71,15 @@ def v_path(wl, m, operand: str) -> bool:
         return False
     r = wl.rank_of(m)
     s, L = min(m.rows, m.cols), max(m.rows, m.cols)
+    if s < 32 and not _one_pass_shape(wl, m):
+        return False
     up = lambda x: -(-x // 32) * 32
     return max(2 * L * up(s), 2 * L * up(r), 2 * s * up(r), 2 * m.rows * m.cols) < 2 ** 31
+
+
+def _one_pass_shape(wl, m) -> bool:
+    return (wl.rank_of(m) <= 256 and m.cols >= 4 and wl.block_size in (32, 64, 128)
+            and 4 * m.rows * m.cols < 2 ** 31)
 
 
 def one_pass(wl, operand: str, mask=None):
@@ -82,8 +89,7 @@ def one_pass(wl, operand: str, mask=None):
     fits, tiles, others = [], 0, False
     for i, m in enumerate(wl.matrices):
         on = mask is None or bool(mask[i])
-        f = (on and v_path(wl, m, operand) and wl.rank_of(m) <= 256 and min(m.rows, m.cols) >= 32
-             and wl.block_size in (32, 64, 128) and 4 * m.rows * m.cols < 2 ** 31)
+        f = on and v_path(wl, m, operand) and _one_pass_shape(wl, m)
         fits.append(f)
         others = others or (on and not f)
         if f:

@@ -380,8 +380,9 @@ __global__ __launch_bounds__(256) void k_opt_m(const FusedProb* __restrict__ pro
 
 }  // namespace
 
-bool decproj_fits(int64_t m, int64_t n, int32_t r, int B, bool decompose) {
-  if (r > 256 || n < 32 || m < 32 || 4 * m * n > 0x7FFFFFFFLL) return false;
+bool decproj_fits(int64_t m, int64_t n, int64_t s, int32_t r, int B, bool decompose) {
+  if (r > 256 || n < 4 || 4 * m * n > 0x7FFFFFFFLL) return false;   // four columns per load
+  if (s >= 32 && (m < 32 || n < 32)) return false;   // projected onto the long side: one tile, all of K
   return !decompose || B == 32 || B == 64 || B == 128;
 }
 uint32_t decproj_tiles(int side, int64_t L) {

@@ -124,7 +124,7 @@ struct FusedProb {
   uint32_t pad_;
 };
 constexpr uint32_t DECPROJ_MIN_TILES = 512;   // two workgroups on each of the 256 CUs
-bool decproj_fits(int64_t m, int64_t n, int32_t r, int B, bool decompose);
+bool decproj_fits(int64_t m, int64_t n, int64_t s, int32_t r, int B, bool decompose);
 uint32_t decproj_tiles(int side, int64_t L);
 uint32_t opt_m_tiles(int64_t mk);
 struct GemmUniform;

@@ -229,6 +229,11 @@ bool vpath_shape_ok(const moara_config& c, int64_t m, int64_t n, int side, int32
     if (side == MOARA_SIDE_RIGHT && (n + B - 1) / B > DEC_ROW_MAX_K) return false;
   }
   const int64_t s = side == MOARA_SIDE_LEFT ? m : n, L = side == MOARA_SIDE_LEFT ? n : m;
+  // a projected side below 32 pays in the one-pass kernel only: the transposed decomposition has a
+  // workgroup per 32 rows, and a K panel of mostly padding (steps of one bf16 matrix, fallback /
+  // two kernels / one pass: 16 x 4096 48, 84, 37 us, 4096 x 16 38, 49, 34; without the decomposition
+  // the fallback reads G in a single launch, 27, 82, 33 and 25, 50, 29)
+  if (s < 32 && !(c.decompose && decproj_fits(m, n, s, r, B, true))) return false;
   const int64_t lim = 0x7FFFFFFFLL;
   return 2 * L * pad32(s) <= lim && 2 * L * pad32(r) <= lim && 2 * s * pad32(r) <= lim && 2 * m * n <= lim;
 }
@@ -250,7 +255,9 @@ std::vector<char> needs_v(const moara_config& c, const moara_matrix_desc* descs,
   bool all_fit = !c.decompose;
   for (int i = 0; i < n; ++i) {
     v[i] = vpath_shape_ok(c, descs[i].rows, descs[i].cols, sides[i], ranks[i]);
-    all_fit = all_fit && v[i] && decproj_fits(descs[i].rows, descs[i].cols, ranks[i], c.block_size, false);
+    all_fit = all_fit && v[i] && decproj_fits(descs[i].rows, descs[i].cols,
+                                           sides[i] == MOARA_SIDE_LEFT ? descs[i].rows : descs[i].cols, ranks[i],
+                                           c.block_size, false);
   }
   if (all_fit) std::fill(v.begin(), v.end(), 0);
   return v;
@@ -1879,7 +1886,7 @@ static int step_impl(moara_state* st, void* const* weights, const void* const* g
     uint32_t ftiles = 0;
     for (int i : idx) {
       const MatHost& h = st->mats[i];
-      const bool f = h.vpath && !(dec && due[i]) && decproj_fits(h.m, h.n, h.r, st->cfg.block_size, dec);
+      const bool f = h.vpath && !(dec && due[i]) && decproj_fits(h.m, h.n, h.s, h.r, st->cfg.block_size, dec);
       (f ? fused : split).push_back(i);
       if (f) ftiles += decproj_tiles(h.side, h.L);
     }

@@ -72,6 +72,32 @@ FUSED = [(32, 128, WL.Q), (129, 32, WL.GATE), (96, 257, WL.K), (127, 128, WL.V),
 FUSED_RANKS = [1, 31, 33, 64, 100, 97, 256, 255, 129]
 
 
+# fewer rows or columns than a panel: the one-pass kernel down to four columns, below that (and at
+# other block sizes) the 128-row kernels
+THIN = [(16, 4096, WL.Q), (4096, 16, WL.GATE), (5, 700, WL.K), (700, 5, WL.UP), (3, 64, WL.V), (64, 3, WL.O),
+        (1, 300, WL.DOWN), (300, 1, WL.GATE), (4, 4, WL.Q), (31, 129, WL.K), (65, 31, WL.UP)]
+THIN_RANKS = [16, 9, 5, 3, 2, 3, 1, 1, 4, 31, 30]
+
+
+@pytest.mark.parametrize("B,wdt,mom", [(32, "bf16", "bf16"), (64, "f32", "f32"), (128, "bf16", "f32"),
+                                       (16, "f32", "bf16"), (256, "bf16", "f32")])
+def test_thin_matrices_from_a_restored_state(B, wdt, mom):
+    # bf16 moments are held to 99 % equal bits; sums of four products or fewer have so few bits that
+    # 0.9 e + 0.1 R meets midpoints of bf16 exactly, which the library's fp32 beta1 breaks otherwise
+    # than the oracle's fp64 one (3 x 64: 2 of 128 moments within 6e-15 of a midpoint)
+    keep = [i for i, (m, n, _) in enumerate(THIN) if mom == "f32" or min(m, n) > 4]
+    c = Case(shapes=[THIN[i] for i in keep], ranks=[THIN_RANKS[i] for i in keep], block_size=B, operand_dtype="bf16",
+             weight_dtype=wdt, moment_dtype=mom, weight_std=1e-2 if wdt == "bf16" else 1e-5)
+    history_parity(c, 2, 430 + B, _grad(c, 430 + B))
+
+
+@pytest.mark.parametrize("misalign", [False, True])
+def test_thin_matrices_without_the_decomposition(misalign):
+    c = Case(shapes=THIN, ranks=THIN_RANKS, block_size=64, operand_dtype="bf16", weight_dtype="bf16", weight_std=0.02,
+             decompose=False)
+    step_parity(c, 2, misalign=misalign)
+
+
 @pytest.mark.parametrize("B,wdt,mom", [(32, "bf16", "bf16"), (64, "f32", "f32"), (128, "bf16", "f32"),
                                        (128, "f32", "bf16")])
 def test_one_pass_projection_from_a_restored_state(B, wdt, mom):
@@ -105,8 +131,8 @@ def test_padding_stays_zero_when_the_decomposition_epsilon_is_zero(two_pass, eps
     history_parity(c, 2, 330, _grad(c, 330))
 
 
-@pytest.mark.parametrize("block", [64, 256])
-def test_one_pass_and_two_pass_projection_are_bit_identical(block):
+@pytest.mark.parametrize("block,thin", [(64, False), (256, False), (64, True)])
+def test_one_pass_and_two_pass_projection_are_bit_identical(block, thin):
     """A matrix whose rank exceeds the one-pass kernel's range sends a short list of matrices through
     the two-pass kernels, and its update through 256-column tiles: the same matrices give the same
     bits with and without it beside them. Blocks of 256 columns take the two-pass kernels either
@@ -115,7 +141,7 @@ def test_one_pass_and_two_pass_projection_are_bit_identical(block):
     import torch
     from paper_2609_15037_amd import moara as M
     from tests.harness import gpu_state, rng, to_dev
-    shapes, ranks = FUSED, FUSED_RANKS
+    shapes, ranks = (THIN, THIN_RANKS) if thin else (FUSED, FUSED_RANKS)
     big, rbig = (300, 320, WL.V), 257
     out = []
     for extra in (False, True):
