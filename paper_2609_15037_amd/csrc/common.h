@@ -42,6 +42,8 @@ struct MatDev {
   int32_t n_kp;        // ... in the blocked layout kp_index(l, j, L)
   int32_t mom_bf16;    // zero-gradient step: exp1 / exp2 hold bf16 values
   int32_t ldr;         // row stride of exp1 / exp2
+  int32_t parts;       // transposed decomposition: column parts of a row group, one workgroup each
+  int32_t pad_;
 };
 
 struct StepParams {
@@ -158,9 +160,12 @@ hipError_t launch_cast(const CastList& l, uint32_t total, hipStream_t st);
 // Optimizer_M.
 bool decompose_plain(const float* G, int64_t n, int k, bool decompose, bool transposed);
 hipError_t launch_decompose(const MatDev* mats_dev, const StepParams& p, int adam_m, bool plain, hipStream_t st);
-hipError_t launch_decompose_vt(const MatDev* mats_dev, const StepParams& p, int adam_m, bool plain, hipStream_t st);
+// split: some matrix of the list has parts > 1
+hipError_t launch_decompose_vt(const MatDev* mats_dev, const StepParams& p, int adam_m, bool plain, bool split,
+                               hipStream_t st);
 int decompose_tiles(int64_t m);
-int decompose_vt_tiles(int64_t m);
+int decompose_vt_tiles(int64_t m);          // row groups; times MatDev::parts workgroups
+int decompose_vt_max_parts(int64_t n);
 // Optimizer_M and Optimizer_V of a matrix whose gradient is exactly zero (no G is read):
 // magnitude moments -> dM (when p.decompose), direction moments -> N; tile_dec holds the
 // matrix's first workgroup, zero_grad_tiles(...) workgroups per matrix.

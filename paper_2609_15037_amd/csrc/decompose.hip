@@ -211,7 +211,8 @@ __global__ __launch_bounds__(256) void k_decompose(const MatDev* __restrict__ ma
 // row groups read by one instruction on distinct banks. Optimizer_M then runs over the
 // VT_ROWS x k sums as in k_decompose. 32-row slabs (143 VGPRs, three waves per SIMD)
 // measured 1.7 % faster than 64-row ones (231 VGPRs, two). The sums of DEC_VT_MAX_K blocks per
-// row fit in LDS; longer rows run in column ranges of that many blocks. Rows past m are zero in
+// row fit in LDS; longer rows run in column ranges of that many blocks. SPLIT: a row group's columns
+// go to MatDev::parts workgroups (short lists, whose few row groups would each walk all columns). Rows past m are zero in
 // the last K panel. Preconditions (checked by the host): B a power of two in [4, 256], or no
 // decomposition (V = G); PLAIN: decompose_plain.
 #ifndef DEC_VT_ROWS
@@ -222,14 +223,15 @@ constexpr int VT_RPW = VT_ROWS / 4;    // rows per wave
 constexpr int VT_GRP = VT_ROWS / 8;    // 8-row groups of a column (16-byte output runs)
 static_assert(VT_ROWS % 32 == 0, "whole 32-row K panels of the blocked output");
 
-template <bool PLAIN>
+template <bool PLAIN, bool SPLIT>
 __global__ __launch_bounds__(256) void k_decompose_vt(const MatDev* __restrict__ mats, StepParams p, int adam_m) {
   __shared__ float sums[VT_ROWS * DEC_VT_MAX_K];
   __shared__ __attribute__((aligned(16))) bf16 T[VT_ROWS * VT_PITCH];
   const uint32_t t = blockIdx.x;
   const int mi = find_mat(mats, p.nmat, t, [](const MatDev& d) { return d.tile_dec; });
   const MatDev d = mats[mi];
-  const int64_t row0 = (int64_t)(t - d.tile_dec) * VT_ROWS;
+  const uint32_t lt = t - d.tile_dec, parts = SPLIT ? (uint32_t)d.parts : 1u;
+  const int64_t row0 = (int64_t)(lt / parts) * VT_ROWS;
   const int rows = (int)((d.m - row0 < VT_ROWS) ? d.m - row0 : VT_ROWS);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const bool dec = PLAIN || p.decompose != 0;
@@ -285,14 +287,19 @@ __global__ __launch_bounds__(256) void k_decompose_vt(const MatDev* __restrict__
       block_out(d, p, row0 + rr, kc0 + j, sums[e], adam_m);
     }
   };
-  load(0, va);
+  // this workgroup's columns: whole slabs, parts of equal length but for the last ones
+  const int64_t len = SPLIT ? ((n + VT_COLS - 1) / VT_COLS + parts - 1) / parts * VT_COLS : n;
+  const int64_t cb = lt % parts * len, cend = cb + len < n ? cb + len : n;
+  if (SPLIT && cb >= cend) return;
+  load(cb, va);
   if (PLAIN) {
-    kc = k;
-    for (int64_t c0 = 0; c0 < n; c0 += 2 * VT_COLS) {
-      if (c0 + VT_COLS < n) load(c0 + VT_COLS, vb);
+    kc0 = (int)(cb >> lgB);
+    kc = (int)((cend + B - 1) >> lgB) - kc0;
+    for (int64_t c0 = cb; c0 < cend; c0 += 2 * VT_COLS) {
+      if (c0 + VT_COLS < cend) load(c0 + VT_COLS, vb);
       process(c0, va);
-      if (c0 + VT_COLS >= n) break;
-      if (c0 + 2 * VT_COLS < n) load(c0 + 2 * VT_COLS, va);
+      if (c0 + VT_COLS >= cend) break;
+      if (c0 + 2 * VT_COLS < cend) load(c0 + 2 * VT_COLS, va);
       process(c0 + VT_COLS, vb);
     }
     adam_m_blocks();
@@ -300,19 +307,19 @@ __global__ __launch_bounds__(256) void k_decompose_vt(const MatDev* __restrict__
   }
   // column ranges of at most DEC_VT_MAX_K blocks, whole slabs (B divides VT_COLS)
   const int64_t span = dec ? (int64_t)DEC_VT_MAX_K * B / VT_COLS * VT_COLS : n;
-  for (int64_t cr = 0; cr < n; cr += span) {
-    const int64_t ce = cr + span < n ? cr + span : n;
+  for (int64_t cr = cb; cr < cend; cr += span) {
+    const int64_t ce = cr + span < cend ? cr + span : cend;
     kc0 = (int)(cr >> lgB);
     kc = (int)((ce + B - 1) >> lgB) - kc0;
     for (int64_t c0 = cr; c0 < ce; c0 += 2 * VT_COLS) {
-      if (c0 + VT_COLS < n) load(c0 + VT_COLS, vb);
+      if (c0 + VT_COLS < cend) load(c0 + VT_COLS, vb);
       process(c0, va);
       if (c0 + VT_COLS >= ce) {   // odd number of slabs: the next range starts with vb's columns
 #pragma unroll
         for (int i = 0; i < VT_RPW; ++i) va[i] = vb[i];
         break;
       }
-      if (c0 + 2 * VT_COLS < n) load(c0 + 2 * VT_COLS, va);
+      if (c0 + 2 * VT_COLS < cend) load(c0 + 2 * VT_COLS, va);
       process(c0 + VT_COLS, vb);
     }
     if (!dec) break;
@@ -428,15 +435,23 @@ hipError_t launch_zero_grad(const MatDev* mats_dev, const StepParams& p, hipStre
 
 int decompose_tiles(int64_t m) { return (int)((m + DEC_ROWS - 1) / DEC_ROWS); }
 int decompose_vt_tiles(int64_t m) { return (int)((m + VT_ROWS - 1) / VT_ROWS); }
+int decompose_vt_max_parts(int64_t n) {   // two slabs a part: the second one's loads run under the first
+  const int64_t slabs = (n + VT_COLS - 1) / VT_COLS;
+  return slabs < 4 ? 1 : slabs < 0x10000 ? (int)(slabs / 2) : 0x8000;
+}
 
 bool decompose_plain(const float* G, int64_t n, int k, bool decompose, bool transposed) {
   return decompose && (n & 3) == 0 && ((uintptr_t)G & 15) == 0 && (!transposed || k <= DEC_VT_MAX_K);
 }
 
-hipError_t launch_decompose_vt(const MatDev* mats_dev, const StepParams& p, int adam_m, bool plain, hipStream_t st) {
+hipError_t launch_decompose_vt(const MatDev* mats_dev, const StepParams& p, int adam_m, bool plain, bool split,
+                               hipStream_t st) {
   if (p.total_dec == 0) return hipSuccess;
-  if (plain) hipLaunchKernelGGL((k_decompose_vt<true>), dim3(p.total_dec), dim3(256), 0, st, mats_dev, p, adam_m);
-  else hipLaunchKernelGGL((k_decompose_vt<false>), dim3(p.total_dec), dim3(256), 0, st, mats_dev, p, adam_m);
+  const dim3 g(p.total_dec), b(256);
+  if (plain && !split) hipLaunchKernelGGL((k_decompose_vt<true, false>), g, b, 0, st, mats_dev, p, adam_m);
+  else if (plain) hipLaunchKernelGGL((k_decompose_vt<true, true>), g, b, 0, st, mats_dev, p, adam_m);
+  else if (!split) hipLaunchKernelGGL((k_decompose_vt<false, false>), g, b, 0, st, mats_dev, p, adam_m);
+  else hipLaunchKernelGGL((k_decompose_vt<false, true>), g, b, 0, st, mats_dev, p, adam_m);
   return hipGetLastError();
 }
 

@@ -478,6 +478,7 @@ struct DecPlan {
   // four lists: row-major and transposed V, each split into plain and other matrices
   std::vector<MatDev> md[4];
   uint32_t tiles[4] = {0, 0, 0, 0};
+  bool split[4] = {};   // a transposed list whose matrices run in column parts
   size_t off[4] = {};
   int stage(Stager& sg) {
     for (int q = 0; q < 4; ++q)
@@ -487,6 +488,7 @@ struct DecPlan {
   }
 };
 
+constexpr uint32_t DEC_VT_WGS = 768;   // workgroups of the transposed decomposition at once: three per CU
 DecPlan plan_decompose(const moara_state* st, const std::vector<int>& idx, const void* const* grads,
                        const std::vector<char>* usev) {
   DecPlan P;
@@ -507,9 +509,24 @@ DecPlan plan_decompose(const moara_state* st, const std::vector<int>& idx, const
     d.Vb = wv ? (bf16*)h.V : nullptr;
     d.vt = vt ? 1 : 0;
     const int q = 2 * (vt ? 1 : 0) + (decompose_plain(d.G, h.n, h.k, st->cfg.decompose != 0, vt) ? 0 : 1);
-    d.tile_dec = tiles[q];
+    d.parts = 1;
     tiles[q] += (uint32_t)(vt ? decompose_vt_tiles(h.m) : decompose_tiles(h.m));
     md[q].push_back(d);
+  }
+  // A transposed list of fewer row groups than run at once is split by columns too (a step, without
+  // and with: 300 x 20000 at rank 260, ten groups, 331 -> 89 us; 33 x 50000 with B = 256, two, 745 -> 52;
+  // 4096 x 4096 at rank 1024 without the decomposition, 128, 211 -> 186); longer lists run the kernel
+  // without it, which keeps 12 registers fewer (736 groups: 321 against 330 us).
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t rows = tiles[q];
+    tiles[q] = 0;
+    for (MatDev& d : md[q]) {
+      if (q >= 2 && rows < DEC_VT_WGS)
+        d.parts = std::min(decompose_vt_max_parts(d.n), (int)(DEC_VT_WGS / rows));
+      P.split[q] = P.split[q] || d.parts > 1;
+      d.tile_dec = tiles[q];
+      tiles[q] += (uint32_t)(q >= 2 ? decompose_vt_tiles(d.m) * d.parts : decompose_tiles(d.m));
+    }
   }
   return P;
 }
@@ -524,7 +541,7 @@ int launch_plan(moara_state* st, const DecPlan& P, bool adam_m, hipStream_t stre
     p.total_dec = P.tiles[q];
     const MatDev* dev = (const MatDev*)(st->dev_arena + P.off[q]);
     const bool plain = (q & 1) == 0;
-    HIP_TRY(q >= 2 ? launch_decompose_vt(dev, p, adam_m ? 1 : 0, plain, stream)
+    HIP_TRY(q >= 2 ? launch_decompose_vt(dev, p, adam_m ? 1 : 0, plain, P.split[q], stream)
                    : launch_decompose(dev, p, adam_m ? 1 : 0, plain, stream));
   }
   return MOARA_OK;

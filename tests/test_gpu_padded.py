@@ -245,6 +245,34 @@ def test_bf16_gradients_step_as_their_fp32_copies(case):
             assert np.array_equal(x, y), f"matrix {i}: a moment or the projector differs"
 
 
+@pytest.mark.parametrize("block,decompose", [(16, True), (64, True), (256, True), (64, False)])
+def test_transposed_decomposition_split_by_columns_gives_the_same_bits(block, decompose):
+    """A LEFT matrix's two-pass step alone, its decomposition split over column parts, and in a list
+    of enough row groups to run without the split; rows of more blocks than the kernel holds at once
+    (B = 16), widths that leave the last part short or empty."""
+    import numpy as np
+    import torch
+    from paper_2609_15037_amd import moara as M
+    from tests.harness import assert_same_state, gpu_state, rng, to_dev
+    few = [(300, 5001, WL.Q), (259, 4096, WL.K), (257, 2305, WL.V), (289, 1025, WL.O)]
+    shapes = few + [(320, 640, WL.DOWN)] * 76   # ten row groups of 32 each
+    c = Case(shapes=shapes, ranks=[257] * len(shapes), block_size=block, operand_dtype="bf16", weight_dtype="bf16",
+             moment_dtype="bf16", decompose=decompose)
+    out = []
+    for alone in (False, True):
+        st = gpu_state(c)
+        W = [to_dev(0.02 * rng(10, 1, i % 5).standard_normal(s[:2]), "bf16") for i, s in enumerate(shapes)]
+        G = [to_dev(rng(10, 2, i % 5).standard_normal(s[:2]), "f32") for i, s in enumerate(shapes)]
+        for i, (m, n, _) in enumerate(shapes):
+            M.moara_set_tensor(st, i, M.MOARA_T_P, np.eye(m, 257, dtype=np.float32) + 0.01)
+        for one in (range(len(few)) if alone else [None]):
+            M.moara_step(st, W, G, lr=1e-2, active=None if one is None else [j == one for j in range(len(shapes))])
+        torch.cuda.synchronize()
+        out.append((st, W))
+    (sa, Wa), (sb, Wb) = out
+    assert_same_state(M, sa, sb, Wa, Wb, range(len(few)))
+
+
 def test_fp32_tiles_of_either_size_give_the_same_bits():
     """fp32 operands: lists of more than 4096 tiles of 128 x 128 run on those, shorter ones on 64 x 64
     tiles. Matrices stepped all at once (both projections and the update past the line) and one by one."""
