@@ -258,7 +258,7 @@ __global__ __launch_bounds__(256) void k_decompose_vt(const MatDev* __restrict__
       ss = group_sum(ss, gl);
       if (dec && rr < rows && c < n && (lane & (gl - 1)) == 0) sums[rr * kc + (int)(c >> lgB) - kc0] = ss;
       // rows past m are K padding of V and have to stay zero, also where 1 / (0 + eps_d) is infinite
-      const float inv = !dec ? 1.0f : rr < rows ? 1.0f / (sqrtf(ss) + p.decomp_eps) : 0.0f;
+      const float scale = dec ? 1.0f / (sqrtf(ss) + p.decomp_eps) : 1.0f, inv = rr < rows ? scale : 0.0f;
       bf16x2 a, b;
       a[0] = f2bf(v[i].x * inv); a[1] = f2bf(v[i].y * inv);
       b[0] = f2bf(v[i].z * inv); b[1] = f2bf(v[i].w * inv);

@@ -238,7 +238,7 @@ __global__ __launch_bounds__(FNT, 4) void k_decproj(const FusedProb* __restrict_
       inv = 1.0f / (sqrtf(sel) + U.decomp_eps);
       // LEFT: gradient rows past m are K padding and have to stay zero, also where eps_d is so
       // small that 1 / (0 + eps_d) is infinite
-      if (left && !inside(c) && row_of(c, tf) + row_s * us >= m) inv = 0.f;
+      if (left && L_KC * (c + 1) > m && row_of(c, tf) + row_s * us >= m) inv = 0.f;
     }
     const int grp = ((tf & 63) - us) << 2;   // byte address of the group's first lane
     auto scale = [&](int u) {
